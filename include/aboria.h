@@ -379,7 +379,7 @@ aboria_status aboria_dense_sum_noalloc(aboria_ctx* ctx, aboria_dtype dtype, abor
  * for K = phi(q), q = |xt_i - xs_j|^2.  When targets and sources are the same
  * points, dL/dx = gxt + gxs.  Each output may be NULL (not computed); all are
  * overwritten, in dtype, and must not overlap the inputs or each other.  gw and
- * gxs come from one pass over the pairs, gxt from a second.  Uses
+ * gxs come from one pass over the pairs, gxt from a second (all three requested: in one launch).  Uses
  * the same grow-only scratch as the forward (a first call of a size must not
  * be captured).  Errors as for aboria_dense_sum. */
 aboria_status aboria_dense_sum_backward(aboria_ctx* ctx, aboria_dtype dtype, aboria_kernel kernel,
@@ -440,7 +440,7 @@ aboria_status aboria_autotune_cells(aboria_ctx* ctx, aboria_dtype dtype, int32_t
                                     const void* gy, int32_t ny, aboria_box* boxes_out, double* factor_host);
 
 /* Dense-sum launch tuning (Sections 1 and 1.1, the kernel sums of
- * aboria_dense_sum): times the launch plans -- targets kept per lane (2, 4, or
+ * aboria_dense_sum): times the launch plans -- targets kept per lane (1, 2, 4, or
  * for float 8) and the number of workgroups the source split aims for (1024,
  * 2048, 4096) -- of aboria_dense_sum (gy == NULL) or of
  * aboria_dense_sum_backward computing all three gradients (gy given) on the
@@ -460,7 +460,7 @@ aboria_status aboria_autotune_dense(aboria_ctx* ctx, aboria_dtype dtype, aboria_
 /* Name of a dense launch plan ("" when out of range); static storage. */
 const char* aboria_dense_plan_name(int32_t plan);
 /* Forces dense launch plan `plan` for later dense sums on ctx (-1: the tuned
- * choice, else plan 0); a float-only plan runs plan 0 in float64.
+ * choice, else a rule on the number of pairs); a float-only plan runs plan 0 in float64.
  * INVALID_ARG for an unknown plan. */
 aboria_status aboria_set_dense_plan(aboria_ctx* ctx, int32_t plan);
 

@@ -26,7 +26,8 @@
 namespace aboria {
 
 constexpr int kDenseBlock = 256;
-constexpr int kDenseTile = 256;
+constexpr int kDenseTile = 256;  // sources staged in LDS at once
+constexpr int kDenseStep = 64;   // the source splits' granularity
 
 // Scratch of aboria_dense_sum_noalloc: its split partial sums live in this
 // file-scope device array (each GPU holds its own copy until the process ends)
@@ -45,21 +46,28 @@ __device__ __forceinline__ double ksqrt(double a) { return ::sqrt(a); }
 __device__ __forceinline__ float krsqrt(float a) { return __builtin_amdgcn_rsqf(a); }
 __device__ __forceinline__ double krsqrt(double a) { return ::rsqrt(a); }
 
-// phi of the kernel on its working coordinates (value) and the factor of the
-// gradient summand w_j * slope * (a - b) (the constant 2 phi' / slope is
-// applied by the reduction): Gaussian value = slope = exp(-q') on coordinates
-// scaled by sqrt(c); multiquadric value = sqrt(q + c^2) and slope =
-// 1/sqrt(q + c^2), each one transcendental instruction, so a pass needing both
-// computes the value exactly as the forward does.
-template <typename T, int KERN>
+// The radial argument q of a pair (displacement dk on the working coordinates), phi(q)
+// (value) and the factor of the gradient summand w_j * slope * (a - b) (the constant
+// 2 phi' / slope is applied by the reduction): Gaussian q = |dk|^2 on coordinates scaled
+// by sqrt(c), value = slope = exp(-q); multiquadric q = |dk|^2 + c^2 (c^2 starts the
+// multiply-add chain, one addition less per pair), value = sqrt(q) and slope =
+// 1/sqrt(q), each one transcendental instruction, so a pass needing both computes the
+// value exactly as the forward does.
+template <typename T, int D, int KERN>
 struct Radial {
-    __device__ __forceinline__ static T value(T q, T c2) {
-        if constexpr (KERN == ABORIA_K_GAUSSIAN) return kexp(q);
-        else return ksqrt(q + c2);
+    __device__ __forceinline__ static T arg(const T* dk, T c2) {
+        T q = KERN == ABORIA_K_GAUSSIAN ? dk[0] * dk[0] : kfma(dk[0], dk[0], c2);
+        if constexpr (D >= 2) q = kfma(dk[1], dk[1], q);
+        if constexpr (D >= 3) q = kfma(dk[2], dk[2], q);
+        return q;
     }
-    __device__ __forceinline__ static T slope(T q, T c2) {
+    __device__ __forceinline__ static T value(T q) {
         if constexpr (KERN == ABORIA_K_GAUSSIAN) return kexp(q);
-        else return krsqrt(q + c2);
+        else return ksqrt(q);
+    }
+    __device__ __forceinline__ static T slope(T q) {
+        if constexpr (KERN == ABORIA_K_GAUSSIAN) return kexp(q);
+        else return krsqrt(q);
     }
 };
 
@@ -74,15 +82,28 @@ enum DenseMode { kSum = 0, kGrad = 1, kSumGrad = 2 };
 template <int MODE, int D>
 constexpr int dense_out() { return MODE == kSum ? 1 : (MODE == kGrad ? D : D + 1); }
 
+// One pass: targets, sources and weights, the sources of a split (a multiple of
+// kDenseStep) and where the split partials go.
+template <typename T>
+struct DenseJob {
+    const T* xt;
+    const T* xs;
+    const T* w;
+    T* part;
+    uint32_t nt, ns, jchunk, tblocks;
+};
+
+// Target block tb of the pass against the sources of split `split`: what bounds
+// it is the issue of the per-pair VALU instructions (6.1 slots per pair for the
+// 2-d Gaussian at 65536 points, 0.68 ms), so a source is read once per TI
+// targets.  A split may be shorter than a tile: only the tile's filled part,
+// rounded up to the unroll (zero weights), is walked.
 template <typename T, int D, int TI, int KERN, int MODE>
-__global__ __launch_bounds__(kDenseBlock) void k_dense(const T* __restrict__ xt, uint32_t nt,
-                                                       const T* __restrict__ xs, const T* __restrict__ w,
-                                                       uint32_t ns, T sc, T c2, uint32_t jchunk,
-                                                       T* __restrict__ ypart) {
+__device__ __forceinline__ void dense_block(const DenseJob<T>& jb, T sc, T c2, uint32_t tb, uint32_t split,
+                                            VecN<T, 4>* tile) {
+    using R = Radial<T, D, KERN>;
     constexpr int OUT = dense_out<MODE, D>();
-    __shared__ VecN<T, 4> tile[kDenseTile];
-    const uint32_t tb = xcd_tile(blockIdx.x, gridDim.x);
-    const uint32_t split = blockIdx.y;
+    const uint32_t nt = jb.nt;
     T xi[TI][D];
     T acc[TI][OUT];
 #pragma unroll
@@ -90,12 +111,12 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense(const T* __restrict__ xt,
         const uint32_t t = tb * (kDenseBlock * TI) + q * kDenseBlock + threadIdx.x;
         const uint32_t tc = t < nt ? t : nt - 1;
 #pragma unroll
-        for (int k = 0; k < D; ++k) xi[q][k] = xt[(size_t)tc * D + k] * sc;
+        for (int k = 0; k < D; ++k) xi[q][k] = jb.xt[(size_t)tc * D + k] * sc;
 #pragma unroll
         for (int k = 0; k < OUT; ++k) acc[q][k] = T(0);
     }
-    const uint32_t jbeg = split * jchunk;
-    const uint32_t jend = min(ns, jbeg + jchunk);
+    const uint32_t jbeg = split * jb.jchunk;
+    const uint32_t jend = min(jb.ns, jbeg + jb.jchunk);
     for (uint32_t j0 = jbeg; j0 < jend; j0 += kDenseTile) {
         __syncthreads();
         {
@@ -104,8 +125,8 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense(const T* __restrict__ xt,
             v.v[0] = v.v[1] = v.v[2] = v.v[3] = T(0);
             if (j < jend) {
 #pragma unroll
-                for (int k = 0; k < D; ++k) v.v[k] = xs[(size_t)j * D + k] * sc;
-                v.v[3] = w[j];
+                for (int k = 0; k < D; ++k) v.v[k] = jb.xs[(size_t)j * D + k] * sc;
+                v.v[3] = jb.w[j];
             }
             tile[threadIdx.x] = v;
         }
@@ -115,34 +136,28 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense(const T* __restrict__ xt,
         for (int q = 0; q < TI; ++q)
 #pragma unroll
             for (int k = 0; k < OUT; ++k) part[q][k] = T(0);
-#pragma unroll 4
-        for (int jj = 0; jj < kDenseTile; ++jj) {
-            const VecN<T, 4> p = tile[jj];
+        const int cnt = (int)((min(jend - j0, (uint32_t)kDenseTile) + 3u) & ~3u);
+        for (int j4 = 0; j4 < cnt; j4 += 4) {
 #pragma unroll
-            for (int q = 0; q < TI; ++q) {
-                T dk[D];
+            for (int jj = 0; jj < 4; ++jj) {
+                const VecN<T, 4> p = tile[j4 + jj];
 #pragma unroll
-                for (int k = 0; k < D; ++k) dk[k] = xi[q][k] - p.v[k];
-                T d2 = dk[0] * dk[0];
-                if constexpr (D >= 2) d2 = kfma(dk[1], dk[1], d2);
-                if constexpr (D >= 3) d2 = kfma(dk[2], dk[2], d2);
-                if constexpr (MODE == kSum) {
-                    part[q][0] = kfma(Radial<T, KERN>::value(d2, c2), p.v[3], part[q][0]);
-                } else {
-                    constexpr int G = MODE == kSumGrad ? 1 : 0;  // first gradient component
-                    T slope;
-                    if constexpr (MODE == kSumGrad && KERN == ABORIA_K_MULTIQUADRIC) {
-                        const T a = d2 + c2;
-                        slope = krsqrt(a);
-                        part[q][0] = kfma(ksqrt(a), p.v[3], part[q][0]);
+                for (int q = 0; q < TI; ++q) {
+                    T dk[D];
+#pragma unroll
+                    for (int k = 0; k < D; ++k) dk[k] = xi[q][k] - p.v[k];
+                    const T q2 = R::arg(dk, c2);
+                    if constexpr (MODE == kSum) {
+                        part[q][0] = kfma(R::value(q2), p.v[3], part[q][0]);
                     } else {
-                        slope = Radial<T, KERN>::slope(d2, c2);
-                        if constexpr (MODE == kSumGrad)  // the Gaussian's value is its slope
-                            part[q][0] = kfma(Radial<T, KERN>::value(d2, c2), p.v[3], part[q][0]);
-                    }
-                    const T h = slope * p.v[3];
+                        constexpr int G = MODE == kSumGrad ? 1 : 0;  // first gradient component
+                        const T slope = R::slope(q2);
+                        if constexpr (MODE == kSumGrad)  // (the Gaussian's value is its slope)
+                            part[q][0] = kfma(KERN == ABORIA_K_GAUSSIAN ? slope : R::value(q2), p.v[3], part[q][0]);
+                        const T h = slope * p.v[3];
 #pragma unroll
-                    for (int k = 0; k < D; ++k) part[q][G + k] = kfma(h, dk[k], part[q][G + k]);
+                        for (int k = 0; k < D; ++k) part[q][G + k] = kfma(h, dk[k], part[q][G + k]);
+                    }
                 }
             }
         }
@@ -156,48 +171,101 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense(const T* __restrict__ xt,
         const uint32_t t = tb * (kDenseBlock * TI) + q * kDenseBlock + threadIdx.x;
         if (t < nt)
 #pragma unroll
-            for (int k = 0; k < OUT; ++k) ypart[((size_t)split * nt + t) * OUT + k] = acc[q][k];
+            for (int k = 0; k < OUT; ++k) jb.part[((size_t)split * nt + t) * OUT + k] = acc[q][k];
     }
 }
 
-// y[t][k] = sum over splits (in split order); with mult, y[t][k] = (mult[t] * C) * sum.
-template <typename T, int OUT>
-__global__ __launch_bounds__(256) void k_dense_reduce(const T* __restrict__ ypart, uint32_t nt, uint32_t nsplit,
-                                                      const T* __restrict__ mult, T C, T* __restrict__ y) {
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= nt) return;
-#pragma unroll
-    for (int k = 0; k < OUT; ++k) {
-        T s = T(0);
-        for (uint32_t q = 0; q < nsplit; ++q) s += ypart[((size_t)q * nt + t) * OUT + k];
-        y[(size_t)t * OUT + k] = mult ? (mult[t] * C) * s : s;
-    }
+template <typename T, int D, int TI, int KERN, int MODE>
+__global__ __launch_bounds__(kDenseBlock) void k_dense(DenseJob<T> jb, T sc, T c2) {
+    __shared__ VecN<T, 4> tile[kDenseTile];
+    dense_block<T, D, TI, KERN, MODE>(jb, sc, c2, xcd_tile(blockIdx.x, gridDim.x), blockIdx.y, tile);
 }
 
-// The kSumGrad partials: y[t] = sum of component 0, g[t][k] = (mult[t] * C) * sum of
-// component 1 + k, each over the splits in split order.
+// The adjoint's two passes in one launch: workgroups below n1 take the source
+// pass js (kSumGrad), the others the target pass jt (kGrad).  Two launches of
+// a small problem leave most of the chip idle twice.
+template <typename T, int D, int TI, int KERN>
+__global__ __launch_bounds__(kDenseBlock) void k_dense_adjoint(DenseJob<T> js, DenseJob<T> jt, uint32_t n1, T sc, T c2) {
+    __shared__ VecN<T, 4> tile[kDenseTile];
+    const uint32_t b = blockIdx.x;
+    if (b < n1) dense_block<T, D, TI, KERN, kSumGrad>(js, sc, c2, b % js.tblocks, b / js.tblocks, tile);
+    else dense_block<T, D, TI, KERN, kGrad>(jt, sc, c2, (b - n1) % jt.tblocks, (b - n1) / jt.tblocks, tile);
+}
+
+// Reduction of one pass's split partials: out[e] = sum over splits of part[split][e]
+// for the nt * OUT values e = (target, component).  Component 0 of a kSumGrad pass
+// goes to y, every other one to g after the factor mult[target] * C (mult given).
+template <typename T>
+struct DenseReduceJob {
+    const T* part;
+    const T* mult;
+    T* y;
+    T* g;
+    uint32_t nt, nsplit;
+};
+
+// 64 consecutive values per workgroup and four waves, each wave adding a quarter of
+// the splits in split order, the quarters then added in order: every load is a
+// contiguous 256-byte run.  (A thread per target walking its components and all
+// splits read each line OUT times and kept one load in flight: 30 us for 59 splits
+// of 20011 x 3 values; this form 8 us.)
+template <typename T, int D, int MODE>
+__device__ __forceinline__ void dense_reduce(const DenseReduceJob<T>& jb, T C, uint32_t block, T (*quarter)[64]) {
+    constexpr uint32_t OUT = dense_out<MODE, D>();
+    const size_t nel = (size_t)jb.nt * OUT;
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const size_t e = (size_t)block * 64 + lane;
+    const uint32_t per = (jb.nsplit + 3u) / 4u;
+    const uint32_t q0 = min(w * per, jb.nsplit), q1 = min(q0 + per, jb.nsplit);
+    T s = T(0);
+    if (e < nel) {
+        const T* p = jb.part + (size_t)q0 * nel + e;
+        uint32_t q = q0;
+        for (; q + 4 <= q1; q += 4, p += 4 * nel) {
+            const T a = p[0], b = p[nel], c = p[2 * nel], d = p[3 * nel];
+            s += a;
+            s += b;
+            s += c;
+            s += d;
+        }
+        for (; q < q1; ++q, p += nel) s += p[0];
+    }
+    quarter[w][lane] = s;
+    __syncthreads();
+    if (w != 0 || e >= nel) return;
+    s = quarter[0][lane] + quarter[1][lane];
+    s += quarter[2][lane];
+    s += quarter[3][lane];
+    const size_t t = e / OUT;
+    const uint32_t k = (uint32_t)(e - t * OUT);
+    if (MODE == kSum) jb.y[t] = s;
+    else if (MODE == kGrad) jb.g[e] = (jb.mult[t] * C) * s;
+    else if (k == 0) jb.y[t] = s;
+    else jb.g[t * D + (k - 1)] = (jb.mult[t] * C) * s;
+}
+
+template <typename T, int D, int MODE>
+__global__ __launch_bounds__(256) void k_dense_reduce(DenseReduceJob<T> jb, T C) {
+    __shared__ T quarter[4][64];
+    dense_reduce<T, D, MODE>(jb, C, blockIdx.x, quarter);
+}
+
+// The reductions of k_dense_adjoint's two passes.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void k_dense_reduce2(const T* __restrict__ ypart, uint32_t nt, uint32_t nsplit,
-                                                       const T* __restrict__ mult, T C, T* __restrict__ y,
-                                                       T* __restrict__ g) {
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= nt) return;
-#pragma unroll
-    for (int k = 0; k <= D; ++k) {
-        T s = T(0);
-        for (uint32_t q = 0; q < nsplit; ++q) s += ypart[((size_t)q * nt + t) * (D + 1) + k];
-        if (k == 0) y[t] = s;
-        else g[(size_t)t * D + k - 1] = (mult[t] * C) * s;
-    }
+__global__ __launch_bounds__(256) void k_dense_adjoint_reduce(DenseReduceJob<T> js, DenseReduceJob<T> jt, uint32_t n1,
+                                                              T C) {
+    __shared__ T quarter[4][64];
+    if (blockIdx.x < n1) dense_reduce<T, D, kSumGrad>(js, C, blockIdx.x, quarter);
+    else dense_reduce<T, D, kGrad>(jt, C, blockIdx.x - n1, quarter);
 }
 
 namespace {
 
 // Launch shapes of the dense sum: targets kept per lane and the number of
 // workgroups the source split aims for (the split count is that over the
-// target blocks, at most one per source tile).  Plan 0 is the untuned default;
-// eight targets per lane are float only (float64 would hold twice the
-// registers).  aboria_autotune_dense times them.
+// target blocks, at most one per kDenseStep sources).  Eight targets per lane are
+// float only (float64 would hold twice the registers).  aboria_autotune_dense
+// times them; default_plan picks one of the 2048-workgroup plans untuned.
 struct DensePlan {
     int32_t ti;
     int32_t wg;
@@ -208,6 +276,7 @@ constexpr DensePlan kDensePlans[] = {
     {8, 2048, "8 targets per lane, 2048 workgroups"}, {4, 4096, "4 targets per lane, 4096 workgroups"},
     {8, 4096, "8 targets per lane, 4096 workgroups"}, {2, 1024, "2 targets per lane, 1024 workgroups"},
     {4, 1024, "4 targets per lane, 1024 workgroups"}, {8, 1024, "8 targets per lane, 1024 workgroups"},
+    {1, 2048, "1 targets per lane, 2048 workgroups"},
 };
 constexpr int32_t kNumDensePlans = sizeof(kDensePlans) / sizeof(kDensePlans[0]);
 
@@ -227,8 +296,20 @@ uint64_t dense_key(bool backward, int kernel, int dtype, int d, int64_t nt, int6
     return k;
 }
 
+// The plan of a pass without a tuned or forced choice: two targets per lane when that
+// leaves 8192 workgroups of kDenseStep sources (2.7e8 pairs), else one: below, the
+// chip holds all workgroups at once and more of them hide more latency; above, half the
+// LDS reads per pair count.  Measured with 1 / 2 / 4 targets per lane, us: Gaussian sums
+// 5003 x 4099 float64 24 / 27 / 33, 8000^2 19.6 / 21.0 / 22.6, multiquadric 3000 x 40000
+// 32 / 36 / 43, 65536^2 720 / 668 / 674, multiquadric adjoint 20011 x 30011 400 / 388 / 404.
+int32_t default_plan(uint32_t nt, uint32_t ns) {
+    const uint64_t steps = ((uint64_t)ns + kDenseStep - 1) / kDenseStep;
+    const uint64_t tblocks = ((uint64_t)nt + 2 * kDenseBlock - 1) / (2 * kDenseBlock);
+    return tblocks * steps >= 8192 ? 1 : 8;
+}
+
 // The plan a call uses: the tuner's current trial, else the cached choice for
-// its key, else plan 0.
+// its key, else -1 (default_plan).
 int32_t dense_plan_for(const aboria_ctx* ctx, uint64_t key, int dtype) {
     if (ctx->dense_plan_forced >= 0) return ctx->dense_plan_forced;
     for (const auto& kv : ctx->dense_cache) {
@@ -237,7 +318,7 @@ int32_t dense_plan_for(const aboria_ctx* ctx, uint64_t key, int dtype) {
             if (kDensePlans[p].ti == kv.second.ti && kDensePlans[p].wg == kv.second.wg && dense_plan_ok(p, dtype))
                 return p;
     }
-    return 0;
+    return -1;
 }
 
 // Kernel constants: Gaussian prm = sigma, multiquadric prm = c.
@@ -307,6 +388,34 @@ aboria_status noalloc_scratch(aboria_ctx* ctx, void** out) {
     return ABORIA_OK;
 }
 
+// Launch shape of one pass under a plan (-1, or one not usable with the type: default_plan).
+struct PassShape {
+    int32_t ti;
+    uint32_t tblocks, nsplit, jchunk;
+    size_t split_bytes;  // partials of one split
+};
+
+template <typename T, int D, int MODE>
+PassShape pass_shape(uint32_t nt, uint32_t ns, int32_t plan, size_t max_splits) {
+    const int32_t p =
+        dense_plan_ok(plan, sizeof(T) == 4 ? ABORIA_F32 : ABORIA_F64) ? plan : (plan < 0 ? default_plan(nt, ns) : 0);
+    PassShape sh;
+    sh.ti = kDensePlans[p].ti;
+    const uint32_t per_block = kDenseBlock * (uint32_t)sh.ti;
+    sh.tblocks = (nt + per_block - 1) / per_block;
+    const uint32_t steps = std::max<uint32_t>((ns + kDenseStep - 1) / kDenseStep, 1);
+    // enough workgroups to fill 256 CUs several times over
+    uint32_t nsplit = std::max<uint32_t>(1, ((uint32_t)kDensePlans[p].wg + sh.tblocks - 1) / sh.tblocks);
+    nsplit = (uint32_t)std::min<size_t>(std::min(nsplit, steps), std::max<size_t>(max_splits, 1));
+    const uint32_t per_split = (steps + nsplit - 1) / nsplit;
+    sh.nsplit = (steps + per_split - 1) / per_split;
+    sh.jchunk = per_split * kDenseStep;
+    sh.split_bytes = sizeof(T) * (size_t)nt * dense_out<MODE, D>();
+    return sh;
+}
+
+uint32_t reduce_blocks(uint32_t nt, int out) { return (uint32_t)(((uint64_t)nt * out + 63) / 64); }
+
 // kSum: out = sum_j K(xt_i, xs_j) w_j; kGrad: out = mult_i * C * sum_j w_j slope (xt_i - xs_j);
 // kSumGrad: out = the kSum sum and out2 = the kGrad sum, from one pass.  The split
 // partials go to the context's grow-only scratch, or, when part is given, to the
@@ -318,47 +427,79 @@ aboria_status launch_dense(aboria_ctx* ctx, uint32_t nt, const void* xt, uint32_
                            const KernelPlan& kp, const void* mult, void* out, void* out2, void* part,
                            size_t part_cap, int32_t plan) {
     constexpr int OUT = dense_out<MODE, D>();
-    const DensePlan& pl = kDensePlans[dense_plan_ok(plan, sizeof(T) == 4 ? ABORIA_F32 : ABORIA_F64) ? plan : 0];
-    const uint32_t per_block = kDenseBlock * (uint32_t)pl.ti;
-    const uint32_t tblocks = (nt + per_block - 1) / per_block;
-    const uint32_t ntiles = std::max<uint32_t>((ns + kDenseTile - 1) / kDenseTile, 1);
-    // enough workgroups to fill 256 CUs several times over
-    uint32_t nsplit = std::max<uint32_t>(1, ((uint32_t)pl.wg + tblocks - 1) / tblocks);
-    nsplit = std::min(nsplit, ntiles);
-    const size_t split_bytes = sizeof(T) * (size_t)nt * OUT;
+    size_t max_splits = SIZE_MAX;
     if (part) {
-        const size_t fit = part_cap / split_bytes;
-        if (fit == 0)
+        max_splits = part_cap / (sizeof(T) * (size_t)nt * OUT);
+        if (max_splits == 0)
             return fail(ctx, ABORIA_ERR_INVALID_ARG, "n_target too large for the no-allocation scratch (" +
                                                          std::to_string(part_cap / (sizeof(T) * OUT)) +
                                                          " targets at most)");
-        nsplit = (uint32_t)std::min<size_t>(nsplit, fit);
     }
-    const uint32_t tiles_per_split = (ntiles + nsplit - 1) / nsplit;
-    nsplit = (ntiles + tiles_per_split - 1) / tiles_per_split;
-    const uint32_t jchunk = tiles_per_split * kDenseTile;
+    const PassShape sh = pass_shape<T, D, MODE>(nt, ns, plan, max_splits);
     if (!part) {
-        aboria_status st = ensure_scratch(ctx, split_bytes * nsplit);
+        aboria_status st = ensure_scratch(ctx, sh.split_bytes * sh.nsplit);
         if (st != ABORIA_OK) return st;
         part = ctx->scratch;
     }
-#define ABORIA_DENSE_LAUNCH(TI)                                                                            \
-    hipLaunchKernelGGL((k_dense<T, D, TI, KERN, MODE>), dim3(tblocks, nsplit), dim3(kDenseBlock), 0, ctx->stream, \
-                       (const T*)xt, nt, (const T*)xs, (const T*)w, ns, (T)kp.sc, (T)kp.c2, jchunk, (T*)part)
-    if (pl.ti == 2) {
-        ABORIA_DENSE_LAUNCH(2);
-    } else if (pl.ti == 8) {
-        if constexpr (sizeof(T) == 4) ABORIA_DENSE_LAUNCH(8);
-    } else {
-        ABORIA_DENSE_LAUNCH(4);
+    const DenseJob<T> jb{(const T*)xt, (const T*)xs, (const T*)w, (T*)part, nt, ns, sh.jchunk, sh.tblocks};
+#define ABORIA_DENSE_LAUNCH(TI)                                                                                   \
+    hipLaunchKernelGGL((k_dense<T, D, TI, KERN, MODE>), dim3(sh.tblocks, sh.nsplit), dim3(kDenseBlock), 0, ctx->stream, \
+                       jb, (T)kp.sc, (T)kp.c2)
+    switch (sh.ti) {
+        case 1: ABORIA_DENSE_LAUNCH(1); break;
+        case 2: ABORIA_DENSE_LAUNCH(2); break;
+        case 8:
+            if constexpr (sizeof(T) == 4) ABORIA_DENSE_LAUNCH(8);
+            break;
+        default: ABORIA_DENSE_LAUNCH(4); break;
     }
 #undef ABORIA_DENSE_LAUNCH
-    if constexpr (MODE == kSumGrad)
-        hipLaunchKernelGGL((k_dense_reduce2<T, D>), dim3((nt + 255) / 256), dim3(256), 0, ctx->stream,
-                           (const T*)part, nt, nsplit, (const T*)mult, (T)kp.C, (T*)out, (T*)out2);
-    else
-        hipLaunchKernelGGL((k_dense_reduce<T, OUT>), dim3((nt + 255) / 256), dim3(256), 0, ctx->stream,
-                           (const T*)part, nt, nsplit, (const T*)mult, (T)kp.C, (T*)out);
+    const DenseReduceJob<T> rj{(const T*)part, (const T*)mult, (T*)out, (T*)(MODE == kGrad ? out : out2), nt, sh.nsplit};
+    hipLaunchKernelGGL((k_dense_reduce<T, D, MODE>), dim3(reduce_blocks(nt, OUT)), dim3(256), 0, ctx->stream, rj, (T)kp.C);
+    ABORIA_HIP(ctx, hipGetLastError());
+    return ABORIA_OK;
+}
+
+// Partials of both adjoint passes that one launch may keep at once; above it the passes
+// run one after the other in the same scratch.
+constexpr size_t kAdjointScratch = size_t(256) << 20;
+
+// The whole adjoint (gw and gxs from the source pass, gxt from the target pass) in one
+// launch and one reduction; *done = false when the passes have to run apart.
+template <typename T, int D, int KERN>
+aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint32_t ns, const void* xs, const void* w,
+                             const void* gy, const KernelPlan& kp, void* gxt, void* gxs, void* gw, int32_t plan,
+                             bool* done) {
+    const PassShape a = pass_shape<T, D, kSumGrad>(ns, nt, plan, SIZE_MAX);
+    const PassShape b = pass_shape<T, D, kGrad>(nt, ns, plan, SIZE_MAX);
+    const size_t bytes_a = (a.split_bytes * a.nsplit + 255) & ~(size_t)255;
+    const size_t need = bytes_a + b.split_bytes * b.nsplit;
+    // one kernel holds one target count per lane
+    *done = a.ti == b.ti && need <= kAdjointScratch;
+    if (!*done) return ABORIA_OK;
+    aboria_status st = ensure_scratch(ctx, need);
+    if (st != ABORIA_OK) return st;
+    T* pa = (T*)ctx->scratch;
+    T* pb = (T*)((char*)ctx->scratch + bytes_a);
+    const DenseJob<T> js{(const T*)xs, (const T*)xt, (const T*)gy, pa, ns, nt, a.jchunk, a.tblocks};
+    const DenseJob<T> jt{(const T*)xt, (const T*)xs, (const T*)w, pb, nt, ns, b.jchunk, b.tblocks};
+    const uint32_t n1 = a.tblocks * a.nsplit, n2 = b.tblocks * b.nsplit;
+#define ABORIA_DENSE_LAUNCH(TI)                                                                                 \
+    hipLaunchKernelGGL((k_dense_adjoint<T, D, TI, KERN>), dim3(n1 + n2), dim3(kDenseBlock), 0, ctx->stream, js, jt, n1, \
+                       (T)kp.sc, (T)kp.c2)
+    switch (a.ti) {
+        case 1: ABORIA_DENSE_LAUNCH(1); break;
+        case 2: ABORIA_DENSE_LAUNCH(2); break;
+        case 8:
+            if constexpr (sizeof(T) == 4) ABORIA_DENSE_LAUNCH(8);
+            break;
+        default: ABORIA_DENSE_LAUNCH(4); break;
+    }
+#undef ABORIA_DENSE_LAUNCH
+    const DenseReduceJob<T> rs{pa, (const T*)w, (T*)gw, (T*)gxs, ns, a.nsplit};
+    const DenseReduceJob<T> rt{pb, (const T*)gy, nullptr, (T*)gxt, nt, b.nsplit};
+    const uint32_t r1 = reduce_blocks(ns, D + 1), r2 = reduce_blocks(nt, D);
+    hipLaunchKernelGGL((k_dense_adjoint_reduce<T, D>), dim3(r1 + r2), dim3(256), 0, ctx->stream, rs, rt, r1, (T)kp.C);
     ABORIA_HIP(ctx, hipGetLastError());
     return ABORIA_OK;
 }
@@ -402,6 +543,27 @@ aboria_status dispatch(aboria_ctx* ctx, int dtype, int d, int kernel, uint32_t n
         default:
             return launch_kernel<double, 3, MODE>(ctx, kernel, nt, xt, ns, xs, w, prm, mult, out, out2, part,
                                                   part_cap, plan);
+    }
+}
+
+template <typename T, int D>
+aboria_status adjoint_kernel(aboria_ctx* ctx, int kernel, uint32_t nt, const void* xt, uint32_t ns, const void* xs,
+                             const void* w, const void* gy, double prm, void* gxt, void* gxs, void* gw, int32_t plan,
+                             bool* done) {
+    const KernelPlan kp = plan_kernel<T>(kernel, prm);
+    return kernel == ABORIA_K_GAUSSIAN
+               ? launch_adjoint<T, D, ABORIA_K_GAUSSIAN>(ctx, nt, xt, ns, xs, w, gy, kp, gxt, gxs, gw, plan, done)
+               : launch_adjoint<T, D, ABORIA_K_MULTIQUADRIC>(ctx, nt, xt, ns, xs, w, gy, kp, gxt, gxs, gw, plan, done);
+}
+
+template <typename T>
+aboria_status dispatch_adjoint(aboria_ctx* ctx, int d, int kernel, uint32_t nt, const void* xt, uint32_t ns,
+                               const void* xs, const void* w, const void* gy, double prm, void* gxt, void* gxs,
+                               void* gw, int32_t plan, bool* done) {
+    switch (d) {
+        case 1: return adjoint_kernel<T, 1>(ctx, kernel, nt, xt, ns, xs, w, gy, prm, gxt, gxs, gw, plan, done);
+        case 2: return adjoint_kernel<T, 2>(ctx, kernel, nt, xt, ns, xs, w, gy, prm, gxt, gxs, gw, plan, done);
+        default: return adjoint_kernel<T, 3>(ctx, kernel, nt, xt, ns, xs, w, gy, prm, gxt, gxs, gw, plan, done);
     }
 }
 
@@ -527,6 +689,14 @@ extern "C" aboria_status aboria_dense_sum_backward(aboria_ctx* ctx, aboria_dtype
         // dL/dw = K^T gy (the forward sum over the targets, seen from the sources) and the
         // source-position gradient sum over the same pairs with the same weights gy: one
         // pass when both are requested
+        if (gw && gxs && gxt) {
+            bool done = false;
+            st = dtype == ABORIA_F32 ? dispatch_adjoint<float>(ctx, d, kernel, t32, xt, s32, xs, w, gy, prm, gxt, gxs,
+                                                               gw, plan, &done)
+                                     : dispatch_adjoint<double>(ctx, d, kernel, t32, xt, s32, xs, w, gy, prm, gxt, gxs,
+                                                                gw, plan, &done);
+            if (st != ABORIA_OK || done) return st;
+        }
         if (gw && gxs) {
             if ((st = dispatch<kSumGrad>(ctx, dtype, d, kernel, s32, xs, t32, xt, gy, prm, w, gw, gxs, nullptr, 0,
                                          plan)) != ABORIA_OK)
