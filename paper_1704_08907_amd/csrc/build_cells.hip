@@ -1076,12 +1076,6 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
         // bucket pass's random gather into a sequential read, which pays when a system's
         // positions do not fit in L2 (a 12 MB cube: 58 -> 38 us), while the gather of a
         // 0.8 MB system already hits L2 and the payload only adds traffic.
-        if (ctx->lds_per_block == 0) {
-            int v = 0;
-            if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device) != hipSuccess)
-                v = 65536;
-            ctx->lds_per_block = v;
-        }
         int64_t largest = 0;
         for (int32_t b = 0; b < c->nsys; ++b)
             largest = std::max<int64_t>(largest, c->sys_off[(size_t)b + 1] - c->sys_off[(size_t)b]);
@@ -1090,7 +1084,7 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
         Row* pout = reinterpret_cast<Row*>(c->work);
         const size_t lds_bytes = (6 * (size_t)radix + 2 * (size_t)kSortTile) * sizeof(uint32_t) +
                                  (payload ? (size_t)kSortTile * sizeof(Row) : 0);
-        const bool fits = lds_bytes + (kTopInline + 4) * sizeof(uint32_t) <= (size_t)ctx->lds_per_block;
+        const bool fits = lds_bytes + (kTopInline + 4) * sizeof(uint32_t) <= (size_t)lds_limit(ctx);
         const bool shuffle = fits && (c->shuffle_pref == 1 || (c->shuffle_pref == 0 && ntiles <= 512));
         for (int p = 0; p < c->passes; ++p) {
             const int shift = c->low_bits + p * c->digit_bits;

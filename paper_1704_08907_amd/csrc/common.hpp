@@ -209,6 +209,9 @@ aboria_status scan_finish_u32(aboria_ctx* ctx, uint32_t* out, int64_t len, const
 int64_t scan_block_count(int64_t len);
 aboria_status fill_u32(aboria_ctx* ctx, uint32_t* p, uint32_t v, int64_t len);
 
+// LDS a workgroup may use on the context's device.
+uint32_t lds_limit(aboria_ctx* ctx);
+
 // True if [a, a+na) and [b, b+nb) overlap (byte ranges).
 inline bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
     if (!a || !b || na == 0 || nb == 0) return false;

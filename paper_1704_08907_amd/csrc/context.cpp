@@ -46,6 +46,15 @@ aboria_status hip_fail(aboria_ctx* ctx, hipError_t e, const char* what) {
     return e == hipErrorOutOfMemory ? ABORIA_ERR_OUT_OF_MEMORY : ABORIA_ERR_DEVICE;
 }
 
+uint32_t lds_limit(aboria_ctx* ctx) {
+    if (ctx->lds_per_block == 0) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device) != hipSuccess) v = 65536;
+        ctx->lds_per_block = v;
+    }
+    return (uint32_t)ctx->lds_per_block;
+}
+
 int32_t op_ny(int32_t op, int32_t d) {
     switch (op) {
         case ABORIA_OP_COUNT: return 1;

@@ -61,34 +61,40 @@ __global__ __launch_bounds__(256) void k_integrate(T* __restrict__ x, T* __restr
 // its position) and v[perm[s]], and its new position and velocity go to
 // x_out[s], v_out[s], so the outputs come out in cell order and only v is
 // gathered.
-template <typename T, int D, int OP, bool BATCH, bool OFF32, bool SORTED>
-__global__ __launch_bounds__(256) void k_md_step(const T* __restrict__ xs, const uint32_t* __restrict__ off,
+template <typename T, int D, int OP, bool BATCH, bool OFF32, bool SORTED, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_md_step(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                  const uint32_t* __restrict__ perm, uint32_t n,
                                                  const SysParams<T>* __restrict__ sp,
                                                  const uint32_t* __restrict__ sys_part, int nsys, OpArgs<T> q, T dt,
                                                  T* __restrict__ x, T* __restrict__ v, T* __restrict__ x_out,
-                                                 T* __restrict__ v_out) {
+                                                 T* __restrict__ v_out, int32_t split) {
     using Op = PairOp<T, D, OP>;
     static_assert(Op::NY == D, "the step needs a force operator");
-    const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
-    const uint32_t s = first + threadIdx.x;
-    const int b = system_of_row<BATCH>(sys_part, nsys, first, s);
-    if (s >= n) return;
-    const SysParams<T> P = sp[b];
+    constexpr uint32_t WB = WindowBytes<T, D, 0>::value;
+    extern __shared__ __align__(32) char lds[];
+    const WaveRows w = wave_rows<D, SPLIT>(split);
+    const uint32_t s = w.s;
+    const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
+    WaveSums<T, D, D, SPLIT> ws(split, part_lds(lds, WB));
+    auto& sums = ws.sums;
     T xi[D];
-    load_point<T, D>(xs, s, xi);
-    T acc[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) acc[k] = T(0);
-    const T r = P.r;
-    auto visit = [&](uint32_t, const T* dx, T d2, bool) { Op::fwd(q, r, dx, d2, T(0), T(0), acc); };
-    neighbour_loop_staged<T, D, OFF32>(P, xs, off, n, xi, visit);
+    if (s < n) {
+        const SysParams<T> P = sp[b];
+        load_point<T, D>(xs, s, xi);
+        const T r = P.r;
+        auto visit = [&](uint32_t, const T* dx, T d2, bool) { Op::fwd(q, r, dx, d2, T(0), T(0), sums.acc); };
+        neighbour_loop_staged<T, D, OFF32, 0>(P, xs, (const T*)nullptr, off, n, xi, visit,
+                                              [&](int32_t row) { ws.row_done(row); }, w.range,
+                                              wave_window(lds, w.wave, WB));
+    }
+    if (!ws.finish(w, n)) return;
+    const SysParams<T>& P = sp[b];
     const uint32_t o = perm[s];
 #pragma unroll
     for (int k = 0; k < D; ++k) {
         const size_t e = (size_t)o * D + k;
         T xk = SORTED ? xi[k] : x[e], vk = v[e];
-        euler_update<T>(P, k, acc[k], dt, xk, vk);
+        euler_update<T>(P, k, sums.tot[k], dt, xk, vk);
         const size_t w = SORTED ? (size_t)s * D + k : e;
         (SORTED ? v_out : v)[w] = vk;
         (SORTED ? x_out : x)[w] = xk;
@@ -114,17 +120,17 @@ template <typename T, int D, int OP, bool SORTED>
 void launch_md_step(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, double dt, void* x, void* v,
                     void* x_out, void* v_out) {
     const uint32_t n = (uint32_t)c->n;
-    const dim3 grid((n + 255) / 256);
+    const SearchShape sh = search_shape(ctx, c, WindowBytes<T, D, 0>::value, WaveSums<T, D, D, true>::kPartBytes);
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-#define MD(B, O)                                                                                                 \
-    hipLaunchKernelGGL((k_md_step<T, D, OP, B, O, SORTED>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs,     \
-                       c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, q, (T)dt, (T*)x, (T*)v, (T*)x_out,      \
-                       (T*)v_out)
+#define MD(B, O, S)                                                                                                 \
+    hipLaunchKernelGGL((k_md_step<T, D, OP, B, O, SORTED, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, ctx->stream, \
+                       (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, q, (T)dt, (T*)x, (T*)v,  \
+                       (T*)x_out, (T*)v_out, sh.split)
     const bool o32 = off32_rows<T>(n);
     if (c->nsys == 1) {
-        if (o32) MD(false, true); else MD(false, false);
+        if (sh.split > 0) MD(false, true, (D > 1)); else if (o32) MD(false, true, false); else MD(false, false, false);
     } else {
-        if (o32) MD(true, true); else MD(true, false);
+        if (sh.split > 0) MD(true, true, (D > 1)); else if (o32) MD(true, true, false); else MD(true, false, false);
     }
 #undef MD
 }

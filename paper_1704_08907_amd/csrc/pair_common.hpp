@@ -329,8 +329,7 @@ __device__ __forceinline__ bool pair_test(const T* xj, const T* xi, const T* sh,
 // next, which are adjacent slots).  When every lane's run lies in that range
 // and it has at most kWindow slots, the wave copies it once into a window of
 // its own with coalesced loads and the lanes read their candidates from LDS.
-constexpr int kBlockWaves = 4;  // waves of a 256-thread workgroup
-constexpr int kWindow = 128;    // slots of a wave's LDS window
+constexpr int kWindow = 128;  // slots of a wave's LDS window
 
 // Bytes of one window: kWindow position rows and, with G > 0, as many rows of G
 // elements.
@@ -555,20 +554,37 @@ __device__ __forceinline__ bool wrap_cell(int32_t v, int32_t n, int32_t periodic
     return true;
 }
 
+// Rows of the box search in visiting order: dz-major, then dy (D = 2: dy; D = 1:
+// one row).  kStencilRows counts those of a grid searched one cell deep in y and z.
+template <int D>
+constexpr int32_t kStencilRows = D == 1 ? 1 : (D == 2 ? 3 : 9);
+
+// The rows [first, last) of a search (last past the number of rows: all).
+struct RowRange {
+    int32_t first, last;
+};
+constexpr RowRange kAllRows = {0, 0x7FFFFFFF};
+
+struct NoRowDone {
+    __device__ __forceinline__ void operator()(int32_t) const {}
+};
+
 // Box search of the point xi (a particle of the cell list, Section 2.2.2): its
 // cell and every cell up to m_k = P.reach[k] cells away in dimension k (m = 1:
 // the adjacent cells), walked as (2 m_y + 1)(2 m_z + 1) x-rows in (z, y)
-// order.  On a grid at least 2 m_x + 1 cells wide a row is one contiguous run
+// order, those in range; row_done(row) ends each.  On a grid at least 2 m_x + 1
+// cells wide a row is one contiguous run
 // of up to 2 m_x + 1 cells clipped to the grid, then, when periodic, the
 // wrapped remainder with its image shift (only one side can wrap); on a
 // narrower grid each offset is its own piece, in offset order.  A piece whose shift is zero on every active
 // lane of the wave runs the loop without the shift additions (adding zero is
 // exact, so both loops give the canonical dx).  flat_loop visits the accepted
-// neighbours in this same order.
-template <typename T, int D, bool OFF32, int NAUX, typename Visit, bool STAGE = false>
+// neighbours in this same order.  With STAGE, wb is the wave's LDS window.
+template <typename T, int D, bool OFF32, int NAUX, bool STAGE, typename Visit, typename RowDone>
 __device__ __forceinline__ void neighbour_loop_aux(const SysParams<T>& P, const T* __restrict__ xs,
                                                    const T* __restrict__ aux, const uint32_t* __restrict__ off,
-                                                   uint32_t n, const T* xi, Visit&& visit) {
+                                                   uint32_t n, const T* xi, Visit&& visit,
+                                                   RowDone&& row_done, RowRange range, char* wb) {
     int32_t c[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -607,113 +623,231 @@ __device__ __forceinline__ void neighbour_loop_aux(const SysParams<T>& P, const 
     auto piece = [&](uint32_t ca, uint32_t cb, const T* sh) {
         piece_j(std::integral_constant<bool, false>(), off[ca], min(off[cb + 1], n), sh, WinRef{nullptr, 0u});
     };
+    const int32_t zl = D >= 3 ? P.reach[2] : 0, yl = D >= 2 ? P.reach[1] : 0;
+    // calls row(dz, dy) for the rows in range, then row_done
+    auto for_rows = [&](int32_t zr, int32_t yr, auto&& row) {
+        int32_t q = 0;
+#pragma unroll 1
+        for (int32_t dz = -zr; dz <= zr; ++dz) {
+#pragma unroll 1
+            for (int32_t dy = -yr; dy <= yr; ++dy, ++q) {
+                if (q < range.first || q >= range.last) continue;
+                row(dz, dy);
+                row_done(q);
+            }
+        }
+    };
     if constexpr (STAGE && OFF32) {
         // Every grid of the wave at least 2 m + 1 cells wide, one reach in y and z
-        // for all its lanes, workgroups of at most kBlockWaves waves: each row's
-        // main runs are read through the wave's LDS window when they fit in it.
-        const int32_t zl = D >= 3 ? P.reach[2] : 0, yl = D >= 2 ? P.reach[1] : 0;
+        // for all its lanes: each row's main runs are read through the wave's LDS
+        // window when they fit in it.
         const int32_t zr = __builtin_amdgcn_readfirstlane(zl), yr = __builtin_amdgcn_readfirstlane(yl);
-        if (__ballot(!wide || zl != zr || yl != yr) == 0ull && blockDim.x <= 64u * kBlockWaves) {
+        if (__ballot(!wide || zl != zr || yl != yr) == 0ull) {
             constexpr int G = NAUX > 0 ? GyPitch<NAUX>::value : 0;
-            __shared__ VecN<T, 4> win[kBlockWaves][WindowBytes<T, D, G>::value / sizeof(VecN<T, 4>)];
-            char* const wb = reinterpret_cast<char*>(&win[threadIdx.x >> 6][0]);
             const uint64_t act = __ballot(true);
             const uint32_t nact = (uint32_t)__popcll(act);
             const uint32_t rank =
                 __builtin_amdgcn_mbcnt_hi((uint32_t)(act >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)act, 0u));
-#pragma unroll 1
-            for (int32_t dz = -zr; dz <= zr; ++dz) {
-#pragma unroll 1
-                for (int32_t dy = -yr; dy <= yr; ++dy) {
-                    int32_t cz = 0, cy = 0;
-                    T sz = T(0), sy = T(0);
-                    const bool ez = D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz);
-                    const bool ey = D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy);
-                    const bool ex = ez && ey;
-                    uint32_t rowbase = 0, jm0 = 0, jm1 = 0;
-                    if (ex) {
-                        rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
-                        jm0 = off[rowbase + a0];
-                        jm1 = max(min(off[rowbase + b0 + 1], n), jm0);
-                    }
-                    const bool has = jm1 > jm0;
-                    const uint64_t hb = __ballot(has);
-                    bool staged = false;
-                    uint32_t lo = 0;
-                    if (hb != 0ull) {
-                        lo = __builtin_amdgcn_readlane(jm0, __builtin_ctzll(hb));
-                        const uint32_t hi = __builtin_amdgcn_readlane(jm1, 63 - __builtin_clzll(hb));
-                        const bool inside = !has || (jm0 >= lo && jm1 <= hi);
-                        // all inside: the first lane's run gives lo < hi
-                        staged = __ballot(!inside) == 0ull && hi - lo <= (uint32_t)kWindow;
-                        if (staged) stage_window<T, D, G>(xs, aux, wb, lo, hi - lo, rank, nact);
-                    }
-                    if (ex) {
-                        T sh[3] = {T(0), sy, sz};
-                        if (staged) piece_j(std::integral_constant<bool, true>(), jm0, jm1, sh, WinRef{wb, lo});
-                        else piece_j(std::integral_constant<bool, false>(), jm0, jm1, sh, WinRef{nullptr, 0u});
-                        if (b1 >= a1) {
-                            sh[0] = s1;
-                            piece(rowbase + a1, rowbase + b1, sh);
-                        }
+            for_rows(zr, yr, [&](int32_t dz, int32_t dy) {
+                int32_t cz = 0, cy = 0;
+                T sz = T(0), sy = T(0);
+                const bool ez = D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz);
+                const bool ey = D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy);
+                const bool ex = ez && ey;
+                uint32_t rowbase = 0, jm0 = 0, jm1 = 0;
+                if (ex) {
+                    rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
+                    jm0 = off[rowbase + a0];
+                    jm1 = max(min(off[rowbase + b0 + 1], n), jm0);
+                }
+                const bool has = jm1 > jm0;
+                const uint64_t hb = __ballot(has);
+                bool staged = false;
+                uint32_t lo = 0;
+                if (hb != 0ull) {
+                    lo = __builtin_amdgcn_readlane(jm0, __builtin_ctzll(hb));
+                    const uint32_t hi = __builtin_amdgcn_readlane(jm1, 63 - __builtin_clzll(hb));
+                    const bool inside = !has || (jm0 >= lo && jm1 <= hi);
+                    // all inside: the first lane's run gives lo < hi
+                    staged = __ballot(!inside) == 0ull && hi - lo <= (uint32_t)kWindow;
+                    if (staged) stage_window<T, D, G>(xs, aux, wb, lo, hi - lo, rank, nact);
+                }
+                if (ex) {
+                    T sh[3] = {T(0), sy, sz};
+                    if (staged) piece_j(std::integral_constant<bool, true>(), jm0, jm1, sh, WinRef{wb, lo});
+                    else piece_j(std::integral_constant<bool, false>(), jm0, jm1, sh, WinRef{nullptr, 0u});
+                    if (b1 >= a1) {
+                        sh[0] = s1;
+                        piece(rowbase + a1, rowbase + b1, sh);
                     }
                 }
-            }
+            });
             return;
         }
     }
-    const int32_t zr = D >= 3 ? P.reach[2] : 0, yr = D >= 2 ? P.reach[1] : 0;
-    for (int32_t dz = -zr; dz <= zr; ++dz) {
-        int32_t cz = 0;
-        T sz = T(0);
-        if (D >= 3 && !wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz)) continue;
-        for (int32_t dy = -yr; dy <= yr; ++dy) {
-            int32_t cy = 0;
-            T sy = T(0);
-            if (D >= 2 && !wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy)) continue;
-            const uint32_t rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
-            T sh[3] = {T(0), sy, sz};
-            if (wide) {
-                piece(rowbase + a0, rowbase + b0, sh);
-                if (b1 >= a1) {
-                    sh[0] = s1;
-                    piece(rowbase + a1, rowbase + b1, sh);
-                }
-            } else {
-                for (int32_t o = -M; o <= M; ++o) {
-                    int32_t cx;
-                    if (!wrap_cell(c[0] + o, nx, P.periodic[0], P.L[0], &cx, &sh[0])) continue;
-                    piece(rowbase + cx, rowbase + cx, sh);
-                }
+    for_rows(zl, yl, [&](int32_t dz, int32_t dy) {
+        int32_t cz = 0, cy = 0;
+        T sz = T(0), sy = T(0);
+        if (D >= 3 && !wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz)) return;
+        if (D >= 2 && !wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy)) return;
+        const uint32_t rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
+        T sh[3] = {T(0), sy, sz};
+        if (wide) {
+            piece(rowbase + a0, rowbase + b0, sh);
+            if (b1 >= a1) {
+                sh[0] = s1;
+                piece(rowbase + a1, rowbase + b1, sh);
+            }
+        } else {
+            for (int32_t o = -M; o <= M; ++o) {
+                int32_t cx;
+                if (!wrap_cell(c[0] + o, nx, P.periodic[0], P.L[0], &cx, &sh[0])) continue;
+                piece(rowbase + cx, rowbase + cx, sh);
             }
         }
-    }
-}
-
-// neighbour_loop_aux with each row's main runs read through the wave's LDS
-// window where they fit (same pairs, same order, same sums).
-template <typename T, int D, bool OFF32, int NAUX, typename Visit>
-__device__ __forceinline__ void neighbour_loop_aux_staged(const SysParams<T>& P, const T* __restrict__ xs,
-                                                          const T* __restrict__ aux,
-                                                          const uint32_t* __restrict__ off, uint32_t n, const T* xi,
-                                                          Visit&& visit) {
-    neighbour_loop_aux<T, D, OFF32, NAUX, Visit, true>(P, xs, aux, off, n, xi, visit);
+    });
 }
 
 // The box search without prefetched per-candidate rows: visit(j, dx, d2, shifted).
-template <typename T, int D, bool OFF32 = false, typename Visit>
+template <typename T, int D, bool OFF32 = false, typename Visit, typename RowDone = NoRowDone>
 __device__ __forceinline__ void neighbour_loop(const SysParams<T>& P, const T* __restrict__ xs,
                                                const uint32_t* __restrict__ off, uint32_t n, const T* xi,
-                                               Visit&& visit) {
-    neighbour_loop_aux<T, D, OFF32, 0>(P, xs, nullptr, off, n, xi, visit);
+                                               Visit&& visit, RowDone&& row_done = RowDone(),
+                                               RowRange range = kAllRows) {
+    neighbour_loop_aux<T, D, OFF32, 0, false>(P, xs, (const T*)nullptr, off, n, xi, visit, row_done, range, nullptr);
 }
 
-// neighbour_loop with each row's main runs read through the wave's LDS window.
-template <typename T, int D, bool OFF32 = false, typename Visit>
+// neighbour_loop_aux with each row's main runs read through the wave's LDS
+// window wb (WindowBytes) where they fit (same pairs, same order, same sums).
+template <typename T, int D, bool OFF32, int NAUX, typename Visit, typename RowDone>
 __device__ __forceinline__ void neighbour_loop_staged(const SysParams<T>& P, const T* __restrict__ xs,
-                                                      const uint32_t* __restrict__ off, uint32_t n, const T* xi,
-                                                      Visit&& visit) {
-    neighbour_loop_aux<T, D, OFF32, 0, Visit, true>(P, xs, nullptr, off, n, xi, visit);
+                                                      const T* __restrict__ aux, const uint32_t* __restrict__ off,
+                                                      uint32_t n, const T* xi, Visit&& visit, RowDone&& row_done,
+                                                      RowRange range, char* wb) {
+    neighbour_loop_aux<T, D, OFF32, NAUX, true>(P, xs, aux, off, n, xi, visit, row_done, range, wb);
+}
+
+// ---------------------------------------------------------------------------
+// rows of a particle over one wave or several
+// ---------------------------------------------------------------------------
+
+// On small cell lists (row_split has the rule) every box-search sum is formed row by
+// row: a row's pairs are added in visiting order, and the rows' sums are added in row
+// order.  The rows of 64 particles can then be spread over several waves whose sums
+// are added in the same order: same bits, whichever kernel forms them.  On larger
+// cell lists one wave takes all rows of its 64 particles and adds every pair to one
+// running sum.  Kernels with SPLIT do the former, with `split` waves per 64 particles;
+// a wave's part of the work:
+struct WaveRows {
+    uint32_t first;   // first particle slot of the workgroup
+    uint32_t s;       // this lane's particle slot
+    int32_t wave;     // wave of the workgroup
+    RowRange range;   // the wave's rows
+};
+
+template <int D, bool SPLIT>
+__device__ __forceinline__ WaveRows wave_rows(int32_t split) {
+    const int32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    if (!SPLIT || split == 1) {
+        const uint32_t first = tile * blockDim.x;
+        return WaveRows{first, first + threadIdx.x, wave, kAllRows};
+    }
+    const int32_t per = kStencilRows<D> / split;
+    return WaveRows{tile * 64u, tile * 64u + (threadIdx.x & 63u), wave, RowRange{wave * per, (wave + 1) * per}};
+}
+
+// The NV sums of a lane's particle: acc the running sum or, by rows, the current
+// row's, tot the finished rows'.
+template <typename T, int NV>
+struct RowSums {
+    T acc[NV], tot[NV];
+    bool by_rows;
+    __device__ __forceinline__ explicit RowSums(bool rows) : by_rows(rows) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) acc[k] = tot[k] = T(0);
+    }
+    __device__ __forceinline__ void row_done() {
+        if (!by_rows) return;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            tot[k] += acc[k];
+            acc[k] = T(0);
+        }
+    }
+    // row_done() where the lane's new_row is set, without a branch (by_rows false: the
+    // caller clears new_row)
+    __device__ __forceinline__ void row_done_if(bool new_row) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            tot[k] += new_row ? acc[k] : T(0);
+            acc[k] = new_row ? T(0) : acc[k];
+        }
+    }
+    __device__ __forceinline__ void last() {  // the running sum, or the last row's
+#pragma unroll
+        for (int k = 0; k < NV; ++k) tot[k] += acc[k];
+    }
+};
+
+// RowSums of a search kernel; with split > 1 the rows' sums go to LDS ([row][NV][64]).
+template <typename T, int D, int NV, bool SPLIT>
+struct WaveSums {
+    RowSums<T, NV> sums;
+    int32_t split;
+    char* part;
+    static constexpr uint32_t kPartBytes = SPLIT ? (uint32_t)kStencilRows<D> * NV * 64u * (uint32_t)sizeof(T) : 0u;
+
+    __device__ __forceinline__ WaveSums(int32_t sp, char* part_lds) : sums(SPLIT), split(sp), part(part_lds) {}
+    __device__ __forceinline__ void row_done(int32_t row) {
+        if constexpr (SPLIT) {
+            if (split == 1) {
+                sums.row_done();
+                return;
+            }
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                reinterpret_cast<T*>(part)[(row * NV + k) * 64 + (threadIdx.x & 63u)] = sums.acc[k];
+                sums.acc[k] = T(0);
+            }
+        }
+    }
+    // Completes sums.tot; every thread of the workgroup calls it.  True on the lanes
+    // that hold a particle's result.
+    __device__ __forceinline__ bool finish(const WaveRows& w, uint32_t n) {
+        if (SPLIT && split > 1) {
+            __syncthreads();
+            if (w.wave != 0) return false;
+            for (int32_t row = 0; row < kStencilRows<D>; ++row)
+#pragma unroll
+                for (int k = 0; k < NV; ++k)
+                    sums.tot[k] += reinterpret_cast<const T*>(part)[(row * NV + k) * 64 + (threadIdx.x & 63u)];
+        } else {
+            sums.last();
+        }
+        return w.s < n;
+    }
+};
+
+constexpr int kSearchThreads = 64 * 9;  // most threads of a search workgroup (a wave per row)
+
+// row_split: waves per 64 particles of a cell list by its size (0: a running sum).
+// (Kernels that always take one wave only look whether it is 0.)
+// search_shape: launch shape of a box-search kernel whose waves each need wave_bytes of LDS (their
+// window) and, when split, whose workgroup needs part_bytes more.
+struct SearchShape {
+    int32_t split;
+    uint32_t blocks, threads, lds;
+};
+int32_t row_split(const aboria_cells* c);
+SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, uint32_t wave_bytes, uint32_t part_bytes);
+
+// The dynamic LDS of a search workgroup: the waves' windows, then the row sums.
+__device__ __forceinline__ char* wave_window(char* lds, int32_t wave, uint32_t wave_bytes) {
+    return lds + (uint32_t)wave * wave_bytes;
+}
+__device__ __forceinline__ char* part_lds(char* lds, uint32_t wave_bytes) {
+    return lds + (blockDim.x >> 6) * wave_bytes;
 }
 
 // ---------------------------------------------------------------------------
@@ -722,12 +856,15 @@ __device__ __forceinline__ void neighbour_loop_staged(const SysParams<T>& P, con
 
 // Per-lane slot ranges of the flattened search, in LDS: entry k of lane t at
 // [k][t] (consecutive lanes in consecutive banks).  code packs the image shift
-// of the range, two bits per dimension (0: none, 1: -L, 2: +L).
+// of the range, two bits per dimension (0: none, 1: -L, 2: +L), and kFlatNewRow
+// where the range is the first one of its row.
 template <int CAP, int BLOCK>
 struct FlatRanges {
     uint2 range[CAP][BLOCK];
     uint8_t code[CAP][BLOCK];
 };
+
+constexpr uint32_t kFlatNewRow = 0x40u;
 
 template <typename T, int D>
 __device__ __forceinline__ void decode_shift(const SysParams<T>& P, uint32_t code, T* sh) {
@@ -762,11 +899,12 @@ __device__ __forceinline__ T gap2(const SysParams<T>& P, int k, int32_t o, T fr)
 // candidates the predicate rejects).  A lane uses its own LDS column only, so
 // no barrier is needed and lanes past the end may simply not call it.  t_self
 // is the lane's own slot (< n), the target of loads issued past its last
-// candidate.
-template <typename T, int D, int CAP, int BLOCK, bool OFF32, typename Visit>
+// candidate.  row_done() is called between the candidates of one row and the next.
+template <typename T, int D, int CAP, int BLOCK, bool OFF32, typename Visit, typename RowDone>
 __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __restrict__ xs,
                                           const uint32_t* __restrict__ off, uint32_t n, const T* xi,
-                                          uint32_t t_self, FlatRanges<CAP, BLOCK>& fr_lds, Visit&& visit) {
+                                          uint32_t t_self, FlatRanges<CAP, BLOCK>& fr_lds, Visit&& visit,
+                                          RowDone&& row_done) {
     constexpr int PITCH = Pitch<D>::value;
     const uint32_t t = threadIdx.x;
     int32_t c[3] = {0, 0, 0};
@@ -795,18 +933,21 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
         // ---- list up to CAP ranges ----
         int kd = 0;
         bool any_shift = false;
+        uint32_t new_row = 0u;
         auto put = [&](uint32_t ca, uint32_t cb, uint32_t code) {
             const uint32_t j0 = off[ca];
             const uint32_t j1 = min(off[cb + 1], n);
             if (j1 > j0) {
                 fr_lds.range[kd][t] = make_uint2(j0, j1);
-                fr_lds.code[kd][t] = (uint8_t)code;
+                fr_lds.code[kd][t] = (uint8_t)(code | new_row);
                 any_shift |= code != 0u;
+                new_row = 0u;
                 ++kd;
             }
         };
         while (rows_left && kd + pmax <= CAP) {
             const int32_t ry = dy, rz = dz;
+            new_row = kFlatNewRow;
             if (++dy > yr) {
                 dy = -yr;
                 if (++dz > zr) rows_left = false;
@@ -853,15 +994,18 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
             constexpr bool SHIFT = decltype(shift_tag)::value;
             uint32_t kr = 0u;  // index of the next range to take
             uint2 ndp = fr_lds.range[0][t];
-            uint32_t ndc = SHIFT ? (uint32_t)fr_lds.code[0][t] : 0u;
+            uint32_t ndc = (uint32_t)fr_lds.code[0][t];
             uint32_t j = 0u, e = 0u;
+            bool nr = false;  // the slot just stepped to is the first of its row
             bool alive = true;
             T cs[3] = {T(0), T(0), T(0)};  // shift of the cursor's range
             // the slot of the lane's next candidate (its own slot once it has none)
             auto step = [&]() -> uint32_t {
                 ++j;
+                nr = false;
                 if (j >= e) {
                     if (kr < (uint32_t)kd) {
+                        nr = (ndc & kFlatNewRow) != 0u;
                         j = ndp.x;
                         e = ndp.y;
                         if (SHIFT) decode_shift<T, D>(P, ndc, cs);
@@ -872,12 +1016,13 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
                 }
                 const uint32_t kn = min(kr, (uint32_t)(CAP - 1));
                 ndp = fr_lds.range[kn][t];
-                if (SHIFT) ndc = fr_lds.code[kn][t];
+                ndc = fr_lds.code[kn][t];
                 return alive ? j : t_self;
             };
             // evaluated on every lane (an idle lane tests its own row, which the
             // predicate rejects) so that the wait for the row is never skipped
-            auto test = [&](const VecN<T, PITCH>& xj, uint32_t jj, const T* sh, bool valid) {
+            auto test = [&](const VecN<T, PITCH>& xj, uint32_t jj, const T* sh, bool valid, bool first) {
+                if (first) row_done();
                 T dx[D], d2;
                 const bool acc = pair_test<T, D, SHIFT>(xj.v, xi, sh, r2, dx, &d2);
                 if (acc & valid) {
@@ -891,24 +1036,25 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
             };
             T sa[3], sb[3];
             uint32_t ja = step();
-            bool va = alive;
+            bool va = alive, fa = nr;
 #pragma unroll
             for (int k = 0; k < 3; ++k) sa[k] = cs[k];
             VecN<T, PITCH> A = load_row<T, PITCH, OFF32>(xs, ja);
             for (;;) {
                 const uint32_t jb = step();
-                const bool vb = alive;
+                const bool vb = alive, fb = nr;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) sb[k] = cs[k];
                 const VecN<T, PITCH> B = load_row<T, PITCH, OFF32>(xs, jb);
-                test(A, ja, sa, va);
+                test(A, ja, sa, va, fa);
                 if (__ballot(vb) == 0ull) break;
                 ja = step();
                 va = alive;
+                fa = nr;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) sa[k] = cs[k];
                 A = load_row<T, PITCH, OFF32>(xs, ja);
-                test(B, jb, sb, vb);
+                test(B, jb, sb, vb, fb);
                 if (__ballot(va) == 0ull) break;
             }
         };
@@ -983,9 +1129,12 @@ __device__ __forceinline__ T group_reduce(T v) {
 // ---------------------------------------------------------------------------
 
 // An entry of a recorded list: the neighbour's slot, with the top bit set when
-// the box search reached it through a nonzero image shift.
+// the box search reached it through a nonzero image shift, and the next one when
+// it is the first neighbour of its stencil row.  (Lists of more than 2^30 slots
+// are not replayed.)
 constexpr uint32_t kNbrShift = 0x80000000u;
-constexpr uint32_t kNbrSlot = 0x7FFFFFFFu;
+constexpr uint32_t kNbrRow = 0x40000000u;
+constexpr uint32_t kNbrSlot = 0x3FFFFFFFu;
 
 // Displacement and squared distance of a recorded pair, bit for bit those of
 // the box search: dx_k = fl(t_k + s_k) with t_k = fl(x_jk - x_ik).  For a
@@ -1013,13 +1162,13 @@ __device__ __forceinline__ T replay_pair(const SysParams<T>& P, const T* xj, con
 }
 
 // Calls visit(j, dx, d2) for the recorded neighbours of slot s in recorded
-// order.  Entry k of slot s is at nbr[k * n + s], so the lanes of a wave read
+// order, row_if(first) before each: first is set on the first one of each row.  Entry k of slot s is at nbr[k * n + s], so the lanes of a wave read
 // consecutive words.  Two entries per iteration keep two position loads in
 // flight.
-template <typename T, int D, typename Visit>
+template <typename T, int D, typename Visit, typename RowIf>
 __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __restrict__ xs,
                                             const uint32_t* __restrict__ nbr, uint32_t n, uint32_t s, uint32_t cnt,
-                                            const T* xi, Visit& visit) {
+                                            const T* xi, Visit& visit, RowIf&& row_if) {
     constexpr int PITCH = Pitch<D>::value;
     const VecN<T, PITCH>* __restrict__ xv = reinterpret_cast<const VecN<T, PITCH>*>(xs);
     const uint32_t* p = nbr + s;
@@ -1033,7 +1182,9 @@ __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __re
         const VecN<T, PITCH> b = xv[e1 & kNbrSlot];
         T dx[D];
         T d2 = replay_pair<T, D>(P, a.v, xi, (e0 & kNbrShift) != 0u, dx);
+        row_if((e0 & kNbrRow) != 0u);
         visit(e0 & kNbrSlot, dx, d2);
+        row_if((e1 & kNbrRow) != 0u);
         d2 = replay_pair<T, D>(P, b.v, xi, (e1 & kNbrShift) != 0u, dx);
         visit(e1 & kNbrSlot, dx, d2);
     }
@@ -1042,6 +1193,7 @@ __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __re
         const VecN<T, PITCH> a = xv[e0 & kNbrSlot];
         T dx[D];
         const T d2 = replay_pair<T, D>(P, a.v, xi, (e0 & kNbrShift) != 0u, dx);
+        row_if((e0 & kNbrRow) != 0u);
         visit(e0 & kNbrSlot, dx, d2);
     }
 }
@@ -1102,12 +1254,12 @@ __device__ __forceinline__ T shift_of(uint32_t code, int k, T L) {
 
 // Lane-per-particle forward.
 template <typename T, int D, int OP, bool BATCH>
-void launch_lane_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, int block);
+void launch_lane_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y);
 
 // Lane-per-particle adjoint.
 template <typename T, int D, int OP, bool BATCH>
 void launch_lane_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
-                     T* ga, int block);
+                     T* ga);
 
 // Forward / adjoint over the cell list's recorded neighbour list (a particle
 // with more neighbours than the list holds is summed by the box search).

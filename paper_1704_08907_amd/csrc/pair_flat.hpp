@@ -19,7 +19,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
                                                      const uint32_t* __restrict__ sys_part, int nsys,
                                                      const T* __restrict__ a_s, const T* __restrict__ gy_s,
                                                      OpArgs<T> q, T* __restrict__ y, T* __restrict__ gx,
-                                                     T* __restrict__ ga) {
+                                                     T* __restrict__ ga, bool by_rows) {
     static_assert(kFlatCap >= 2 * kMaxReach + 1, "a row of a narrow grid must fit one round");
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
@@ -35,11 +35,11 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
     const T ai = OpShape<OP, D>::NA ? a_s[s] : T(0);
     T gyi[NY];
     if (BWD) load_gy<T, NY, OFF32>(gy_s, s, gyi);
-    T acc[NY], accx[D], acca[1] = {T(0)};
-#pragma unroll
-    for (int k = 0; k < NY; ++k) acc[k] = T(0);
-#pragma unroll
-    for (int k = 0; k < D; ++k) accx[k] = T(0);
+    constexpr int NA = OpShape<OP, D>::NA;
+    RowSums<T, NY + D + NA> sums(by_rows);
+    T* const acc = sums.acc;  // y, gx, ga
+    T* const accx = acc + NY;
+    T* const acca = accx + (NA ? D : 0);
     const T r = P.r;
     auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
         const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
@@ -50,16 +50,17 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
             Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
         }
     };
-    flat_loop<T, D, kFlatCap, kFlatBlock, OFF32>(P, xs, off, n, xi, s, ranges, visit);
+    flat_loop<T, D, kFlatCap, kFlatBlock, OFF32>(P, xs, off, n, xi, s, ranges, visit, [&]() { sums.row_done(); });
+    sums.last();
     const uint32_t o = perm[s];
     if (FWD) {
 #pragma unroll
-        for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = acc[k];
+        for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = sums.tot[k];
     }
     if (BWD) {
 #pragma unroll
-        for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = accx[k];
-        if (OpShape<OP, D>::NA && ga) ga[o] = acca[0];
+        for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = sums.tot[NY + k];
+        if (NA && ga) ga[o] = sums.tot[NY + D + NA - 1];
     }
 }
 
@@ -69,12 +70,15 @@ void launch_flat(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, con
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const dim3 grid((n + kFlatBlock - 1) / kFlatBlock);
+    const bool by_rows = row_split(c) > 0;
     if (off32_rows<T>(n))
         hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, true, MODE>), grid, dim3(kFlatBlock), 0, ctx->stream,
-                           (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga);
+                           (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga,
+                           by_rows);
     else
         hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, false, MODE>), grid, dim3(kFlatBlock), 0, ctx->stream,
-                           (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga);
+                           (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga,
+                           by_rows);
 }
 
 }  // namespace aboria

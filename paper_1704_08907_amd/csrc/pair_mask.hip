@@ -35,9 +35,11 @@ constexpr int kMaskBits = 64;  // candidates per stencil row a record covers
 // on a grid narrower than 2 m + 1 cells, one run per offset), then end(row).
 // Rows are numbered (dz + 1) * 3^(d-2) + (dy + 1) in visiting order, so skipped
 // rows keep their numbers.
-template <typename T, int D, typename Begin, typename Piece, typename End>
+// Only the rows in range are walked; row_done(row) follows every one of them.
+template <typename T, int D, typename Begin, typename Piece, typename End, typename RowDone = NoRowDone>
 __device__ __forceinline__ void for_each_piece(const SysParams<T>& P, const uint32_t* __restrict__ off, uint32_t n,
-                                               const T* xi, Begin&& begin, Piece&& piece, End&& end) {
+                                               const T* xi, Begin&& begin, Piece&& piece, End&& end,
+                                               RowDone&& row_done = RowDone(), RowRange range = kAllRows) {
     int32_t c[3] = {0, 0, 0};
 #pragma unroll
     for (int k = 0; k < D; ++k) {
@@ -55,19 +57,19 @@ __device__ __forceinline__ void for_each_piece(const SysParams<T>& P, const uint
         else if (c[0] + M >= nx) { a1 = 0; b1 = c[0] + M - nx; s1 = P.L[0]; }
     }
     const int32_t zr = D >= 3 ? 1 : 0, yr = D >= 2 ? 1 : 0;
+    int32_t row = -1;
     // the row and offset loops stay rolled: unrolled, the compiler hoists work
     // across rows and the kernels hold 8 to 9 more registers per lane
 #pragma unroll 1
-    for (int32_t dz = -zr; dz <= zr; ++dz) {
-        int32_t cz = 0;
-        T sz = T(0);
-        if (D >= 3 && !wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz)) continue;
+    for (int32_t dz = -zr; dz <= zr; ++dz)
 #pragma unroll 1
-        for (int32_t dy = -yr; dy <= yr; ++dy) {
-            int32_t cy = 0;
-            T sy = T(0);
-            if (D >= 2 && !wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy)) continue;
-            const int row = (dz + zr) * (2 * yr + 1) + (dy + yr);
+    for (int32_t dy = -yr; dy <= yr; ++dy) {
+        ++row;
+        if (row < range.first || row >= range.last) continue;
+        int32_t cz = 0, cy = 0;
+        T sz = T(0), sy = T(0);
+        if ((D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz)) &&
+            (D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy))) {
             const uint32_t rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
             T sh[3] = {T(0), sy, sz};
             begin(row);
@@ -88,6 +90,7 @@ __device__ __forceinline__ void for_each_piece(const SysParams<T>& P, const uint
             }
             end(row);
         }
+        row_done(row);
     }
 }
 
@@ -104,10 +107,11 @@ __device__ __forceinline__ void for_each_piece(const SysParams<T>& P, const uint
 // for_each_piece in the same order, so sums and records are identical.  All
 // lanes of the wave that are still running take part in every row (no lane
 // skips ahead), so the copy and the window reads stay in step.
-template <typename T, int D, int G, typename Begin, typename Piece, typename End, typename Win>
+template <typename T, int D, int G, typename Begin, typename Piece, typename End, typename Win, typename RowDone>
 __device__ __forceinline__ void staged_rows(const SysParams<T>& P, const uint32_t* __restrict__ off, uint32_t n,
                                             const T* xi, const T* __restrict__ xs, const T* __restrict__ ys,
-                                            char* wb, Begin&& begin, Piece&& piece, End&& end, Win&& win) {
+                                            char* wb, Begin&& begin, Piece&& piece, End&& end, Win&& win,
+                                            RowDone&& row_done, RowRange range) {
     const uint64_t act = __ballot(true);
     const uint32_t nact = (uint32_t)__popcll(act);
     const uint32_t rank =
@@ -128,78 +132,103 @@ __device__ __forceinline__ void staged_rows(const SysParams<T>& P, const uint32_
         else if (c[0] + M >= nx) { a1 = 0; b1 = c[0] + M - nx; s1 = P.L[0]; }
     }
     const int32_t zr = D >= 3 ? 1 : 0, yr = D >= 2 ? 1 : 0;
+    int32_t row = -1;
 #pragma unroll 1
-    for (int32_t dz = -zr; dz <= zr; ++dz) {
+    for (int32_t dz = -zr; dz <= zr; ++dz)
 #pragma unroll 1
-        for (int32_t dy = -yr; dy <= yr; ++dy) {
-            int32_t cz = 0, cy = 0;
-            T sz = T(0), sy = T(0);
-            const bool ez = D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz);
-            const bool ey = D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy);
-            const bool ex = ez && ey;
-            const int row = (dz + zr) * (2 * yr + 1) + (dy + yr);
-            uint32_t rowbase = 0, jm0 = 0, jm1 = 0;
-            if (ex) {
-                rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
-                jm0 = off[rowbase + a0];
-                jm1 = max(min(off[rowbase + b0 + 1], n), jm0);
-            }
-            const bool has = jm1 > jm0;
-            const uint64_t hb = __ballot(has);
-            bool staged = false;
-            uint32_t lo = 0;
-            if (hb != 0ull) {
-                lo = __builtin_amdgcn_readlane(jm0, __builtin_ctzll(hb));
-                const uint32_t hi = __builtin_amdgcn_readlane(jm1, 63 - __builtin_clzll(hb));
-                const bool inside = !has || (jm0 >= lo && jm1 <= hi);
-                // all inside: the first lane's run gives lo < hi
-                staged = __ballot(!inside) == 0ull && hi - lo <= (uint32_t)kWindow;
-                if (staged) stage_window<T, D, G>(xs, ys, wb, lo, hi - lo, rank, nact);
-            }
-            if (ex) {
-                begin(row);
-                T sh[3] = {T(0), sy, sz};
-                if (staged) win(jm0, jm1, sh, wb, lo);
-                else piece(jm0, jm1, sh);
-                if (b1 >= a1) {
-                    sh[0] = s1;
-                    piece(off[rowbase + a1], min(off[rowbase + b1 + 1], n), sh);
-                }
-                end(row);
-            }
+    for (int32_t dy = -yr; dy <= yr; ++dy) {
+        ++row;
+        if (row < range.first || row >= range.last) continue;
+        int32_t cz = 0, cy = 0;
+        T sz = T(0), sy = T(0);
+        const bool ez = D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz);
+        const bool ey = D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy);
+        const bool ex = ez && ey;
+        uint32_t rowbase = 0, jm0 = 0, jm1 = 0;
+        if (ex) {
+            rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
+            jm0 = off[rowbase + a0];
+            jm1 = max(min(off[rowbase + b0 + 1], n), jm0);
         }
+        const bool has = jm1 > jm0;
+        const uint64_t hb = __ballot(has);
+        bool staged = false;
+        uint32_t lo = 0;
+        if (hb != 0ull) {
+            lo = __builtin_amdgcn_readlane(jm0, __builtin_ctzll(hb));
+            const uint32_t hi = __builtin_amdgcn_readlane(jm1, 63 - __builtin_clzll(hb));
+            const bool inside = !has || (jm0 >= lo && jm1 <= hi);
+            // all inside: the first lane's run gives lo < hi
+            staged = __ballot(!inside) == 0ull && hi - lo <= (uint32_t)kWindow;
+            if (staged) stage_window<T, D, G>(xs, ys, wb, lo, hi - lo, rank, nact);
+        }
+        if (ex) {
+            begin(row);
+            T sh[3] = {T(0), sy, sz};
+            if (staged) win(jm0, jm1, sh, wb, lo);
+            else piece(jm0, jm1, sh);
+            if (b1 >= a1) {
+                sh[0] = s1;
+                piece(off[rowbase + a1], min(off[rowbase + b1 + 1], n), sh);
+            }
+            end(row);
+        }
+        row_done(row);
     }
 }
 
+// Sums and LDS of the two modes: the forward's y and position rows, the adjoint's
+// gx, ga and position and gradient rows (no window in float64).
+template <int MODE, int OP, int D>
+struct MaskSums {
+    static constexpr int NV = MODE == 0 ? OpShape<OP, D>::NY : D + OpShape<OP, D>::NA;
+    template <typename T>
+    static constexpr uint32_t WindowSize =
+        sizeof(T) == 4 ? WindowBytes<T, D, MODE == 0 ? 0 : GyPitch<OpShape<OP, D>::NY>::value>::value : 0u;
+    // row sums, and with MODE 0 a word per wave and lane for the rows' overflow
+    template <typename T>
+    static constexpr uint32_t PartSize =
+        WaveSums<T, D, NV, true>::kPartBytes + (MODE == 0 ? (uint32_t)kStencilRows<D> * 64u * 4u : 0u);
+};
+
 // MODE 0: forward sum + record.  MODE 1: adjoint from the record (gy_s gathered
 // into cell order, rows padded as gradient rows).
-template <typename T, int D, int OP, bool BATCH, bool OFF32, int MODE>
-__global__ __launch_bounds__(256) void k_lane_mask(const T* __restrict__ xs, const uint32_t* __restrict__ off,
+template <typename T, int D, int OP, bool BATCH, bool OFF32, int MODE, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_mask(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                    const uint32_t* __restrict__ perm, uint32_t n,
                                                    const SysParams<T>* __restrict__ sp,
                                                    const uint32_t* __restrict__ sys_part, int nsys,
                                                    const T* __restrict__ a_s, const T* __restrict__ gy_s,
                                                    OpArgs<T> q, T* __restrict__ y, T* __restrict__ gx,
                                                    T* __restrict__ ga, uint32_t* __restrict__ masks,
-                                                   uint32_t* __restrict__ status, const uint32_t* __restrict__ gen) {
+                                                   uint32_t* __restrict__ status, const uint32_t* __restrict__ gen,
+                                                   int32_t split) {
     using Op = PairOp<T, D, OP>;
-    constexpr int NY = Op::NY;
+    constexpr int NY = Op::NY, NA = OpShape<OP, D>::NA;
     constexpr int PITCH = Pitch<D>::value;
     constexpr int GP = GyPitch<NY>::value;
-    const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
-    const uint32_t s = first + threadIdx.x;
-    const int b = system_of_row<BATCH>(sys_part, nsys, first, s);
-    if (s >= n) return;
-    const SysParams<T> P = sp[b];
-    T xi[D];
-    load_point<T, D>(xs, s, xi);
-    const T ai = OpShape<OP, D>::NA ? a_s[s] : T(0);
-    const T r = P.r, r2 = P.r2;
+    constexpr int NV = MaskSums<MODE, OP, D>::NV;
+    constexpr uint32_t WB = MaskSums<MODE, OP, D>::template WindowSize<T>;
+    extern __shared__ __align__(32) char lds[];
+    const WaveRows w = wave_rows<D, SPLIT>(split);
+    const uint32_t s = w.s;
+    const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
+    WaveSums<T, D, NV, SPLIT> ws(split, part_lds(lds, WB));
+    auto& sums = ws.sums;
+    T* const acc = sums.acc;
+    auto row_done = [&](int32_t row) { ws.row_done(row); };
+    char* const wave_wb = wave_window(lds, w.wave, WB);
     if constexpr (MODE == 0) {
-        T acc[NY];
-#pragma unroll
-        for (int k = 0; k < NY; ++k) acc[k] = T(0);
-        bool overflow = false;
+      bool overflow = false;
+      // split: each row's overflow, after the rows' sums
+      uint32_t* const row_ovf =
+          reinterpret_cast<uint32_t*>(ws.part + WaveSums<T, D, NV, SPLIT>::kPartBytes) + (threadIdx.x & 63u);
+      if (s < n) {
+        const SysParams<T> P = sp[b];
+        T xi[D];
+        load_point<T, D>(xs, s, xi);
+        const T ai = NA ? a_s[s] : T(0);
+        const T r = P.r, r2 = P.r2;
         auto visit = [&](uint32_t j, const T* dx, T d2) {
             const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
             Op::fwd(q, r, dx, d2, ai, aj, acc);
@@ -380,7 +409,6 @@ __global__ __launch_bounds__(256) void k_lane_mask(const T* __restrict__ xs, con
             if (__ballot(P.n[0] < 2 * P.reach[0] + 1) == 0ull) {
                 // Every grid of the wave is at least 2 m + 1 cells wide: each row's main
                 // runs are staged in LDS (below); otherwise the plain walk.
-                __shared__ VecN<T, PITCH> win[kBlockWaves][kWindow];
                 auto win_piece = [&](uint32_t j0, uint32_t j1, const T* sh, const char* wb, uint32_t lo) {
                     j1 = max(j1, j0);
                     if (__ballot(sh[1] != T(0) || sh[2] != T(0)) != 0ull)
@@ -389,24 +417,34 @@ __global__ __launch_bounds__(256) void k_lane_mask(const T* __restrict__ xs, con
                         scan_window(std::integral_constant<bool, false>(), j0, j1, sh, rec, wb, lo);
                     pos += j1 - j0;
                 };
-                staged_rows<T, D, 0>(P, off, n, xi, xs, nullptr, reinterpret_cast<char*>(&win[threadIdx.x >> 6][0]),
-                                     begin_row, piece, end_row, win_piece);
+                staged_rows<T, D, 0>(P, off, n, xi, xs, nullptr, wave_wb, begin_row, piece, end_row, win_piece, row_done,
+                                     w.range);
             } else {
-                for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row);
+                for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
             }
         } else {
-            for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row);
+            for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
         }
-        status[s] = overflow ? kGenNone : gen[0];
-        const uint32_t o = perm[s];
+        if (SPLIT && split > 1) row_ovf[w.wave * 64] = overflow ? 1u : 0u;
+      }
+      if (!ws.finish(w, n)) return;
+      if (SPLIT && split > 1)
+          for (int32_t q = 0; q < split; ++q) overflow |= row_ovf[q * 64] != 0u;
+      status[s] = overflow ? kGenNone : gen[0];
+      const uint32_t o = perm[s];
 #pragma unroll
-        for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = acc[k];
+      for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = sums.tot[k];
     } else {
+      if (s < n) {
+        const SysParams<T> P = sp[b];
+        T xi[D];
+        load_point<T, D>(xs, s, xi);
+        const T ai = NA ? a_s[s] : T(0);
+        const T r = P.r, r2 = P.r2;
         T gyi[NY];
         load_gy<T, NY, OFF32>(gy_s, s, gyi);
-        T accx[D], acca[1] = {T(0)};
-#pragma unroll
-        for (int k = 0; k < D; ++k) accx[k] = T(0);
+        T* const accx = acc;
+        T* const acca = acc + (NA ? D : 0);
         auto pair = [&](uint32_t j, const T* dx, T d2, const T* gyj) {
             const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
             Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
@@ -504,20 +542,17 @@ __global__ __launch_bounds__(256) void k_lane_mask(const T* __restrict__ xs, con
                 if (__ballot(P.n[0] < 2 * P.reach[0] + 1) == 0ull) {
                     // as in the forward: each row's main runs from the wave's LDS window
                     // (positions, then the gy rows)
-                    constexpr int kWinRows = kWindow * (int)(sizeof(VecN<T, PITCH>) + sizeof(VecN<T, GP>)) /
-                                             (int)sizeof(VecN<T, 4>);
-                    __shared__ VecN<T, 4> win[kBlockWaves][kWinRows];
-                    staged_rows<T, D, GP>(P, off, n, xi, xs, gy_s, reinterpret_cast<char*>(&win[threadIdx.x >> 6][0]),
-                                          begin_row, piece, end_row,
+                    staged_rows<T, D, GP>(P, off, n, xi, xs, gy_s, wave_wb, begin_row, piece, end_row,
                                           [&](uint32_t j0, uint32_t j1, const T* sh, const char* wb, uint32_t lo) {
                                               const uint64_t bits = piece_bits(j0, j1);
                                               replay(std::integral_constant<bool, true>(), j0, bits, sh, wb, lo);
-                                          });
+                                          },
+                                          row_done, w.range);
                 } else {
-                    for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row);
+                    for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
                 }
             } else {
-                for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row);
+                for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
             }
         } else {
             // no record: the plain row search (not its deferred form, whose
@@ -526,12 +561,14 @@ __global__ __launch_bounds__(256) void k_lane_mask(const T* __restrict__ xs, con
                 const VecN<T, GP> gj = load_row<T, GP, OFF32>(gy_s, j);
                 pair(j, dx, d2, gj.v);
             };
-            neighbour_loop<T, D, OFF32>(P, xs, off, n, xi, visit);
+            neighbour_loop<T, D, OFF32>(P, xs, off, n, xi, visit, row_done, w.range);
         }
-        const uint32_t o = perm[s];
+      }
+      if (!ws.finish(w, n)) return;
+      const uint32_t o = perm[s];
 #pragma unroll
-        for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = accx[k];
-        if (OpShape<OP, D>::NA && ga) ga[o] = acca[0];
+      for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = sums.tot[k];
+      if (NA && ga) ga[o] = sums.tot[D + NA - 1];
     }
 }
 
@@ -780,35 +817,32 @@ void launch_half_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q,
     }
 }
 
-template <typename T, int D, int OP, bool BATCH>
-void launch_mask_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y) {
+template <typename T, int D, int OP, bool BATCH, int MODE>
+void launch_mask(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* y, T* gx,
+                 T* ga) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-    const dim3 grid((n + 255) / 256);
-    if (off32_rows<T>(n))
-        hipLaunchKernelGGL((k_lane_mask<T, D, OP, BATCH, true, 0>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs,
-                           c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, nullptr, q, y, nullptr, nullptr,
-                           c->masks, c->mask_status, c->gen);
-    else
-        hipLaunchKernelGGL((k_lane_mask<T, D, OP, BATCH, false, 0>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs,
-                           c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, nullptr, q, y, nullptr, nullptr,
-                           c->masks, c->mask_status, c->gen);
+    using MS = MaskSums<MODE, OP, D>;
+    const SearchShape sh = search_shape(ctx, c, MS::template WindowSize<T>, MS::template PartSize<T>);
+#define LM(O, S)                                                                                                    \
+    hipLaunchKernelGGL((k_lane_mask<T, D, OP, BATCH, O, MODE, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds,       \
+                       ctx->stream, (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, \
+                       y, gx, ga, c->masks, c->mask_status, c->gen, sh.split)
+    if (sh.split > 0) LM(true, (D > 1));
+    else if (off32_rows<T>(n)) LM(true, false);
+    else LM(false, false);
+#undef LM
+}
+
+template <typename T, int D, int OP, bool BATCH>
+void launch_mask_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y) {
+    launch_mask<T, D, OP, BATCH, 0>(ctx, c, q, a_s, nullptr, y, nullptr, nullptr);
 }
 
 template <typename T, int D, int OP, bool BATCH>
 void launch_mask_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
                      T* ga) {
-    const uint32_t n = (uint32_t)c->n;
-    const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-    const dim3 grid((n + 255) / 256);
-    if (off32_rows<T>(n))
-        hipLaunchKernelGGL((k_lane_mask<T, D, OP, BATCH, true, 1>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs,
-                           c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, nullptr, gx, ga,
-                           c->masks, c->mask_status, c->gen);
-    else
-        hipLaunchKernelGGL((k_lane_mask<T, D, OP, BATCH, false, 1>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs,
-                           c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, nullptr, gx, ga,
-                           c->masks, c->mask_status, c->gen);
+    launch_mask<T, D, OP, BATCH, 1>(ctx, c, q, a_s, gy_s, nullptr, gx, ga);
 }
 
 #define ABORIA_INST(T, D, OP, BATCH)                                                                          \

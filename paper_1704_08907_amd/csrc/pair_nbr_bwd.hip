@@ -17,7 +17,7 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
                                                  const uint32_t* __restrict__ nbr_count, uint32_t cap,
                                                  const uint32_t* __restrict__ gen, const T* __restrict__ a_s,
                                                  const T* __restrict__ gy_s, OpArgs<T> q, T* __restrict__ gx,
-                                                 T* __restrict__ ga) {
+                                                 T* __restrict__ ga, bool by_rows) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
@@ -30,9 +30,10 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
     const T ai = OpShape<OP, D>::NA ? a_s[s] : T(0);
     T gyi[NY];
     load_gy<T, NY>(gy_s, s, gyi);
-    T accx[D], acca[1] = {T(0)};
-#pragma unroll
-    for (int k = 0; k < D; ++k) accx[k] = T(0);
+    constexpr int NA = OpShape<OP, D>::NA;
+    RowSums<T, D + NA> sums(by_rows);
+    T* const accx = sums.acc;
+    T* const acca = accx + (NA ? D : 0);
     const T r = P.r;
     auto pair = [&](uint32_t j, const T* dx, T d2) {
         const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
@@ -41,16 +42,17 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
         Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
     };
     const uint32_t cnt = nbr_count[s];
-    if (gen[0] == gen[1] && cnt <= cap) {
-        replay_list<T, D>(P, xs, nbr, n, s, cnt, xi, pair);
+    if (gen[0] == gen[1] && cnt <= cap && n <= kNbrSlot + 1u) {
+        replay_list<T, D>(P, xs, nbr, n, s, cnt, xi, pair, [&](bool first) { sums.row_done_if(first & by_rows); });
     } else {
         auto visit = [&](uint32_t j, const T* dx, T d2, bool) { pair(j, dx, d2); };
-        neighbour_loop<T, D>(P, xs, off, n, xi, visit);
+        neighbour_loop<T, D>(P, xs, off, n, xi, visit, [&](int32_t) { sums.row_done(); });
     }
+    sums.last();
     const uint32_t o = perm[s];
 #pragma unroll
-    for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = accx[k];
-    if (OpShape<OP, D>::NA && ga) ga[o] = acca[0];
+    for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = sums.tot[k];
+    if (NA && ga) ga[o] = sums.tot[D + NA - 1];
 }
 
 template <typename T, int D, int OP, bool BATCH>
@@ -59,7 +61,8 @@ void launch_nbr_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, 
     const uint32_t n = (uint32_t)c->n;
     hipLaunchKernelGGL((k_nbr_bwd<T, D, OP, BATCH>), dim3((n + 255) / 256), dim3(256), 0, ctx->stream,
                        (const T*)c->xs, c->off, c->perm, n, reinterpret_cast<const SysParams<T>*>(c->params_dev),
-                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen, a_s, gy_s, q, gx, ga);
+                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen, a_s, gy_s, q, gx, ga,
+                       row_split(c) > 0);
 }
 
 #define ABORIA_INST(T, D, OP, BATCH)                                                                         \

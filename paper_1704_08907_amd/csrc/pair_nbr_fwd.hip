@@ -16,7 +16,7 @@ __global__ __launch_bounds__(256) void k_nbr_fwd(const T* __restrict__ xs, const
                                                  const uint32_t* __restrict__ nbr,
                                                  const uint32_t* __restrict__ nbr_count, uint32_t cap,
                                                  const uint32_t* __restrict__ gen, const T* __restrict__ a_s,
-                                                 OpArgs<T> q, T* __restrict__ y) {
+                                                 OpArgs<T> q, T* __restrict__ y, bool by_rows) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
@@ -27,27 +27,27 @@ __global__ __launch_bounds__(256) void k_nbr_fwd(const T* __restrict__ xs, const
     T xi[D];
     load_point<T, D>(xs, s, xi);
     const T ai = OpShape<OP, D>::NA ? a_s[s] : T(0);
-    T acc[NY];
-#pragma unroll
-    for (int k = 0; k < NY; ++k) acc[k] = T(0);
+    RowSums<T, NY> sums(by_rows);
+    T* const acc = sums.acc;
     const T r = P.r;
     const uint32_t cnt = nbr_count[s];
-    if (gen[0] == gen[1] && cnt <= cap) {
+    if (gen[0] == gen[1] && cnt <= cap && n <= kNbrSlot + 1u) {
         auto visit = [&](uint32_t j, const T* dx, T d2) {
             const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
             Op::fwd(q, r, dx, d2, ai, aj, acc);
         };
-        replay_list<T, D>(P, xs, nbr, n, s, cnt, xi, visit);
+        replay_list<T, D>(P, xs, nbr, n, s, cnt, xi, visit, [&](bool first) { sums.row_done_if(first & by_rows); });
     } else {
         auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
             const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
             Op::fwd(q, r, dx, d2, ai, aj, acc);
         };
-        neighbour_loop<T, D>(P, xs, off, n, xi, visit);
+        neighbour_loop<T, D>(P, xs, off, n, xi, visit, [&](int32_t) { sums.row_done(); });
     }
+    sums.last();
     const uint32_t o = perm[s];
 #pragma unroll
-    for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = acc[k];
+    for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = sums.tot[k];
 }
 
 template <typename T, int D, int OP, bool BATCH>
@@ -55,7 +55,8 @@ void launch_nbr_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, 
     const uint32_t n = (uint32_t)c->n;
     hipLaunchKernelGGL((k_nbr_fwd<T, D, OP, BATCH>), dim3((n + 255) / 256), dim3(256), 0, ctx->stream,
                        (const T*)c->xs, c->off, c->perm, n, reinterpret_cast<const SysParams<T>*>(c->params_dev),
-                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen, a_s, q, y);
+                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen, a_s, q, y,
+                       row_split(c) > 0);
 }
 
 #define ABORIA_INST(T, D, OP, BATCH) \

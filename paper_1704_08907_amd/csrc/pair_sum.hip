@@ -89,17 +89,16 @@ struct Variant {
     int kind;   // 0 = lane per particle, 2 = recorded neighbour list, 3 = all pairs,
                 // 5 = flattened pruned search, 6 = lane per particle with recorded
                 // accepted-pair masks, 7 = half stencil (forward; the adjoint is kind 0's)
-    int block;  // threads per workgroup
     const char* name;
 };
 
 const Variant kVariants[] = {
-    {0, 256, "lane per particle, 256-thread workgroups, adjoint evaluated on every candidate"},
-    {2, 256, "lane per particle over the recorded neighbour list (accepted pairs only)"},
-    {3, 256, "lane per particle over all particles of its system (minimum image; small systems)"},
-    {5, 256, "lane per particle, flattened box search over pruned slot ranges listed in LDS"},
-    {6, 256, "lane per particle, forward records accepted-pair bit masks per stencil row, adjoint replays them"},
-    {7, 256, "lane per particle, half stencil: each pair tested once, the partner reads the recorded bit"},
+    {0, "lane per particle, 256-thread workgroups, adjoint evaluated on every candidate"},
+    {2, "lane per particle over the recorded neighbour list (accepted pairs only)"},
+    {3, "lane per particle over all particles of its system (minimum image; small systems)"},
+    {5, "lane per particle, flattened box search over pruned slot ranges listed in LDS"},
+    {6, "lane per particle, forward records accepted-pair bit masks per stencil row, adjoint replays them"},
+    {7, "lane per particle, half stencil: each pair tested once, the partner reads the recorded bit"},
 };
 
 // Modes of the flattened kernel (pair_flat.hpp).
@@ -153,7 +152,7 @@ void launch_fwd_variant(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>&
     else if (v.kind == 5) launch_flat<T, D, OP, BATCH, kFlatModeFwd>(ctx, c, q, a_s, nullptr, y, nullptr, nullptr);
     else if (v.kind == 3) launch_all_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else if (v.kind == 2) launch_nbr_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
-    else launch_lane_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y, v.block);
+    else launch_lane_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
 }
 
 template <typename T, int D, int OP, bool BATCH>
@@ -163,7 +162,7 @@ void launch_bwd_variant(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>&
     else if (v.kind == 5) launch_flat<T, D, OP, BATCH, kFlatModeBwd>(ctx, c, q, a_s, gy_s, nullptr, gx, ga);
     else if (v.kind == 3) launch_all_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
     else if (v.kind == 2) launch_nbr_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
-    else launch_lane_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga, v.block);
+    else launch_lane_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
 }
 
 const Variant& variant_of(int variant) { return kVariants[(variant < 0 || variant >= kNumVariants) ? 0 : variant]; }
@@ -261,6 +260,35 @@ aboria_status check_variant(aboria_ctx* ctx, const aboria_cells* c, int variant)
 }
 
 }  // namespace
+
+// How many waves share the rows of 64 particles (3^(d-1) rows where the grid is
+// searched one cell deep in y and z): a wave per row up to 640 waves of particles,
+// three up to 10000, above it one wave with a running sum.  A wave takes tens of
+// microseconds for nine rows, most of it waiting, so the chip wants several waves on
+// each of its 1024 SIMDs more than it minds their set-up; where 64 particles a wave
+// already give ten or more, the set-up is all that is left.  Measured with 1 / 3 / 9
+// waves, forward and adjoint, us: 5000 particles (3-d, 30 neighbours, float32)
+// 48 / 20 / 9.4 and 64 / 29 / 14.4; 20000: 39 / 16.5 / 10.2 and 55 / 25 / 15.7; 60000 in
+// float64: 52 / 27 / 29.6 and 66 / 38 / 47; 100003: 49 / 25 / 34 and 49 / 34 / 41; 2^18
+// (soft sphere, 40 neighbours) 60 / 50 / 71 and 84 / 71 / 103; 2^19: 80 / 75 / 128 and
+// 130 / 116 / 168; 2^20: 122 / 123 / 222 and 204 / 206 / 316 (forward and adjoint in one
+// call 201 / 231).  2-d, 300007: 20.4 / 17.6 and 32 / 28.
+int32_t row_split(const aboria_cells* c) {
+    const uint64_t waves = ((uint64_t)c->n + 63) / 64;
+    const int32_t rows = c->d == 1 ? 1 : (c->d == 2 ? 3 : 9);
+    if (rows == 1 || !rows_reach1(c)) return 0;
+    return waves <= 640 ? rows : (waves <= 10000 ? 3 : 0);
+}
+
+SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, uint32_t wave_bytes, uint32_t part_bytes) {
+    const uint32_t waves = (uint32_t)(((uint64_t)c->n + 63) / 64);
+    int32_t split = row_split(c);
+    // fewer waves (the same sums) where their windows would not fit a workgroup's LDS
+    if (split > 3 && (uint32_t)split * wave_bytes + part_bytes > lds_limit(ctx)) split = 3;
+    if (split > 1 && (uint32_t)split * wave_bytes + part_bytes > lds_limit(ctx)) split = 1;
+    if (split <= 1) return SearchShape{split, (waves + 3) / 4, 256, 4 * wave_bytes};
+    return SearchShape{split, waves, 64u * (uint32_t)split, (uint32_t)split * wave_bytes + part_bytes};
+}
 
 int32_t variant_count() { return kNumVariants; }
 
