@@ -199,8 +199,8 @@ aboria_status aboria_cells_destroy(aboria_cells* cells);
 
 /* Shape of the RADIX build (Section 2.2.1's sort into cell order): keys per
  * thread of a sort tile of 256 threads (4, 8 or 16: tiles of 1024 to 4096
- * keys), the key bits the last pass sorts per bucket of cells in LDS (8 to 10;
- * the radix passes take the remaining high bits) and whether a radix pass
+ * keys), the key bits the last pass sorts per bucket of cells in LDS (8 to 10, the
+ * rule may take fewer; the radix passes take the remaining high bits) and whether a radix pass
  * shuffles its tile into digit order in LDS before writing (1: where the LDS
  * fits, 2: never).  The shape does not change the cell list, only the work
  * mapping of its build.  aboria_set_build_shape fixes it for cell lists

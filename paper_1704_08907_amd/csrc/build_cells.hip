@@ -142,15 +142,30 @@ __global__ __launch_bounds__(IdsThreads<IPT>::value) void k_cell_ids_hist(const 
     bool bad = false;
     uint32_t key[KPT];
     // all keys first (their position loads in flight together), then the histogram
+    auto take = [&](const SysParams<T>& P, int k, uint32_t i) {
+        key[k] = cell_key<T, D>(P, x, i, &bad);
+        keys[i] = key[k];
+    };
+    const int bu = __builtin_amdgcn_readfirstlane(b);
+    if (!BATCH || bu + 1 >= nsys || sys_part[bu + 1] >= base + kBlock * IPT) {
+        // the whole tile in one system, as most are: its parameters come through the
+        // scalar cache (5.8 M particles in 512 systems: 52 -> 46 us)
+        const SysParams<T>& P = sp[bu];
 #pragma unroll
-    for (int k = 0; k < KPT; ++k) {
-        const uint32_t i = base + k * NT + threadIdx.x;
-        key[k] = 0u;
-        if (i < n) {
-            if (BATCH)
+        for (int k = 0; k < KPT; ++k) {
+            const uint32_t i = base + k * NT + threadIdx.x;
+            key[k] = 0u;
+            if (i < n) take(P, k, i);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < KPT; ++k) {
+            const uint32_t i = base + k * NT + threadIdx.x;
+            key[k] = 0u;
+            if (i < n) {
                 while (b + 1 < nsys && sys_part[b + 1] <= i) ++b;
-            key[k] = cell_key<T, D>(sp[b], x, i, &bad);
-            keys[i] = key[k];
+                take(sp[b], k, i);
+            }
         }
     }
 #pragma unroll
@@ -445,20 +460,34 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint32_t* __restric
     for (uint32_t d = threadIdx.x; d < radix; d += kBlock) hist[(size_t)d * ntiles + tile] = lds[d];
 }
 
-// Stable scatter of one tile of kBlock * IPT keys.  Wave w owns keys
-// [w * 64 IPT, (w + 1) * 64 IPT) of the tile and walks them in IPT steps of 64
-// consecutive keys.  Lanes holding the
+// Stable scatter of one tile of kBlock * IPT keys by eight waves.  Wave w owns
+// kBlock * IPT / 8 consecutive keys of the tile and walks them in steps of 64.
+// Lanes holding the
 // same digit find each other with one ballot per digit bit; a lane's rank is
 // the number of such lanes below it plus the wave's running count for the
 // digit (kept in LDS, updated by the lowest such lane).  After all waves are
 // done the per-wave counts become per-wave offsets, and the tile is shuffled
-// into digit order in LDS, so that keys and indices leave in one contiguous
-// run per digit instead of one scattered 4-byte store per lane.  The position
+// into digit order in LDS, over the counts, so that keys and indices leave in one
+// contiguous run per digit instead of one scattered 4-byte store per lane.  The position
 // rows ride along as a payload (FIRST: read from the caller's x in original
 // order; later passes: from the previous pass's payload), so that the bucket
 // pass reads them in order instead of gathering them by index.
+// Bound by the latency of its dependent steps, at two tiles of 2048 rows per CU (LDS):
+// 2^20 particles 17.6 us (42 MB), 21.3 with four waves a tile and the rows loaded after
+// the ranking.
+constexpr int kScatterThreads = 512;
+constexpr int kScatterWaves = kScatterThreads / kWave;
+
+// LDS words of a scatter workgroup: the digits' global and tile starts, then the
+// per-wave counts or (shuffled) the tile's rows, keys and indices.
+inline size_t scatter_lds(uint32_t radix, size_t tile_keys, bool shuffle, size_t row_bytes) {
+    const size_t counts = (size_t)kScatterWaves * radix * sizeof(uint32_t);
+    const size_t tile = shuffle ? tile_keys * (2 * sizeof(uint32_t) + row_bytes) : 0;
+    return std::max<size_t>(2 * radix, 8) * sizeof(uint32_t) + std::max(counts, tile);
+}
+
 template <typename T, int D, bool FIRST, bool SHUFFLE, bool PAYLOAD, int IPT>
-__global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __restrict__ keys_in,
+__global__ __launch_bounds__(kScatterThreads) void k_radix_scatter(const uint32_t* __restrict__ keys_in,
                                                           const uint32_t* __restrict__ vals_in,
                                                           const T* __restrict__ x,
                                                           const VecN<T, Pitch<D>::value>* __restrict__ pay_in,
@@ -469,48 +498,63 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __rest
                                                           const uint32_t* __restrict__ block_sums, uint32_t ntiles,
                                                           int top_done, uint32_t* __restrict__ top_out) {
     constexpr int PITCH = Pitch<D>::value;
+    using Row = VecN<T, PITCH>;
     constexpr int kSortTile = kBlock * IPT;
-    extern __shared__ uint32_t lds[];
-    __shared__ uint32_t s_wsum[4];
+    constexpr int NT = kScatterThreads, NW = kScatterWaves;
+    constexpr int KPT = kSortTile / NT;
+    extern __shared__ __align__(32) uint32_t lds[];
+    __shared__ uint32_t s_wsum[NW];
     __shared__ uint32_t s_top[kTopInline];  // exclusive prefix of the scan blocks' totals
     const uint32_t radix = 1u << bits, mask = radix - 1;
-    uint32_t* cnt = lds;                 // [4][radix] per-wave counts, then per-wave offsets
-    uint32_t* gbase = lds + 4 * radix;   // [radix] first global slot of the tile's keys of a digit
-    uint32_t* tstart = lds + 5 * radix;  // [radix] first tile slot of a digit
-    uint32_t* sk = lds + 6 * radix;      // [kSortTile] keys in digit order
-    uint32_t* sv = sk + kSortTile;       // [kSortTile] indices in digit order
-    // [kSortTile] position rows in digit order (SHUFFLE and PAYLOAD)
-    VecN<T, PITCH>* srow = reinterpret_cast<VecN<T, PITCH>*>(sv + kSortTile);
+    uint32_t* gbase = lds;           // [radix] first global slot of the tile's keys of a digit
+    uint32_t* tstart = lds + radix;  // [radix] first tile slot of a digit
+    uint32_t* cnt = lds + max(2 * radix, 8u);  // [NW][radix] per-wave counts, then per-wave offsets
+    // over the counts: the tile in digit order (its rows first, 32-byte aligned)
+    Row* srow = reinterpret_cast<Row*>(cnt);
+    uint32_t* sk = PAYLOAD ? reinterpret_cast<uint32_t*>(srow + kSortTile) : cnt;
+    uint32_t* sv = sk + kSortTile;
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);  // neighbouring tiles share an XCD's L2
     const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t tbase = tile * kSortTile;
-    const uint32_t wbase = tbase + w * (kWave * IPT);
-    uint32_t key[IPT], val[IPT], loc[IPT];
-    // the tile's key and index loads first, so they are in flight together and
-    // with the histogram reads below
+    const uint32_t wbase = tbase + w * (kWave * KPT);
+    uint32_t key[KPT], val[KPT], loc[KPT];
+    Row row[PAYLOAD ? KPT : 1];
+    // the tile's loads first, so they are in flight together and with the histogram
+    // reads below
 #pragma unroll
-    for (int s = 0; s < IPT; ++s) {
+    for (int s = 0; s < KPT; ++s) {
         const uint32_t idx = wbase + s * kWave + lane;
         const bool valid = idx < n;
         key[s] = valid ? keys_in[idx] : 0u;
         val[s] = valid ? (FIRST ? idx : vals_in[idx]) : 0u;
+        if constexpr (PAYLOAD) {
+            if (valid) {
+                if constexpr (FIRST) {
+#pragma unroll
+                    for (int k = 0; k < PITCH; ++k) row[s].v[k] = k < D ? x[(size_t)idx * D + k] : T(0);
+                } else {
+                    row[s] = pay_in[idx];
+                }
+            }
+        }
     }
+    for (uint32_t d = threadIdx.x; d < NW * radix; d += NT) cnt[d] = 0;
     if (!top_done) {
         // the top level of the histogram scan: every tile prefix-sums the scan
         // blocks' totals itself (tile 0 also stores them for the bucket pass)
         const uint32_t nb = (radix * ntiles + kScanTile - 1) / kScanTile;
-        uint32_t v[kTopInline / kBlock], tot = 0;
+        uint32_t v[kTopInline / NT], tot = 0;
 #pragma unroll
-        for (int q = 0; q < kTopInline / kBlock; ++q) {
-            const uint32_t b = threadIdx.x * (kTopInline / kBlock) + q;
+        for (int q = 0; q < kTopInline / NT; ++q) {
+            const uint32_t b = threadIdx.x * (kTopInline / NT) + q;
             v[q] = b < nb ? block_sums[b] : 0u;
             tot += v[q];
         }
         uint32_t total;
-        uint32_t ex = block_exclusive_scan(tot, s_wsum, &total);
+        uint32_t ex = block_exclusive_scan_w<NW>(tot, s_wsum, &total);
 #pragma unroll
-        for (int q = 0; q < kTopInline / kBlock; ++q) {
-            const uint32_t b = threadIdx.x * (kTopInline / kBlock) + q;
+        for (int q = 0; q < kTopInline / NT; ++q) {
+            const uint32_t b = threadIdx.x * (kTopInline / NT) + q;
             if (b < nb) {
                 s_top[b] = ex;
                 if (tile == 0) top_out[b] = ex;
@@ -519,11 +563,7 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __rest
         }
         __syncthreads();
     }
-    for (uint32_t d = threadIdx.x; d < radix; d += kBlock) {
-        cnt[d] = 0;
-        cnt[radix + d] = 0;
-        cnt[2 * radix + d] = 0;
-        cnt[3 * radix + d] = 0;
+    for (uint32_t d = threadIdx.x; d < radix; d += NT) {
         size_t p = (size_t)d * ntiles + tile;
         gbase[d] = hist_scan[p] + (top_done ? block_sums[p / kScanTile] : s_top[p / kScanTile]);
     }
@@ -531,11 +571,9 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __rest
     uint32_t* wc = cnt + w * radix;
     const uint64_t lt = lanemask_lt();
 #pragma unroll
-    for (int s = 0; s < IPT; ++s) {
-        const uint32_t idx = wbase + s * kWave + lane;
-        const bool valid = idx < n;
-        const uint32_t k = key[s];
-        const uint32_t dg = (k >> shift) & mask;
+    for (int s = 0; s < KPT; ++s) {
+        const bool valid = wbase + s * kWave + lane < n;
+        const uint32_t dg = (key[s] >> shift) & mask;
         uint64_t peers = __ballot(valid);
         for (int b = 0; b < bits; ++b) {
             const bool bit = (dg >> b) & 1u;
@@ -549,69 +587,63 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __rest
     }
     __syncthreads();
     {   // per digit: offsets of the waves, and the tile's exclusive scan over digits
-        constexpr uint32_t kMaxPer = (1u << kMaxDigitBits) / kBlock;
-        const uint32_t per = radix >= (uint32_t)kBlock ? radix / kBlock : 1u;
+        constexpr int kMaxPer = (1 << kMaxDigitBits) / NT > 0 ? (1 << kMaxDigitBits) / NT : 1;
+        const uint32_t per = radix >= (uint32_t)NT ? radix / NT : 1u;
         const uint32_t d0 = threadIdx.x * per;
-        uint32_t tot[kMaxPer > 0 ? kMaxPer : 1];
-        uint32_t sum = 0;
-        for (uint32_t q = 0; q < per; ++q) {
-            tot[q] = 0;
-            const uint32_t d = d0 + q;
-            if (d < radix) {
-                const uint32_t a0 = cnt[d], a1 = cnt[radix + d], a2 = cnt[2 * radix + d], a3 = cnt[3 * radix + d];
-                cnt[d] = 0;
-                cnt[radix + d] = a0;
-                cnt[2 * radix + d] = a0 + a1;
-                cnt[3 * radix + d] = a0 + a1 + a2;
-                tot[q] = a0 + a1 + a2 + a3;
-                sum += tot[q];
+        uint32_t tot[kMaxPer], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxPer; ++k) {
+            tot[k] = 0;
+            const uint32_t d = d0 + k;
+            if ((uint32_t)k < per && d < radix) {
+#pragma unroll
+                for (int q = 0; q < NW; ++q) {
+                    const uint32_t c = cnt[q * radix + d];
+                    cnt[q * radix + d] = tot[k];
+                    tot[k] += c;
+                }
+                sum += tot[k];
             }
         }
         uint32_t total;
-        uint32_t ex = block_exclusive_scan(sum, s_wsum, &total);
-        for (uint32_t q = 0; q < per; ++q) {
-            const uint32_t d = d0 + q;
-            if (d < radix) {
-                tstart[d] = ex;
-                ex += tot[q];
+        uint32_t ex = block_exclusive_scan_w<NW>(sum, s_wsum, &total);
+#pragma unroll
+        for (int k = 0; k < kMaxPer; ++k) {
+            if ((uint32_t)k < per && d0 + k < radix) {
+                tstart[d0 + k] = ex;
+                ex += tot[k];
             }
         }
     }
     __syncthreads();
 #pragma unroll
-    for (int s = 0; s < IPT; ++s) {
-        const uint32_t idx = wbase + s * kWave + lane;
-        if (idx < n) {
-            const uint32_t dg = (key[s] >> shift) & mask;
-            const uint32_t off_d = wc[dg] + loc[s];
-            const uint32_t tl = tstart[dg] + off_d;
-            const uint32_t pos = gbase[dg] + off_d;
-            if (tl < (uint32_t)kSortTile && pos < n) {  // always true for a consistent histogram
-                if (SHUFFLE) {
-                    sk[tl] = key[s];
-                    sv[tl] = val[s];
-                } else {
-                    keys_out[pos] = key[s];
-                    vals_out[pos] = val[s];
-                }
-                if (PAYLOAD) {
-                    VecN<T, PITCH> row;
-                    if (FIRST) {
+    for (int s = 0; s < KPT; ++s) {
+        const uint32_t dg = (key[s] >> shift) & mask;
+        loc[s] += wc[dg] + (SHUFFLE ? tstart[dg] : gbase[dg]);
+    }
+    if constexpr (!SHUFFLE) {
 #pragma unroll
-                        for (int k = 0; k < PITCH; ++k) row.v[k] = k < D ? x[(size_t)idx * D + k] : T(0);
-                    } else {
-                        row = pay_in[idx];
-                    }
-                    if (SHUFFLE) srow[tl] = row;  // leaves with its key, in digit order
-                    else pay_out[pos] = row;
-                }
+        for (int s = 0; s < KPT; ++s) {
+            if (wbase + s * kWave + lane < n && loc[s] < n) {  // (always below n for a consistent histogram)
+                keys_out[loc[s]] = key[s];
+                vals_out[loc[s]] = val[s];
+                if constexpr (PAYLOAD) pay_out[loc[s]] = row[s];
             }
         }
+        return;
     }
-    if (!SHUFFLE) return;
+    __syncthreads();  // the counts make way
+#pragma unroll
+    for (int s = 0; s < KPT; ++s) {
+        if (wbase + s * kWave + lane < n && loc[s] < (uint32_t)kSortTile) {  // (likewise)
+            sk[loc[s]] = key[s];
+            sv[loc[s]] = val[s];
+            if constexpr (PAYLOAD) srow[loc[s]] = row[s];  // leaves with its key, in digit order
+        }
+    }
     __syncthreads();
     const uint32_t count = min((uint32_t)kSortTile, n - tbase);
-    for (uint32_t i = threadIdx.x; i < count; i += kBlock) {
+    for (uint32_t i = threadIdx.x; i < count; i += NT) {
         const uint32_t k = sk[i];
         const uint32_t dg = (k >> shift) & mask;
         const uint32_t pos = gbase[dg] + (i - tstart[dg]);
@@ -629,45 +661,52 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(const uint32_t* __rest
 
 // The input is sorted (stably) by key >> lb, so bucket b -- the cells
 // [b << lb, (b + 1) << lb) -- is one contiguous range of it, in original index
-// order.  One workgroup per bucket: it histograms the low digit of its keys in
-// LDS, writes the offsets of its cells (bucket start + exclusive scan), and
-// places its elements stably, chunk by chunk, with the same wave-ballot ranks
-// as k_radix_scatter, writing the sorted key, the permutation and the position
-// gathered from the original array.  Buckets cover cells 0..ncells inclusive,
-// so off[ncells] = n is written too.
+// order.  One workgroup per bucket: wave-ballot ranks as in k_radix_scatter give
+// each key its stable place among its cell's, the per-wave counts the cells'
+// offsets (bucket start + exclusive scan, written out), and the bucket is put in
+// order in LDS, over the counts, which are no longer needed, and leaves as contiguous
+// runs of keys, permutation and positions.  ROWS: the positions (carried with the keys
+// by the radix passes in pay, or read by index) are loaded with the keys and put in
+// order too; otherwise they are gathered as they leave (from the bucket's rows of pay,
+// or by index), for half the LDS.
+// Buckets cover cells 0..ncells inclusive, so off[ncells] = n is written too.
 // When exactly one radix pass sorted the high bits, its scanned digit-major
 // histogram (hist_scan + block_sums, ntiles tiles) gives each bucket's start
 // directly; otherwise (hist_scan == nullptr) the bounds are found by binary
 // search of the high parts.
-// Threads of a bucket workgroup: eight waves for sort tiles of 2048 keys or
-// more (two workgroups fit a CU's LDS, so sixteen waves hide the bucket's
-// loads), four below.
-template <int IPT>
-struct BucketThreads {
-    static constexpr int value = IPT >= 8 ? 512 : 256;
-};
-
-template <typename T, int D, int IPT, bool STAGE>
-__global__ __launch_bounds__(BucketThreads<IPT>::value) void k_bucket_finalize(const uint32_t* __restrict__ keys_in,
-                                                            const uint32_t* __restrict__ vals_in, uint32_t n,
-                                                            int lb, uint32_t ncells, const T* __restrict__ x,
-                                                            T* __restrict__ xs, uint32_t* __restrict__ keys_out,
-                                                            uint32_t* __restrict__ perm_out,
-                                                            uint32_t* __restrict__ off,
-                                                            const uint32_t* __restrict__ hist_scan,
-                                                            const uint32_t* __restrict__ block_sums, uint32_t ntiles,
-                                                            uint32_t ndigits,
-                                                            const VecN<T, Pitch<D>::value>* __restrict__ pay) {
+// What bounds it is the latency of its few dependent steps, so the LDS a bucket takes
+// (room for cap keys, about what the buckets hold) decides how many buckets a CU
+// runs at once.  2^20 particles, 1256 keys a bucket: 40 KB, four to a CU, 16.5 us (44 MB,
+// 2.7 TB/s); counts beside room for 2048 keys, two to a CU, took 20.6.  100003 particles
+// in buckets of 463 keys: 6.4 us, in 54 buckets of 1850 16.4.  5.8 M particles in 512
+// systems, 8500 keys a bucket, gathered late by 1024 threads: 126 us, chunk by chunk 255.
+// A bucket over cap keys is worked off in chunks of NT * KPT, with scattered stores.
+template <typename T, int D, int NT, int KPT, bool ROWS>
+__global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ? 4 : 8) void k_bucket_finalize(const uint32_t* __restrict__ keys_in,
+                                                        const uint32_t* __restrict__ vals_in, uint32_t n, int lb,
+                                                        uint32_t ncells, const T* __restrict__ x, T* __restrict__ xs,
+                                                        uint32_t* __restrict__ keys_out,
+                                                        uint32_t* __restrict__ perm_out, uint32_t* __restrict__ off,
+                                                        const uint32_t* __restrict__ hist_scan,
+                                                        const uint32_t* __restrict__ block_sums, uint32_t ntiles,
+                                                        uint32_t ndigits,
+                                                        const VecN<T, Pitch<D>::value>* __restrict__ pay,
+                                                        uint32_t cap) {
     constexpr int PITCH = Pitch<D>::value;
-    constexpr int kSortTile = kBlock * IPT;
-    constexpr int NT = BucketThreads<IPT>::value;
+    using Row = VecN<T, PITCH>;
     constexpr int NW = NT / kWave;
-    constexpr int KPT = kSortTile / NT;  // keys of a chunk per thread
-    extern __shared__ uint32_t lds[];
+    constexpr uint32_t kChunk = NT * KPT;
+    constexpr int kMaxPer = (1 << kMaxDigitBits) / NT > 0 ? (1 << kMaxDigitBits) / NT : 1;
+    extern __shared__ __align__(32) uint32_t lds[];
     const uint32_t R = 1u << lb, mask = R - 1u;
-    uint32_t* hist = lds;              // [R]
-    uint32_t* base = lds + R;          // [R] running destination base per digit
-    uint32_t* cnt = lds + 2 * R;       // [NW][R] per-wave counts of the current chunk
+    uint32_t* hist = lds;         // [R] keys per digit (buckets over cap)
+    uint32_t* base = lds + R;     // [R] running destination base per digit (buckets over cap)
+    uint32_t* cnt = lds + 2 * R;  // [NW][R] per-wave counts of the current chunk
+    // the ordered bucket, over the arrays above
+    Row* srow = reinterpret_cast<Row*>(lds);
+    uint32_t* sk = ROWS ? reinterpret_cast<uint32_t*>(srow + cap) : lds;
+    uint32_t* sv = sk + cap;
+    uint32_t* ssrc = sv + cap;  // !ROWS with pay: each key's place in the unordered bucket
     __shared__ uint32_t s_range[2];
     __shared__ uint32_t s_wsum[NW];
     const uint32_t bucket = blockIdx.x;
@@ -693,65 +732,43 @@ __global__ __launch_bounds__(BucketThreads<IPT>::value) void k_bucket_finalize(c
         }
         s_range[threadIdx.x] = lo;
     }
+    for (uint32_t d = threadIdx.x; d < NW * R; d += NT) cnt[d] = 0;
     __syncthreads();
     const uint32_t b0 = s_range[0], b1 = s_range[1];
-    // exclusive scan of hist into base and the offsets of the bucket's cells: each
-    // thread owns a run of R/NT digits (R >= NT) or one
-    auto scan_hist = [&]() {
-        const uint32_t per = R >= (uint32_t)NT ? R / NT : 1u;
-        const uint32_t d0 = threadIdx.x * per;
-        uint32_t tot = 0;
-        if (d0 < R)
-            for (uint32_t k = 0; k < per; ++k) tot += hist[d0 + k];
-        uint32_t total;
-        uint32_t ex = block_exclusive_scan_w<NW>(tot, s_wsum, &total);
-        if (d0 < R) {
-            for (uint32_t k = 0; k < per; ++k) {
-                const uint32_t c = cell0 + d0 + k;
-                base[d0 + k] = ex;
-                if (c <= ncells) off[c] = b0 + ex;
-                ex += hist[d0 + k];
-            }
+    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint64_t lt = lanemask_lt();
+    uint32_t* wc = cnt + w * R;
+    const uint32_t per = R >= (uint32_t)NT ? R / NT : 1u;  // digits a thread owns in the scans
+    const uint32_t d0 = threadIdx.x * per;
+    auto load_xrow = [&](uint32_t p) {
+        Row r;
+#pragma unroll
+        for (int k = 0; k < PITCH; ++k) r.v[k] = k < D ? x[(size_t)p * D + k] : T(0);
+        return r;
+    };
+    auto load_val = [&](uint32_t idx) { return min(vals_in ? vals_in[idx] : idx, n - 1u); };
+    // the chunk's keys and indices: every load first, so they are in flight together
+    // (without ROWS the indices are read when they are placed, for eight waves per SIMD).
+    // dl: a key's digit (its low 10 bits) and above it its place; its key is cell0 + digit.
+    uint32_t dl[KPT], val[ROWS ? KPT : 1];
+    constexpr uint32_t kDigit = (1u << kMaxDigitBits) - 1u;
+    auto load_chunk = [&](uint32_t chunk) {
+        const uint32_t wbase = chunk + w * (kWave * KPT);
+#pragma unroll
+        for (int st = 0; st < KPT; ++st) {
+            const uint32_t idx = wbase + st * kWave + lane;
+            const bool valid = idx < b1;
+            dl[st] = valid ? keys_in[idx] & mask : 0u;
+            if constexpr (ROWS) val[st] = valid ? load_val(idx) : 0u;
         }
     };
-    // A nonempty bucket that fits one chunk takes its histogram from the chunk's
-    // per-wave rank counts below; a larger (or empty) one counts its keys first.
-    const bool single = b1 > b0 && b1 - b0 <= (uint32_t)kSortTile;
-    if (!single) {
-        for (uint32_t d = threadIdx.x; d < R; d += NT) hist[d] = 0;
-        __syncthreads();
-        for (uint32_t i = b0 + threadIdx.x; i < b1; i += NT) atomicAdd(&hist[keys_in[i] & mask], 1u);
-        __syncthreads();
-        scan_hist();
-        __syncthreads();
-    }
-    const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t* wc = cnt + w * R;
-    const uint64_t lt = lanemask_lt();
-    for (uint32_t chunk = b0; chunk < b1; chunk += kSortTile) {
-        for (uint32_t d = threadIdx.x; d < R; d += NT) {
-#pragma unroll
-            for (int q = 0; q < NW; ++q) cnt[q * R + d] = 0;
-        }
-        __syncthreads();
+    // rank of each key among the wave's keys of its digit so far, counts in wc
+    auto rank_chunk = [&](uint32_t chunk) {
         const uint32_t wbase = chunk + w * (kWave * KPT);
-        uint32_t key[KPT], val[KPT], loc[KPT];
-        VecN<T, PITCH> row[KPT];
-        // every load of the chunk first, so they are in flight together
 #pragma unroll
         for (int st = 0; st < KPT; ++st) {
-            const uint32_t idx = wbase + st * kWave + lane;
-            const bool valid = idx < b1;
-            key[st] = valid ? keys_in[idx] : 0u;
-            val[st] = valid ? (vals_in ? vals_in[idx] : idx) : 0u;
-            if (pay && valid) row[st] = pay[idx];  // the row travelled with its key through the radix passes
-        }
-#pragma unroll
-        for (int st = 0; st < KPT; ++st) {
-            const uint32_t idx = wbase + st * kWave + lane;
-            const bool valid = idx < b1;
-            const uint32_t k = key[st];
-            const uint32_t dg = k & mask;
+            const bool valid = wbase + st * kWave + lane < b1;
+            const uint32_t dg = dl[st];
             uint64_t peers = __ballot(valid);
             for (int bb = 0; bb < lb; ++bb) {
                 const bool bit = (dg >> bb) & 1u;
@@ -761,20 +778,105 @@ __global__ __launch_bounds__(BucketThreads<IPT>::value) void k_bucket_finalize(c
             const uint32_t below = (uint32_t)__popcll(peers & lt);
             const uint32_t c = valid ? wc[dg] : 0u;
             if (valid && below == 0) wc[dg] = c + (uint32_t)__popcll(peers);
-            loc[st] = c + below;
+            dl[st] = dg | (c + below) << kMaxDigitBits;
+        }
+    };
+    if (b1 - b0 <= cap) {
+        // ---- the whole bucket at once (cap <= kChunk) ----
+        load_chunk(b0);
+        const uint32_t wbase = b0 + w * (kWave * KPT);
+        Row row[ROWS ? KPT : 1];
+        if constexpr (ROWS) {
+#pragma unroll
+            for (int st = 0; st < KPT; ++st)
+                if (wbase + st * kWave + lane < b1) row[st] = pay ? pay[wbase + st * kWave + lane] : load_xrow(val[st]);
+        }
+        rank_chunk(b0);
+        __syncthreads();
+        // each thread's digits: the waves' counts, their exclusive scan over the bucket,
+        // the cells' offsets and the waves' first places
+        uint32_t tot[kMaxPer], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxPer; ++k) {
+            tot[k] = 0;
+            if ((uint32_t)k < per && d0 + k < R) {
+#pragma unroll
+                for (int q = 0; q < NW; ++q) tot[k] += cnt[q * R + d0 + k];
+            }
+            sum += tot[k];
+        }
+        uint32_t total;
+        uint32_t ex = block_exclusive_scan_w<NW>(sum, s_wsum, &total);
+#pragma unroll
+        for (int k = 0; k < kMaxPer; ++k) {
+            if ((uint32_t)k < per && d0 + k < R) {
+                const uint32_t c = cell0 + d0 + k;
+                if (c <= ncells) off[c] = b0 + ex;
+                uint32_t run = ex;
+#pragma unroll
+                for (int q = 0; q < NW; ++q) {
+                    const uint32_t a = cnt[q * R + d0 + k];
+                    cnt[q * R + d0 + k] = run;
+                    run += a;
+                }
+                ex += tot[k];
+            }
         }
         __syncthreads();
-        if (single) {
-            for (uint32_t d = threadIdx.x; d < R; d += NT) {
-                uint32_t h = 0;
 #pragma unroll
-                for (int q = 0; q < NW; ++q) h += cnt[q * R + d];
-                hist[d] = h;
+        for (int st = 0; st < KPT; ++st) dl[st] += wc[dl[st] & kDigit] << kMaxDigitBits;
+        __syncthreads();  // the counts make way
+#pragma unroll
+        for (int st = 0; st < KPT; ++st) {
+            const uint32_t at = dl[st] >> kMaxDigitBits;
+            if (wbase + st * kWave + lane < b1 && at < cap) {  // (always below it for consistent input)
+                sk[at] = cell0 + (dl[st] & kDigit);
+                if constexpr (ROWS) sv[at] = val[st];
+                else sv[at] = load_val(wbase + st * kWave + lane);
+                if constexpr (ROWS) srow[at] = row[st];
+                else if (pay) ssrc[at] = wbase - b0 + st * kWave + lane;
             }
-            __syncthreads();
-            scan_hist();
+        }
+        __syncthreads();
+        const uint32_t count = min(b1, n) - b0;
+        for (uint32_t i = threadIdx.x; i < count; i += NT) {
+            const uint32_t p = sv[i];
+            keys_out[b0 + i] = sk[i];
+            perm_out[b0 + i] = p;
+            reinterpret_cast<Row*>(xs)[b0 + i] = ROWS ? srow[i] : (pay ? pay[b0 + ssrc[i]] : load_xrow(p));
+        }
+        return;
+    }
+    // ---- a larger bucket: its histogram first, then chunk by chunk ----
+    for (uint32_t d = threadIdx.x; d < R; d += NT) hist[d] = 0;
+    __syncthreads();
+    for (uint32_t i = b0 + threadIdx.x; i < b1; i += NT) atomicAdd(&hist[keys_in[i] & mask], 1u);
+    __syncthreads();
+    {
+        uint32_t sum = 0;
+        if (d0 < R)
+            for (uint32_t k = 0; k < per; ++k) sum += hist[d0 + k];
+        uint32_t total;
+        uint32_t ex = block_exclusive_scan_w<NW>(sum, s_wsum, &total);
+        if (d0 < R) {
+            for (uint32_t k = 0; k < per; ++k) {
+                const uint32_t c = cell0 + d0 + k;
+                base[d0 + k] = ex;
+                if (c <= ncells) off[c] = b0 + ex;
+                ex += hist[d0 + k];
+            }
+        }
+    }
+    __syncthreads();
+    for (uint32_t chunk = b0; chunk < b1; chunk += kChunk) {
+        if (chunk != b0) {
+            for (uint32_t d = threadIdx.x; d < NW * R; d += NT) cnt[d] = 0;
             __syncthreads();
         }
+        const uint32_t wbase = chunk + w * (kWave * KPT);
+        load_chunk(chunk);
+        rank_chunk(chunk);
+        __syncthreads();
         for (uint32_t d = threadIdx.x; d < R; d += NT) {
             // the waves' first destinations of digit d, in wave (= index) order
             uint32_t run = base[d];
@@ -787,53 +889,16 @@ __global__ __launch_bounds__(BucketThreads<IPT>::value) void k_bucket_finalize(c
             base[d] = run;
         }
         __syncthreads();
-        if (STAGE && single) {
-            // sorted order assembled in LDS, then written as contiguous runs (scattered
-            // stores into the bucket's range left partly written lines behind)
-            uint32_t* sk = lds + (2 + NW) * R;  // after hist, base and the NW per-wave counts
-            uint32_t* sv = sk + kSortTile;
-            VecN<T, PITCH>* srow = reinterpret_cast<VecN<T, PITCH>*>(sv + kSortTile);
-#pragma unroll
-            for (int st = 0; st < KPT; ++st) {
-                const uint32_t idx = wbase + st * kWave + lane;
-                if (idx < b1) {
-                    const uint32_t rel = wc[key[st] & mask] + loc[st];
-                    if (rel < (uint32_t)kSortTile) {  // always true for a consistent histogram
-                        sk[rel] = key[st];
-                        sv[rel] = min(val[st], n - 1u);
-                        srow[rel] = row[st];
-                    }
-                }
-            }
-            __syncthreads();
-            const uint32_t count = b1 - b0;
-            for (uint32_t i = threadIdx.x; i < count; i += NT) {
-                if (b0 + i < n) {
-                    keys_out[b0 + i] = sk[i];
-                    perm_out[b0 + i] = sv[i];
-                    reinterpret_cast<VecN<T, PITCH>*>(xs)[b0 + i] = srow[i];
-                }
-            }
-            __syncthreads();
-            continue;
-        }
 #pragma unroll
         for (int st = 0; st < KPT; ++st) {
             const uint32_t idx = wbase + st * kWave + lane;
             if (idx < b1) {
-                const uint32_t dest = b0 + wc[key[st] & mask] + loc[st];
+                const uint32_t dest = b0 + wc[dl[st] & kDigit] + (dl[st] >> kMaxDigitBits);
                 if (dest < n) {  // always true for a consistent histogram; keeps a bad one in bounds
-                    keys_out[dest] = key[st];
-                    const uint32_t p = min(val[st], n - 1u);
-                    perm_out[dest] = p;
-                    VecN<T, PITCH> v;
-                    if (pay) {
-                        v = row[st];
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < PITCH; ++k) v.v[k] = k < D ? x[(size_t)p * D + k] : T(0);
-                    }
-                    reinterpret_cast<VecN<T, PITCH>*>(xs)[dest] = v;
+                    const uint32_t v = load_val(idx);
+                    keys_out[dest] = cell0 + (dl[st] & kDigit);
+                    perm_out[dest] = v;
+                    reinterpret_cast<Row*>(xs)[dest] = pay ? pay[idx] : load_xrow(v);
                 }
             }
         }
@@ -1024,6 +1089,21 @@ uint64_t build_key(int32_t d, int32_t dtype, bool batch, int64_t n, int64_t ncel
     return k;
 }
 
+// Key bits the bucket pass sorts: one bucket of everything where that is at most 2048
+// keys; else about 512 keys a bucket, so that a CU runs several at once -- more, up to
+// 1650, while the buckets are too many for 8 bits of a radix pass (whose runs of a digit
+// get short), and at least what one pass of 10 bits leaves.  Build of 100003 particles
+// (3-d, 14 bits of key), us, with 5 / 6 / 7 / 8 bits: 20.2 / 18.3 / 20.3 / 23.1; 2^18 (15 bits):
+// 28.2 / 24.6 / 24.7 / 27.5; 300007 in 2-d (16 bits), 6 / 7 / 8 bits: 28.2 / 26.0 / 23.9.
+int bucket_bits_for(int64_t n, int64_t ncells, int bits) {
+    if (n <= 2048 && bits <= kMaxDigitBits) return bits;
+    const double per_cell = std::max((double)n / (double)std::max<int64_t>(ncells, 1), 1e-3);
+    const int want = (int)std::lround(9.0 - std::log2(per_cell));
+    const int most = (int)std::floor(std::log2(1650.0 / per_cell));
+    const int lb = std::max(std::max(want, std::min(bits - 8, most)), std::max(1, bits - kMaxDigitBits));
+    return std::min(lb, std::min(bits, kMaxDigitBits));
+}
+
 int sort_ipt_for(int64_t n) {
     if (n >= (int64_t)512 * kBlock * 16) return 16;
     if (n >= (int64_t)512 * kBlock * 8) return 8;
@@ -1070,7 +1150,7 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
         uint32_t* vout = (k0 == c->keys) ? c->perm_alt : c->perm;
         // Two choices, from measurements on MI355X (2^20 particles in one cube vs 512 systems
         // of up to 65536): shuffling a tile into digit order in LDS (keys, indices and carried
-        // rows) makes its writes contiguous but needs tens of KB of LDS (72 KB for 2048 float
+        // rows) makes its writes contiguous but needs tens of KB of LDS (57 KB for 2048 float
         // rows), which pays while the tiles do not outnumber the CUs much (it slowed 1411
         // tiles), and must fit the device's LDS per workgroup; carrying the position rows through the pass turns the
         // bucket pass's random gather into a sequential read, which pays when a system's
@@ -1082,9 +1162,8 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
         const bool payload = (uint64_t)largest * D * sizeof(T) > (2u << 20);
         // position rows follow the keys through the passes, ping-ponging between the work buffers
         Row* pout = reinterpret_cast<Row*>(c->work);
-        const size_t lds_bytes = (6 * (size_t)radix + 2 * (size_t)kSortTile) * sizeof(uint32_t) +
-                                 (payload ? (size_t)kSortTile * sizeof(Row) : 0);
-        const bool fits = lds_bytes + (kTopInline + 4) * sizeof(uint32_t) <= (size_t)lds_limit(ctx);
+        const size_t lds_bytes = scatter_lds(radix, kSortTile, true, payload ? sizeof(Row) : 0);
+        const bool fits = lds_bytes + (kTopInline + kScatterWaves) * sizeof(uint32_t) <= (size_t)lds_limit(ctx);
         const bool shuffle = fits && (c->shuffle_pref == 1 || (c->shuffle_pref == 0 && ntiles <= 512));
         for (int p = 0; p < c->passes; ++p) {
             const int shift = c->low_bits + p * c->digit_bits;
@@ -1098,9 +1177,9 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
             if (s != ABORIA_OK) return s;
             top_scanned = top_done ? c->block_sums : c->block_sums + c->nblock_sums;
             const int pm = (shuffle ? 1 : 0) | (payload ? 2 : 0);
-            const size_t lds_sel = shuffle ? lds_bytes : 6 * (size_t)radix * sizeof(uint32_t);
+            const size_t lds_sel = shuffle ? lds_bytes : scatter_lds(radix, kSortTile, false, 0);
 #define LS(F, SH, PL)                                                                                          \
-    hipLaunchKernelGGL((k_radix_scatter<T, D, F, SH, PL, IPT>), dim3(ntiles), dim3(kBlock), lds_sel, st, kin, vin, \
+    hipLaunchKernelGGL((k_radix_scatter<T, D, F, SH, PL, IPT>), dim3(ntiles), dim3(kScatterThreads), lds_sel, st, kin, vin, \
                        (const T*)x, (const Row*)pay, kout, vout, pout, n, shift, c->digit_bits, c->hist,       \
                        c->block_sums, ntiles, top_done, c->block_sums + c->nblock_sums)
             if (p == 0) {
@@ -1129,23 +1208,39 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
     const uint32_t R = 1u << c->low_bits;
     const uint32_t nbuckets = (uint32_t)(((uint64_t)c->ncells + 1 + R - 1) / R);
     const bool direct = c->passes == 1 && n > 0;
-    // Single-chunk buckets assemble their output in LDS when the rows travelled with the
-    // keys and the staging area stays small (float rows, tiles of at most 2048 keys).
-    constexpr bool kStageable = IPT <= 8 && sizeof(VecN<T, Pitch<D>::value>) <= 16;
-    const bool stage = kStageable && pay != nullptr;
-    const size_t stage_bytes = (size_t)kSortTile * (2 * sizeof(uint32_t) + sizeof(VecN<T, Pitch<D>::value>));
-    constexpr int kBucketThreads = BucketThreads<IPT>::value;
-    const size_t cnt_bytes = (2 + kBucketThreads / kWave) * (size_t)R * sizeof(uint32_t);
-    if (stage)
-        hipLaunchKernelGGL((k_bucket_finalize<T, D, IPT, kStageable>), dim3(nbuckets), dim3(kBucketThreads),
-                           cnt_bytes + stage_bytes, st, kin, vin, n, c->low_bits, (uint32_t)c->ncells,
-                           (const T*)x, (T*)c->xs, c->keys, c->perm, c->off, direct ? c->hist : nullptr,
-                           top_scanned, (uint32_t)c->ntiles, 1u << c->digit_bits, pay);
+    // Threads and keys per thread of a bucket: what holds the mean bucket and eight standard
+    // deviations of a uniform one, in the smallest form.  The largest leaves the positions to
+    // be gathered on the way out (rows of 10240 keys would not fit LDS).
+    const double mean = std::min((double)c->n, (double)c->n / (double)std::max<int64_t>(c->ncells, 1) * (double)R);
+    const double want = std::min((double)c->n, mean + 8.0 * std::sqrt(mean) + 32.0);
+    const size_t row_bytes = sizeof(Row) + 2 * sizeof(uint32_t);
+    const size_t lds_max = std::min<size_t>(lds_limit(ctx), 160 * 1024) - 1024;
+    auto launch = [&](auto nt_tag, auto kpt_tag, auto rows_tag) {
+        constexpr int NT = decltype(nt_tag)::value, KPT = decltype(kpt_tag)::value;
+        constexpr bool ROWS = decltype(rows_tag)::value;
+        const size_t key_bytes = ROWS ? row_bytes : (pay ? 3 : 2) * sizeof(uint32_t);
+        const size_t cnt_bytes = (2 + NT / kWave) * (size_t)R * sizeof(uint32_t);
+        // room for the bucket, and what is left of a CU's LDS when as many buckets share it
+        // as would at that size (at most four)
+        const size_t need = std::max(cnt_bytes, (size_t)want * key_bytes);
+        const size_t share = std::max<size_t>(1, std::min<size_t>(4, lds_max / std::max<size_t>(need, 1)));
+        const uint32_t cap = (uint32_t)std::min<size_t>((size_t)NT * KPT, (lds_max / share - 256) / key_bytes) & ~31u;
+        hipLaunchKernelGGL((k_bucket_finalize<T, D, NT, KPT, ROWS>), dim3(nbuckets), dim3(NT),
+                           std::max(cnt_bytes, cap * key_bytes), st, kin, vin, n, c->low_bits, (uint32_t)c->ncells,
+                           (const T*)x, (T*)c->xs, c->keys, c->perm, c->off, direct ? c->hist : nullptr, top_scanned,
+                           (uint32_t)c->ntiles, 1u << c->digit_bits, pay, cap);
+    };
+    using std::integral_constant;
+    using Rows = integral_constant<bool, true>;
+    using Late = integral_constant<bool, false>;
+    if (want <= 1024.0 && 1024 * row_bytes <= lds_max)
+        launch(integral_constant<int, 512>(), integral_constant<int, 2>(), Rows());
+    else if (want <= 2048.0 && 2048 * row_bytes <= lds_max)
+        launch(integral_constant<int, 512>(), integral_constant<int, 4>(), Rows());
+    else if (want <= 4096.0)
+        launch(integral_constant<int, 512>(), integral_constant<int, 8>(), Late());
     else
-        hipLaunchKernelGGL((k_bucket_finalize<T, D, IPT, false>), dim3(nbuckets), dim3(kBucketThreads), cnt_bytes,
-                           st, kin, vin, n, c->low_bits, (uint32_t)c->ncells, (const T*)x, (T*)c->xs, c->keys,
-                           c->perm, c->off, direct ? c->hist : nullptr, top_scanned, (uint32_t)c->ntiles,
-                           1u << c->digit_bits, pay);
+        launch(integral_constant<int, 1024>(), integral_constant<int, 10>(), Late());
     ABORIA_HIP(ctx, hipGetLastError());
     return ABORIA_OK;
 }
@@ -1264,9 +1359,9 @@ extern "C" aboria_status aboria_build_cells(aboria_ctx* ctx, aboria_dtype dtype,
             int32_t bits = 1;
             while (bits < 32 && ((int64_t)1 << bits) < total_cells) ++bits;
             c->key_bits = bits;
-            // the bucket pass sorts the low bits (8 to 10 of them); LDS-ranked
-            // radix passes of at most 10 bits sort the rest first
-            c->low_bits = std::min(bits, std::max(8, std::min(bits - kMaxDigitBits, kMaxDigitBits)));
+            // the bucket pass sorts the low bits, LDS-ranked radix passes of at most 10 bits
+            // the rest first
+            c->low_bits = bucket_bits_for(n, total_cells, bits);
             c->sort_ipt = sort_ipt_for(n);
             // a forced shape, else the tuned one for this size, replaces the rule
             aboria_ctx::BuildShape shape = ctx->build_forced;
