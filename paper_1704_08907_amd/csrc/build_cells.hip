@@ -10,6 +10,7 @@
 //   k_radix_scatter  stable in-tile ranks from wave ballots, then scatter
 //                    (these three run once per radix pass over the high key
 //                    bits, stably grouping particles by bucket of cells)
+//   k_small_cells    all of it by one workgroup, for a few thousand particles
 //   k_bucket_finalize  the last radix pass, one workgroup per bucket: low-digit
 //                    histogram in LDS -> the bucket's cell offsets, stable
 //                    placement, and the gather of the positions into cell order
@@ -906,6 +907,93 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
     }
 }
 
+// The whole build of a small cell list (at most 2 * kSmallThreads particles, 2^lb >=
+// ncells cells) by one workgroup: cell ids, stable ranks and offsets as above without
+// leaving the registers, the result written in place.  One launch whose few dependent
+// loads are all it waits for: 1000 particles in 2-d 5.3 us, where cell ids and a bucket
+// that looked its bounds up took 1.9 and 7.2.
+constexpr int kSmallThreads = 1024;
+
+template <typename T, int D, bool BATCH>
+__global__ __launch_bounds__(kSmallThreads) void k_small_cells(const T* __restrict__ x, uint32_t n,
+                                                               const SysParams<T>* __restrict__ sp,
+                                                               const uint32_t* __restrict__ sys_part, int nsys, int lb,
+                                                               uint32_t ncells, T* __restrict__ xs,
+                                                               uint32_t* __restrict__ keys,
+                                                               uint32_t* __restrict__ perm, uint32_t* __restrict__ off,
+                                                               uint32_t* __restrict__ flag,
+                                                               uint32_t* __restrict__ gen) {
+    constexpr int PITCH = Pitch<D>::value;
+    constexpr int NW = kSmallThreads / kWave;
+    using Row = VecN<T, PITCH>;
+    extern __shared__ uint32_t cnt[];  // [NW][R] per-wave counts, then first places
+    __shared__ uint32_t s_wsum[NW];
+    const uint32_t R = 1u << lb;
+    const uint32_t t = threadIdx.x, lane = t & 63, w = t >> 6;
+    if (t == 0) {
+        gen[0] = next_generation(gen[0]);
+        off[ncells] = n;
+    }
+    bool bad = false;
+    uint32_t key[2] = {0u, 0u}, loc[2];
+    Row row[2];
+    // wave w takes the 128 consecutive particles from 128 w
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t i = w * 128u + q * 64u + lane;
+        if (i < n) {
+            const SysParams<T>& P = sp[BATCH ? find_system(sys_part, nsys, i) : 0];
+            key[q] = cell_key<T, D>(P, x, i, &bad);
+#pragma unroll
+            for (int k = 0; k < PITCH; ++k) row[q].v[k] = k < D ? x[(size_t)i * D + k] : T(0);
+        }
+    }
+    if (bad) atomicOr(flag, 1u);
+    for (uint32_t d = t; d < NW * R; d += kSmallThreads) cnt[d] = 0;
+    __syncthreads();
+    uint32_t* wc = cnt + w * R;
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const bool valid = w * 128u + q * 64u + lane < n;
+        uint64_t peers = __ballot(valid);
+        for (int bb = 0; bb < lb; ++bb) {
+            const bool bit = (key[q] >> bb) & 1u;
+            const uint64_t m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        const uint32_t below = (uint32_t)__popcll(peers & lt);
+        const uint32_t c = valid ? wc[key[q]] : 0u;
+        if (valid && below == 0) wc[key[q]] = c + (uint32_t)__popcll(peers);
+        loc[q] = c + below;
+    }
+    __syncthreads();
+    uint32_t tot = 0;
+    if (t < R)
+        for (int q = 0; q < NW; ++q) tot += cnt[q * R + t];
+    uint32_t total;
+    uint32_t run = block_exclusive_scan_w<NW>(tot, s_wsum, &total);
+    if (t < R) {
+        if (t < ncells) off[t] = run;
+        for (int q = 0; q < NW; ++q) {
+            const uint32_t a = cnt[q * R + t];
+            cnt[q * R + t] = run;
+            run += a;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t i = w * 128u + q * 64u + lane;
+        if (i < n) {
+            const uint32_t dest = wc[key[q]] + loc[q];
+            keys[dest] = key[q];
+            perm[dest] = i;
+            reinterpret_cast<Row*>(xs)[dest] = row[q];
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -1271,8 +1359,26 @@ aboria_status launch_build_single(aboria_ctx* ctx, aboria_cells* c, const void* 
 }
 
 template <typename T, int D>
+aboria_status launch_build_small(aboria_ctx* ctx, aboria_cells* c, const void* x) {
+    const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
+    const size_t lds = (size_t)(kSmallThreads / kWave) * sizeof(uint32_t) << c->low_bits;
+#define SC(B)                                                                                                      \
+    hipLaunchKernelGGL((k_small_cells<T, D, B>), dim3(1), dim3(kSmallThreads), lds, ctx->stream, (const T*)x,      \
+                       (uint32_t)c->n, sp, c->sys_part_dev, c->nsys, c->low_bits, (uint32_t)c->ncells, (T*)c->xs,  \
+                       c->keys, c->perm, c->off, ctx->d_flag, c->gen)
+    if (c->nsys == 1) SC(false);
+    else SC(true);
+#undef SC
+    ABORIA_HIP(ctx, hipGetLastError());
+    return ABORIA_OK;
+}
+
+template <typename T, int D>
 aboria_status launch_build(aboria_ctx* ctx, aboria_cells* c, const void* x) {
     if (c->ncells == c->nsys) return launch_build_single<T, D>(ctx, c, x);  // one cell per system: no sort
+    // one bucket of everything (2^low_bits >= ncells), small enough for one workgroup
+    if (ctx->build_strategy == ABORIA_BUILD_RADIX && c->passes == 0 && c->n > 0 && c->n <= 2 * kSmallThreads)
+        return launch_build_small<T, D>(ctx, c, x);
     return ctx->build_strategy == ABORIA_BUILD_RADIX ? launch_build_radix<T, D>(ctx, c, x)
                                                      : launch_build_counting<T, D>(ctx, c, x);
 }

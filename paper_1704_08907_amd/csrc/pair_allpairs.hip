@@ -34,11 +34,10 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = T(0);
     const T r = P.r;
-    auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
-        const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
-        Op::fwd(q, r, dx, d2, ai, aj, acc);
-    };
-    if (live) allpairs_loop<T, D>(P, xs, P.part_base + lane, P.part_end, G, xi, visit);
+    auto visit = [&](const T* dx, T d2, const T*, T aj) { Op::fwd(q, r, dx, d2, ai, aj, acc); };
+    if (live)
+        allpairs_loop<T, D, 0, OpShape<OP, D>::NA>(P, xs, (const T*)nullptr, a_s, P.part_base + lane, P.part_end, G, xi,
+                                                   visit);
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = group_reduce<G>(acc[k]);
     if (!live || lane != 0) return;
@@ -71,13 +70,9 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
 #pragma unroll
     for (int k = 0; k < D; ++k) accx[k] = T(0);
     const T r = P.r;
-    auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
-        const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
-        T gyj[NY];
-        load_gy<T, NY>(gy_s, j, gyj);
-        Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
-    };
-    if (live) allpairs_loop<T, D>(P, xs, P.part_base + lane, P.part_end, G, xi, visit);
+    auto visit = [&](const T* dx, T d2, const T* gyj, T aj) { Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca); };
+    if (live)
+        allpairs_loop<T, D, NY, OpShape<OP, D>::NA>(P, xs, gy_s, a_s, P.part_base + lane, P.part_end, G, xi, visit);
 #pragma unroll
     for (int k = 0; k < D; ++k) accx[k] = group_reduce<G>(accx[k]);
     if (OpShape<OP, D>::NA) acca[0] = group_reduce<G>(acca[0]);
