@@ -580,7 +580,7 @@ struct NoRowDone {
 // lane of the wave runs the loop without the shift additions (adding zero is
 // exact, so both loops give the canonical dx).  flat_loop visits the accepted
 // neighbours in this same order.  With STAGE, wb is the wave's LDS window.
-template <typename T, int D, bool OFF32, int NAUX, bool STAGE, typename Visit, typename RowDone>
+template <typename T, int D, bool OFF32, int NAUX, bool STAGE, bool DEFER, typename Visit, typename RowDone>
 __device__ __forceinline__ void neighbour_loop_aux(const SysParams<T>& P, const T* __restrict__ xs,
                                                    const T* __restrict__ aux, const uint32_t* __restrict__ off,
                                                    uint32_t n, const T* xi, Visit&& visit,
@@ -608,16 +608,16 @@ __device__ __forceinline__ void neighbour_loop_aux(const SysParams<T>& P, const 
         bool lane_shift = false;
 #pragma unroll
         for (int k = 0; k < D; ++k) lane_shift |= sh[k] != T(0);
-        if constexpr (NAUX > 0) {
+        if constexpr (DEFER) {
             if (__ballot(lane_shift) != 0ull)
                 scan_range_deferred<T, D, true, OFF32, NAUX, WIN>(xs, aux, j0, j1, xi, sh, r2, lane_shift, visit, w);
             else
                 scan_range_deferred<T, D, false, OFF32, NAUX, WIN>(xs, aux, j0, j1, xi, sh, r2, false, visit, w);
         } else {
             if (__ballot(lane_shift) != 0ull)
-                scan_range<T, D, true, OFF32, 0, WIN>(xs, j0, j1, xi, sh, r2, lane_shift, visit, nullptr, w);
+                scan_range<T, D, true, OFF32, NAUX, WIN>(xs, j0, j1, xi, sh, r2, lane_shift, visit, aux, w);
             else
-                scan_range<T, D, false, OFF32, 0, WIN>(xs, j0, j1, xi, sh, r2, false, visit, nullptr, w);
+                scan_range<T, D, false, OFF32, NAUX, WIN>(xs, j0, j1, xi, sh, r2, false, visit, aux, w);
         }
     };
     auto piece = [&](uint32_t ca, uint32_t cb, const T* sh) {
@@ -714,17 +714,19 @@ __device__ __forceinline__ void neighbour_loop(const SysParams<T>& P, const T* _
                                                const uint32_t* __restrict__ off, uint32_t n, const T* xi,
                                                Visit&& visit, RowDone&& row_done = RowDone(),
                                                RowRange range = kAllRows) {
-    neighbour_loop_aux<T, D, OFF32, 0, false>(P, xs, (const T*)nullptr, off, n, xi, visit, row_done, range, nullptr);
+    neighbour_loop_aux<T, D, OFF32, 0, false, false>(P, xs, (const T*)nullptr, off, n, xi, visit, row_done, range, nullptr);
 }
 
 // neighbour_loop_aux with each row's main runs read through the wave's LDS
-// window wb (WindowBytes) where they fit (same pairs, same order, same sums).
-template <typename T, int D, bool OFF32, int NAUX, typename Visit, typename RowDone>
+// window wb (WindowBytes) where they fit (same pairs, same order, same sums).  With
+// NAUX the neighbours' rows of aux lie in the window too and are passed to visit, with
+// DEFER after all of a chunk's candidates are tested.
+template <typename T, int D, bool OFF32, int NAUX, bool DEFER = (NAUX > 0), typename Visit, typename RowDone>
 __device__ __forceinline__ void neighbour_loop_staged(const SysParams<T>& P, const T* __restrict__ xs,
                                                       const T* __restrict__ aux, const uint32_t* __restrict__ off,
                                                       uint32_t n, const T* xi, Visit&& visit, RowDone&& row_done,
                                                       RowRange range, char* wb) {
-    neighbour_loop_aux<T, D, OFF32, NAUX, true>(P, xs, aux, off, n, xi, visit, row_done, range, wb);
+    neighbour_loop_aux<T, D, OFF32, NAUX, true, DEFER>(P, xs, aux, off, n, xi, visit, row_done, range, wb);
 }
 
 // ---------------------------------------------------------------------------
