@@ -83,7 +83,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_md_step(const 
         load_point<T, D>(xs, s, xi);
         const T r = P.r;
         auto visit = [&](uint32_t, const T* dx, T d2, bool) { Op::fwd(q, r, dx, d2, T(0), T(0), sums.acc); };
-        neighbour_loop_staged<T, D, OFF32, 0>(P, xs, (const T*)nullptr, off, n, xi, visit,
+        neighbour_loop_staged<T, D, OFF32, 0, kDeferForward<T, OP>>(P, xs, (const T*)nullptr, off, n, xi, visit,
                                               [&](int32_t row) { ws.row_done(row); }, w.range,
                                               wave_window(lds, w.wave, WB));
     }

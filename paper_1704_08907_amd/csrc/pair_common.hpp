@@ -443,12 +443,18 @@ __device__ __forceinline__ void scan_range(const T* __restrict__ xs, uint32_t j0
 template <int OP>
 constexpr bool kDeferAdjoint = OP == ABORIA_OP_SPRING || OP == ABORIA_OP_EXP_FORCE || OP == ABORIA_OP_DEM_SPRING;
 
+// Forward summands that do: in 64 bits the exponential's (reciprocal square root and
+// exponential are a dozen operations each; a million particles in 2-d with 9 neighbours
+// 89 -> 77 us, the time step 82 -> 70), not the spring's (60000 in 3-d 26.5 -> 29.5).
+template <typename T, int OP>
+constexpr bool kDeferForward = sizeof(T) == 8 && OP == ABORIA_OP_EXP_FORCE;
+
 // scan_range in two passes per chunk of up to 32 candidates, for summands that
 // cost much more than the pair test (the adjoint): the first pass tests every
 // candidate and keeps a bit per accepted one; the second pops the bits in
 // increasing order, reloads that candidate's position and aux row (the
-// neighbour's gradient row), recomputes its dx and d2 exactly as the test did
-// and calls visit(j, dx, d2, shifted, aux_j).  In SIMD the summand then runs
+// neighbour's gradient row, with NAUX > 0), recomputes its dx and d2 exactly as the test did
+// and calls visit(j, dx, d2, shifted, aux_j) (without aux: visit(j, dx, d2, shifted)).  In SIMD the summand then runs
 // as many times per chunk as the busiest lane has accepted pairs, instead of
 // once per candidate that any lane of the wave accepts.  The pairs and their
 // order are those of scan_range, so the sums are bit for bit the same.
@@ -457,7 +463,7 @@ __device__ __forceinline__ void scan_range_deferred(const T* __restrict__ xs, co
                                                     uint32_t j0, uint32_t j1, const T* xi, const T* sh, T r2,
                                                     bool shifted, Visit& visit, WinRef w = WinRef{nullptr, 0u}) {
     constexpr int PITCH = Pitch<D>::value;
-    constexpr int AP = GyPitch<NAUX>::value;
+    constexpr int AP = NAUX > 0 ? GyPitch<(NAUX > 0 ? NAUX : 1)>::value : 1;
     constexpr uint32_t RB = (uint32_t)sizeof(VecN<T, PITCH>), RA = (uint32_t)sizeof(VecN<T, AP>);
     auto ldx = [&](uint32_t jj, uint32_t k) {
         if constexpr (WIN) return *reinterpret_cast<const VecN<T, PITCH>*>(w.wb + (jj - w.lo + k) * RB);
@@ -491,8 +497,13 @@ __device__ __forceinline__ void scan_range_deferred(const T* __restrict__ xs, co
             else return load_row<T, PITCH, OFF32>(xs, c0 + k);
         };
         auto ldak = [&](uint32_t k) {
-            if constexpr (WIN) return *reinterpret_cast<const VecN<T, AP>*>(paw + k * RA);
+            if constexpr (NAUX == 0) return VecN<T, AP>{};
+            else if constexpr (WIN) return *reinterpret_cast<const VecN<T, AP>*>(paw + k * RA);
             else return load_row<T, AP, OFF32>(aux, c0 + k);
+        };
+        auto call = [&](uint32_t jj, const T* dx, T d2, const VecN<T, AP>& av) {
+            if constexpr (NAUX > 0) visit(jj, dx, d2, shifted, av.v);
+            else visit(jj, dx, d2, shifted);
         };
         // two accepted pairs per iteration, so their four loads overlap
         while (mask != 0u) {
@@ -508,12 +519,12 @@ __device__ __forceinline__ void scan_range_deferred(const T* __restrict__ xs, co
             const VecN<T, AP> avb = ldak(kb);
             T dx[D], d2;
             (void)pair_test<T, D, SHIFT>(a.v, xi, sh, r2, dx, &d2);
-            visit(ja, dx, d2, shifted, ava.v);
+            call(ja, dx, d2, ava);
             keep_issued<D>(b.v);
             keep_issued<NAUX>(avb.v);
             if (vb) {
                 (void)pair_test<T, D, SHIFT>(b.v, xi, sh, r2, dx, &d2);
-                visit(jb, dx, d2, shifted, avb.v);
+                call(jb, dx, d2, avb);
             }
         }
     }

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_fwd(const
             const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
             Op::fwd(q, r, dx, d2, ai, aj, sums.acc);
         };
-        neighbour_loop_staged<T, D, OFF32, 0>(P, xs, (const T*)nullptr, off, n, xi, visit,
+        neighbour_loop_staged<T, D, OFF32, 0, kDeferForward<T, OP>>(P, xs, (const T*)nullptr, off, n, xi, visit,
                                               [&](int32_t row) { ws.row_done(row); }, w.range,
                                               wave_window(lds, w.wave, WB));
     }
