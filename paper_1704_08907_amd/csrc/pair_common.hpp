@@ -1184,40 +1184,64 @@ __device__ __forceinline__ T replay_pair(const SysParams<T>& P, const T* xj, con
     return d2;
 }
 
-// Calls visit(j, dx, d2) for the recorded neighbours of slot s in recorded
-// order, row_if(first) before each: first is set on the first one of each row.  Entry k of slot s is at nbr[k * n + s], so the lanes of a wave read
-// consecutive words.  Two entries per iteration keep two position loads in
-// flight.
-template <typename T, int D, typename Visit, typename RowIf>
+// Calls visit(dx, d2, gyj, aj) for the recorded neighbours of slot s in recorded order
+// (gyj: NAUX elements of aux's row, aj with NA), row_if(first) before each: first is set
+// on the first one of each row.  Entry k of slot s is at nbr[k * n + s], so the lanes of
+// a wave read consecutive words.  A replay waits far more than it computes (with two
+// entries at a time, read when they were due, 78 % of the waves' time; VALU 28 %): U
+// entries at a time, their rows all in flight together, and the entries of the next U
+// read meanwhile.  300007 particles in 2-d with 20 neighbours, the
+// exponential's forward 19.0 -> 16.1 us, adjoint (with its gather) 29.4 -> 27.0; 2^20 in
+// 3-d with 30, the spring's forward 79.6 -> 64.4 (rows of four elements two at a time:
+// four cost its adjoint 147 -> 155).
+template <typename T, int D, int NAUX, int NA, typename Visit, typename RowIf>
 __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __restrict__ xs,
-                                            const uint32_t* __restrict__ nbr, uint32_t n, uint32_t s, uint32_t cnt,
-                                            const T* xi, Visit& visit, RowIf&& row_if) {
+                                            const T* __restrict__ aux, const T* __restrict__ a_s,
+                                            const uint32_t* __restrict__ nbr, uint32_t cap, uint32_t n, uint32_t s,
+                                            uint32_t cnt, const T* xi, Visit&& visit, RowIf&& row_if) {
     constexpr int PITCH = Pitch<D>::value;
-    const VecN<T, PITCH>* __restrict__ xv = reinterpret_cast<const VecN<T, PITCH>*>(xs);
-    const uint32_t* p = nbr + s;
-    const size_t stride = (size_t)n;
-    uint32_t k = 0;
-    for (; k + 1 < cnt; k += 2) {
-        const uint32_t e0 = p[0];
-        const uint32_t e1 = p[stride];
-        p += 2 * stride;
-        const VecN<T, PITCH> a = xv[e0 & kNbrSlot];
-        const VecN<T, PITCH> b = xv[e1 & kNbrSlot];
-        T dx[D];
-        T d2 = replay_pair<T, D>(P, a.v, xi, (e0 & kNbrShift) != 0u, dx);
-        row_if((e0 & kNbrRow) != 0u);
-        visit(e0 & kNbrSlot, dx, d2);
-        row_if((e1 & kNbrRow) != 0u);
-        d2 = replay_pair<T, D>(P, b.v, xi, (e1 & kNbrShift) != 0u, dx);
-        visit(e1 & kNbrSlot, dx, d2);
-    }
-    if (k < cnt) {
-        const uint32_t e0 = p[0];
-        const VecN<T, PITCH> a = xv[e0 & kNbrSlot];
-        T dx[D];
-        const T d2 = replay_pair<T, D>(P, a.v, xi, (e0 & kNbrShift) != 0u, dx);
-        row_if((e0 & kNbrRow) != 0u);
-        visit(e0 & kNbrSlot, dx, d2);
+    constexpr int AP = NAUX > 0 ? GyPitch<(NAUX > 0 ? NAUX : 1)>::value : 1;
+    constexpr uint32_t U = sizeof(T) == 4 && AP < 3 ? 4u : 2u;
+    // rows of the list past a lane's count hold anything: it takes its own slot there
+    uint32_t e[U];
+    if (cnt == 0u) return;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) e[u] = (nbr + (size_t)min(u, cap - 1u) * n)[s];
+    for (uint32_t k = 0; k < cnt; k += U) {
+        VecN<T, PITCH> x[U];
+        VecN<T, AP> g[U];
+        T aj[U];
+        uint32_t next[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            e[u] = k + u < cnt ? e[u] : s;
+            const uint32_t j = e[u] & kNbrSlot;
+            x[u] = reinterpret_cast<const VecN<T, PITCH>*>(xs)[j];
+            if constexpr (NAUX > 0) g[u] = reinterpret_cast<const VecN<T, AP>*>(aux)[j];
+            aj[u] = NA > 0 ? a_s[j] : T(0);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) next[u] = s;
+        if (k + U < cnt) {
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) next[u] = (nbr + (size_t)min(k + U + u, cap - 1u) * n)[s];
+        }
+        T dx[U][D], d2[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) d2[u] = replay_pair<T, D>(P, x[u].v, xi, (e[u] & kNbrShift) != 0u, dx[u]);
+        if constexpr (NAUX > 0) {
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) keep_issued<NAUX>(g[u].v);
+        }
+        if constexpr (NA > 0) keep_issued<U>(aj);
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            if (k + u < cnt) {
+                row_if((e[u] & kNbrRow) != 0u);
+                visit(dx[u], d2[u], g[u].v, aj[u]);
+            }
+            e[u] = next[u];
+        }
     }
 }
 

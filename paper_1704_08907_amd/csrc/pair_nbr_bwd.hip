@@ -35,17 +35,20 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
     T* const accx = sums.acc;
     T* const acca = accx + (NA ? D : 0);
     const T r = P.r;
-    auto pair = [&](uint32_t j, const T* dx, T d2) {
-        const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
-        T gyj[NY];
-        load_gy<T, NY>(gy_s, j, gyj);
-        Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
-    };
     const uint32_t cnt = nbr_count[s];
     if (gen[0] == gen[1] && cnt <= cap && n <= kNbrSlot + 1u) {
-        replay_list<T, D>(P, xs, nbr, n, s, cnt, xi, pair, [&](bool first) { sums.row_done_if(first & by_rows); });
+        constexpr int NG = OP == ABORIA_OP_COUNT ? 0 : NY;  // the count needs no gradient
+        replay_list<T, D, NG, NA>(
+            P, xs, gy_s, a_s, nbr, cap, n, s, cnt, xi,
+            [&](const T* dx, T d2, const T* gyj, T aj) { Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca); },
+            [&](bool first) { sums.row_done_if(first & by_rows); });
     } else {
-        auto visit = [&](uint32_t j, const T* dx, T d2, bool) { pair(j, dx, d2); };
+        auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
+            const T aj = NA ? a_s[j] : T(0);
+            T gyj[NY];
+            load_gy<T, NY>(gy_s, j, gyj);
+            Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
+        };
         neighbour_loop<T, D>(P, xs, off, n, xi, visit, [&](int32_t) { sums.row_done(); });
     }
     sums.last();

@@ -32,11 +32,10 @@ __global__ __launch_bounds__(256) void k_nbr_fwd(const T* __restrict__ xs, const
     const T r = P.r;
     const uint32_t cnt = nbr_count[s];
     if (gen[0] == gen[1] && cnt <= cap && n <= kNbrSlot + 1u) {
-        auto visit = [&](uint32_t j, const T* dx, T d2) {
-            const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
-            Op::fwd(q, r, dx, d2, ai, aj, acc);
-        };
-        replay_list<T, D>(P, xs, nbr, n, s, cnt, xi, visit, [&](bool first) { sums.row_done_if(first & by_rows); });
+        replay_list<T, D, 0, OpShape<OP, D>::NA>(
+            P, xs, (const T*)nullptr, a_s, nbr, cap, n, s, cnt, xi,
+            [&](const T* dx, T d2, const T*, T aj) { Op::fwd(q, r, dx, d2, ai, aj, acc); },
+            [&](bool first) { sums.row_done_if(first & by_rows); });
     } else {
         auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
             const T aj = OpShape<OP, D>::NA ? a_s[j] : T(0);
