@@ -24,55 +24,103 @@ namespace {
 
 constexpr uint32_t kMaxNbrCap = 4096;
 
-// One lane per particle; the rows are read through the wave's LDS window (300007
-// particles in 2-d, 20 neighbours: 33 us, 39 us with candidates gathered from HBM).
-template <typename T, int D, bool BATCH, bool OFF32>
-__global__ __launch_bounds__(256) void k_nbr_build(const T* __restrict__ xs, const uint32_t* __restrict__ off,
+constexpr uint64_t kSharedWaves = 3500;
+
+// Entries of its rows that a lane keeps in LDS before it knows their place in the list
+// (a row of the 3-d stencil has a ninth of the neighbours, three have a third).
+__host__ __device__ constexpr uint32_t stash_of(int32_t split) { return split > 3 ? 16u : 32u; }
+
+// One lane per particle, the rows read through the wave's LDS window.  With SPLIT and
+// split > 1 the rows of 64 particles are shared by that many waves, as in the sums.  A
+// wave then keeps what it finds in LDS ([entry][lane]), and writes it after the entries of
+// the waves before it; a wave with a lane of more entries than it can keep searches its
+// rows once more for the rest.
+template <typename T, int D, bool BATCH, bool OFF32, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_nbr_build(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                    uint32_t n, const SysParams<T>* __restrict__ sp,
                                                    const uint32_t* __restrict__ sys_part, int nsys,
                                                    uint32_t* __restrict__ nbr, uint32_t* __restrict__ nbr_count,
-                                                   uint32_t cap, uint32_t* __restrict__ gen) {
+                                                   uint32_t cap, uint32_t* __restrict__ gen, int32_t split) {
     constexpr uint32_t WB = WindowBytes<T, D, 0>::value;
     extern __shared__ __align__(32) char lds[];
-    const WaveRows w = wave_rows<D, false>(0);
+    const WaveRows w = wave_rows<D, SPLIT>(split);
     const uint32_t s = w.s;
     const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
-    if (s >= n) return;
-    if (s == 0) gen[1] = gen[0];  // the list now belongs to the latest build
-    const SysParams<T> P = sp[b];
+    const bool shared_rows = SPLIT && split > 1;
+    const uint32_t lane = threadIdx.x & 63u;
+    // after the windows: the waves' entries, and their counts
+    const uint32_t kept = stash_of(split);
+    uint32_t* const stash = reinterpret_cast<uint32_t*>(part_lds(lds, WB)) + (uint32_t)w.wave * kept * 64u + lane;
+    uint32_t* const counts = reinterpret_cast<uint32_t*>(part_lds(lds, WB)) + (blockDim.x >> 6) * kept * 64u + lane;
+    SysParams<T> P;
     T xi[D];
-    load_point<T, D>(xs, s, xi);
     uint32_t cnt = 0;
     uint32_t row = kNbrRow;  // set until the row's first neighbour
-    uint32_t* p = nbr + s;
-    const size_t stride = (size_t)n;
-    auto visit = [&](uint32_t j, const T*, T, bool shifted) {
-        if (cnt < cap) {
-            *p = j | (shifted ? kNbrShift : 0u) | row;
-            p += stride;
-        }
-        row = 0u;
-        ++cnt;
+    auto search = [&](auto&& put) {
+        cnt = 0;
+        row = kNbrRow;
+        auto visit = [&](uint32_t j, const T*, T, bool shifted) {
+            put(cnt, j | (shifted ? kNbrShift : 0u) | row);
+            row = 0u;
+            ++cnt;
+        };
+        neighbour_loop_staged<T, D, OFF32, 0>(P, xs, (const T*)nullptr, off, n, xi, visit,
+                                              [&](int32_t) { row = kNbrRow; }, w.range, wave_window(lds, w.wave, WB));
     };
-    neighbour_loop_staged<T, D, OFF32, 0>(P, xs, (const T*)nullptr, off, n, xi, visit,
-                                          [&](int32_t) { row = kNbrRow; }, kAllRows, wave_window(lds, w.wave, WB));
-    nbr_count[s] = cnt;
+    if (s < n) {
+        if (s == 0 && w.wave == 0) gen[1] = gen[0];  // the list now belongs to the latest build
+        P = sp[b];
+        load_point<T, D>(xs, s, xi);
+        if (shared_rows) {
+            search([&](uint32_t k, uint32_t e) {
+                if (k < kept) stash[k * 64u] = e;
+            });
+        } else {
+            uint32_t* p = nbr + s;
+            search([&](uint32_t k, uint32_t e) {
+                if (k < cap) {
+                    *p = e;
+                    p += n;
+                }
+            });
+            nbr_count[s] = cnt;
+        }
+    }
+    if (!shared_rows) return;
+    counts[(uint32_t)w.wave * 64u] = cnt;
+    __syncthreads();
+    if (s >= n) return;
+    uint32_t base = 0;
+    for (int32_t q = 0; q < w.wave; ++q) base += counts[(uint32_t)q * 64u];
+    const uint32_t mine = cnt;
+    for (uint32_t k = 0; k < min(mine, kept); ++k)
+        if (base + k < cap) nbr[(size_t)(base + k) * n + s] = stash[k * 64u];
+    if (w.wave == split - 1) nbr_count[s] = base + mine;
+    if (__ballot(mine > kept) != 0ull)
+        search([&](uint32_t k, uint32_t e) {
+            if (k >= kept && base + k < cap) nbr[(size_t)(base + k) * n + s] = e;
+        });
 }
 
 template <typename T, int D>
 void launch_build_nbr(aboria_ctx* ctx, aboria_cells* c) {
     const uint32_t n = (uint32_t)c->n;
-    const dim3 grid((n + 255) / 256);
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-    const uint32_t lds = 4 * WindowBytes<T, D, 0>::value;
-#define NB(B, O)                                                                                                     \
-    hipLaunchKernelGGL((k_nbr_build<T, D, B, O>), grid, dim3(256), lds, ctx->stream, (const T*)c->xs, c->off, n, sp, \
-                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen)
+    // Shared rows on lists of up to kSharedWaves waves, where the search waits more than it
+    // computes.  One wave / shared: 3000 particles in 2-d 16.3 / 8.6 us, 20000 in 3-d 58 /
+    // 19, 100003 64 / 50, 200000 in 2-d float64 27.4 / 25.9; 300007 in 2-d 33.5 / 34.6.
+    const int32_t split = ((uint64_t)n + 63) / 64 <= kSharedWaves ? row_split(c) : 0;
+    const SearchShape sh = search_shape(
+        ctx, c, split, WindowBytes<T, D, 0>::value + (split > 0 ? (stash_of(split) + 1u) * 256u : 0u), 0u);
+#define NB(B, O, S)                                                                                             \
+    hipLaunchKernelGGL((k_nbr_build<T, D, B, O, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, ctx->stream,     \
+                       (const T*)c->xs, c->off, n, sp, c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, \
+                       c->gen, sh.split)
     const bool o32 = off32_rows<T>(n);
     if (c->nsys == 1) {
-        if (o32) NB(false, true); else NB(false, false);
+        if (sh.split > 0) NB(false, true, (D > 1)); else if (o32) NB(false, true, false); else NB(false, false, false);
     } else {
-        if (o32) NB(true, true); else NB(true, false);
+        if (sh.split > 0) NB(true, true, (D > 1)); else if (o32) NB(true, true, false); else NB(true, false, false);
     }
 #undef NB
 }
