@@ -20,6 +20,7 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
                                                  const T* __restrict__ a_s, OpArgs<T> q, T* __restrict__ y) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
+    constexpr bool DIRECT = G == 64;  // (all_direct)
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x / G);
     const uint32_t s = first + threadIdx.x / G;
     const uint32_t lane = threadIdx.x % G;
@@ -29,15 +30,16 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
     const SysParams<T> P = sp[b];
     T xi[D];
     load_point<T, D>(xs, sc, xi);
-    const T ai = OpShape<OP, D>::NA ? a_s[sc] : T(0);
+    const uint32_t own = DIRECT ? perm[sc] : sc;
+    const T ai = OpShape<OP, D>::NA ? a_s[own] : T(0);
     T acc[NY];
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = T(0);
     const T r = P.r;
     auto visit = [&](const T* dx, T d2, const T*, T aj) { Op::fwd(q, r, dx, d2, ai, aj, acc); };
     if (live)
-        allpairs_loop<T, D, 0, OpShape<OP, D>::NA>(P, xs, (const T*)nullptr, a_s, P.part_base + lane, P.part_end, G, xi,
-                                                   visit);
+        allpairs_loop<T, D, 0, OpShape<OP, D>::NA, DIRECT>(P, xs, (const T*)nullptr, a_s, perm, P.part_base + lane,
+                                                           P.part_end, G, xi, visit);
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = group_reduce<G>(acc[k]);
     if (!live || lane != 0) return;
@@ -54,6 +56,7 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
                                                  OpArgs<T> q, T* __restrict__ gx, T* __restrict__ ga) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
+    constexpr bool DIRECT = G == 64;  // (all_direct)
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x / G);
     const uint32_t s = first + threadIdx.x / G;
     const uint32_t lane = threadIdx.x % G;
@@ -63,16 +66,23 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
     const SysParams<T> P = sp[b];
     T xi[D];
     load_point<T, D>(xs, sc, xi);
-    const T ai = OpShape<OP, D>::NA ? a_s[sc] : T(0);
+    const uint32_t own = DIRECT ? perm[sc] : sc;
+    const T ai = OpShape<OP, D>::NA ? a_s[own] : T(0);
     T gyi[NY];
-    load_gy<T, NY>(gy_s, sc, gyi);
+    if constexpr (DIRECT) {
+#pragma unroll
+        for (int k = 0; k < NY; ++k) gyi[k] = gy_s[(size_t)own * NY + k];
+    } else {
+        load_gy<T, NY>(gy_s, sc, gyi);
+    }
     T accx[D], acca[1] = {T(0)};
 #pragma unroll
     for (int k = 0; k < D; ++k) accx[k] = T(0);
     const T r = P.r;
     auto visit = [&](const T* dx, T d2, const T* gyj, T aj) { Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca); };
     if (live)
-        allpairs_loop<T, D, NY, OpShape<OP, D>::NA>(P, xs, gy_s, a_s, P.part_base + lane, P.part_end, G, xi, visit);
+        allpairs_loop<T, D, NY, OpShape<OP, D>::NA, DIRECT>(P, xs, gy_s, a_s, perm, P.part_base + lane, P.part_end, G,
+                                                            xi, visit);
 #pragma unroll
     for (int k = 0; k < D; ++k) accx[k] = group_reduce<G>(accx[k]);
     if (OpShape<OP, D>::NA) acca[0] = group_reduce<G>(acca[0]);
@@ -81,15 +91,6 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
 #pragma unroll
     for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = accx[k];
     if (OpShape<OP, D>::NA && ga) ga[o] = acca[0];
-}
-
-// Lanes per particle: enough groups for about 64K lanes in flight, at most a wave.
-inline int all_group(uint32_t n) {
-    const uint64_t want = 65536;
-    if ((uint64_t)n * 16 < want) return 64;
-    if ((uint64_t)n * 4 < want) return 16;
-    if ((uint64_t)n < want) return 4;
-    return 1;
 }
 
 template <typename T, int D, int OP, bool BATCH>

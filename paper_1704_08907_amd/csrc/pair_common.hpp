@@ -1098,10 +1098,13 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
 // candidates of a thousand particles, and waiting for them two at a time and for each
 // accepted one's gradient again was what the kernel did (1000 particles in 2-d
 // float64, forward / adjoint: 7.2 / 7.2 us, four at once 6.2 / 6.4, eight 5.6 / 6.1).
-template <typename T, int D, int NAUX, int NA, typename Visit>
+// With DIRECT, aux and a_s are in the caller's order (rows of NAUX elements unpadded) and
+// read through perm.
+template <typename T, int D, int NAUX, int NA, bool DIRECT, typename Visit>
 __device__ __forceinline__ void allpairs_loop(const SysParams<T>& P, const T* __restrict__ xs,
-                                              const T* __restrict__ aux, const T* __restrict__ a_s, uint32_t j0,
-                                              uint32_t j1, uint32_t step, const T* xi, Visit&& visit) {
+                                              const T* __restrict__ aux, const T* __restrict__ a_s,
+                                              const uint32_t* __restrict__ perm, uint32_t j0, uint32_t j1,
+                                              uint32_t step, const T* xi, Visit&& visit) {
     constexpr int PITCH = Pitch<D>::value;
     constexpr int AP = NAUX > 0 ? GyPitch<(NAUX > 0 ? NAUX : 1)>::value : 1;
     const VecN<T, PITCH>* __restrict__ xv = reinterpret_cast<const VecN<T, PITCH>*>(xs);
@@ -1124,8 +1127,15 @@ __device__ __forceinline__ void allpairs_loop(const SysParams<T>& P, const T* __
         for (int e = 0; e < U; ++e) {
             const uint32_t q = min(j + e * step, j1 - 1u);
             a[e] = xv[q];
-            if constexpr (NAUX > 0) g[e] = gv[q];
-            av[e] = NA > 0 ? a_s[q] : T(0);
+            uint32_t p = q;
+            if constexpr (DIRECT && (NAUX > 0 || NA > 0)) p = perm[q];
+            if constexpr (NAUX > 0 && DIRECT) {
+#pragma unroll
+                for (int k = 0; k < NAUX; ++k) g[e].v[k] = aux[(size_t)p * NAUX + k];
+            } else if constexpr (NAUX > 0) {
+                g[e] = gv[q];
+            }
+            av[e] = NA > 0 ? a_s[p] : T(0);
         }
 #pragma unroll
         for (int e = 0; e < U; ++e) {
@@ -1336,7 +1346,22 @@ template <typename T, int D, int OP, bool BATCH, int MODE>
 void launch_flat(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* y,
                  T* gx, T* ga);
 
-// Forward / adjoint over every particle of the lane's system (minimum image).
+// Lanes per particle of the all-pairs kernels: enough groups for about 64K lanes in
+// flight, at most a wave.
+inline int all_group(uint64_t n) {
+    const uint64_t want = 65536;
+    if (n * 16 < want) return 64;
+    if (n * 4 < want) return 16;
+    if (n < want) return 4;
+    return 1;
+}
+// Below that size for a wave the all-pairs kernels read gradients and variables in the
+// caller's order, through perm: gathering them into cell order first costs a launch (1000
+// particles, 2 us and as much on the host) and saves a load per candidate of some 16 a lane.
+inline bool all_direct(uint64_t n) { return all_group(n) == 64; }
+
+// Forward / adjoint over every particle of the lane's system (minimum image); a_s and
+// gy_s in cell order, or with all_direct in the caller's.
 template <typename T, int D, int OP, bool BATCH>
 void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y);
 template <typename T, int D, int OP, bool BATCH>

@@ -48,17 +48,20 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_list(const T* __restrict__ 
 
 // dst[s][:] = src[perm[s]][:] for rows of W elements (W <= 4), written with a
 // row pitch of WP elements (3-wide rows are padded to 4, zero-filled, so that
-// the sums load a row with one vector load): one thread per row.
+// the sums load a row with one vector load), and with dst_a the one-element rows
+// dst_a[s] = a[perm[s]] beside them: one thread per row.
 template <typename T, int W, int WP>
 __global__ __launch_bounds__(256) void k_gather_rows(const T* __restrict__ src, const uint32_t* __restrict__ perm,
-                                                     uint32_t n, T* __restrict__ dst) {
+                                                     uint32_t n, T* __restrict__ dst, const T* __restrict__ a,
+                                                     T* __restrict__ dst_a) {
     const uint32_t s = blockIdx.x * 256 + threadIdx.x;
     if (s >= n) return;
     const uint32_t p = perm[s];
     VecN<T, WP> v;
 #pragma unroll
     for (int k = 0; k < WP; ++k) v.v[k] = k < W ? src[(size_t)p * W + k] : T(0);
-    reinterpret_cast<VecN<T, WP>*>(dst)[s] = v;
+    if (dst_a) dst_a[s] = a[p];
+    *reinterpret_cast<VecN<T, WP>*>(dst + (size_t)s * WP) = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -67,21 +70,36 @@ __global__ __launch_bounds__(256) void k_gather_rows(const T* __restrict__ src, 
 
 namespace {
 
+// Rows of w elements of src, and where a is given its one-element rows, in cell order.
 template <typename T>
-aboria_status gather(aboria_ctx* ctx, const aboria_cells* c, const void* src, int w, void* dst) {
+aboria_status gather(aboria_ctx* ctx, const aboria_cells* c, const void* src, int w, void* dst, const void* a = nullptr,
+                     void* dst_a = nullptr) {
     const uint32_t n = (uint32_t)c->n;
     if (n == 0 || w == 0) return ABORIA_OK;
     const dim3 grid((n + 255) / 256);
-    const T* s = (const T*)src;
-    T* d = (T*)dst;
+#define G(W, WP)                                                                                                    \
+    hipLaunchKernelGGL((k_gather_rows<T, W, WP>), grid, dim3(256), 0, ctx->stream, (const T*)src, c->perm, n, (T*)dst, \
+                       (const T*)a, (T*)dst_a)
     switch (w) {
-        case 1: hipLaunchKernelGGL((k_gather_rows<T, 1, 1>), grid, dim3(256), 0, ctx->stream, s, c->perm, n, d); break;
-        case 2: hipLaunchKernelGGL((k_gather_rows<T, 2, 2>), grid, dim3(256), 0, ctx->stream, s, c->perm, n, d); break;
-        case 3: hipLaunchKernelGGL((k_gather_rows<T, 3, 4>), grid, dim3(256), 0, ctx->stream, s, c->perm, n, d); break;
-        default: hipLaunchKernelGGL((k_gather_rows<T, 4, 4>), grid, dim3(256), 0, ctx->stream, s, c->perm, n, d); break;
+        case 1: G(1, 1); break;
+        case 2: G(2, 2); break;
+        case 3: G(3, 4); break;
+        default: G(4, 4); break;
     }
+#undef G
     ABORIA_HIP(ctx, hipGetLastError());
     return ABORIA_OK;
+}
+
+// A sum's variables and upstream gradient (gy null: none) in the order its kernels read.
+template <typename T>
+aboria_status gather_inputs(aboria_ctx* ctx, const aboria_cells* c, bool direct, const void* a, int32_t na,
+                            const void* gy, int32_t ny, const T** a_s, const T** gy_s) {
+    *a_s = na > 0 ? (const T*)(direct ? a : c->work) : nullptr;
+    *gy_s = gy ? (const T*)(direct ? gy : c->work2) : nullptr;
+    if (direct) return ABORIA_OK;
+    if (gy) return gather<T>(ctx, c, gy, ny, c->work2, na > 0 ? a : nullptr, na > 0 ? c->work : nullptr);
+    return na > 0 ? gather<T>(ctx, c, a, na, c->work) : ABORIA_OK;
 }
 
 // Work-mapping variants of the neighbour sums.
@@ -349,13 +367,11 @@ aboria_status pair_sum_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, 
     const size_t tsz = c->dtype == ABORIA_F32 ? 4 : 8;
     if (overlaps(y, tsz * ny * c->n, a, tsz * na * c->n))
         return fail(ctx, ABORIA_ERR_INVALID_ARG, "y overlaps a");
+    const bool direct = variant_of(variant).kind == 3 && all_direct((uint64_t)c->n);
     if (c->dtype == ABORIA_F32) {
         OpArgs<float> q{nparams > 0 ? (float)params[0] : 0.f};
-        const float* a_s = nullptr;
-        if (na > 0) {
-            if ((st = gather<float>(ctx, c, a, na, c->work)) != ABORIA_OK) return st;
-            a_s = (const float*)c->work;
-        }
+        const float *a_s, *none;
+        if ((st = gather_inputs<float>(ctx, c, direct, a, na, nullptr, 0, &a_s, &none)) != ABORIA_OK) return st;
         switch (c->d) {
             case 1: return fwd_op<float, 1>(ctx, c, op, q, a_s, (float*)y, variant);
             case 2: return fwd_op<float, 2>(ctx, c, op, q, a_s, (float*)y, variant);
@@ -363,11 +379,8 @@ aboria_status pair_sum_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, 
         }
     } else {
         OpArgs<double> q{nparams > 0 ? params[0] : 0.0};
-        const double* a_s = nullptr;
-        if (na > 0) {
-            if ((st = gather<double>(ctx, c, a, na, c->work)) != ABORIA_OK) return st;
-            a_s = (const double*)c->work;
-        }
+        const double *a_s, *none;
+        if ((st = gather_inputs<double>(ctx, c, direct, a, na, nullptr, 0, &a_s, &none)) != ABORIA_OK) return st;
         switch (c->d) {
             case 1: return fwd_op<double, 1>(ctx, c, op, q, a_s, (double*)y, variant);
             case 2: return fwd_op<double, 2>(ctx, c, op, q, a_s, (double*)y, variant);
@@ -389,15 +402,11 @@ aboria_status pair_bwd_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, 
         overlaps(ga, tsz * na * nb, gy, tsz * ny * nb) || overlaps(ga, tsz * na * nb, a, tsz * na * nb) ||
         overlaps(ga, tsz * na * nb, gx, tsz * c->d * nb))
         return fail(ctx, ABORIA_ERR_INVALID_ARG, "outputs overlap inputs");
+    const bool direct = variant_of(variant).kind == 3 && all_direct((uint64_t)c->n);
     if (c->dtype == ABORIA_F32) {
         OpArgs<float> q{nparams > 0 ? (float)params[0] : 0.f};
-        const float* a_s = nullptr;
-        if (na > 0) {
-            if ((st = gather<float>(ctx, c, a, na, c->work)) != ABORIA_OK) return st;
-            a_s = (const float*)c->work;
-        }
-        if ((st = gather<float>(ctx, c, gy, ny, c->work2)) != ABORIA_OK) return st;
-        const float* g_s = (const float*)c->work2;
+        const float *a_s, *g_s;
+        if ((st = gather_inputs<float>(ctx, c, direct, a, na, gy, ny, &a_s, &g_s)) != ABORIA_OK) return st;
         switch (c->d) {
             case 1: return bwd_op<float, 1>(ctx, c, op, q, a_s, g_s, (float*)gx, (float*)ga, variant);
             case 2: return bwd_op<float, 2>(ctx, c, op, q, a_s, g_s, (float*)gx, (float*)ga, variant);
@@ -405,13 +414,8 @@ aboria_status pair_bwd_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, 
         }
     } else {
         OpArgs<double> q{nparams > 0 ? params[0] : 0.0};
-        const double* a_s = nullptr;
-        if (na > 0) {
-            if ((st = gather<double>(ctx, c, a, na, c->work)) != ABORIA_OK) return st;
-            a_s = (const double*)c->work;
-        }
-        if ((st = gather<double>(ctx, c, gy, ny, c->work2)) != ABORIA_OK) return st;
-        const double* g_s = (const double*)c->work2;
+        const double *a_s, *g_s;
+        if ((st = gather_inputs<double>(ctx, c, direct, a, na, gy, ny, &a_s, &g_s)) != ABORIA_OK) return st;
         switch (c->d) {
             case 1: return bwd_op<double, 1>(ctx, c, op, q, a_s, g_s, (double*)gx, (double*)ga, variant);
             case 2: return bwd_op<double, 2>(ctx, c, op, q, a_s, g_s, (double*)gx, (double*)ga, variant);
@@ -449,14 +453,9 @@ aboria_status fused_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, con
                          const void* a, int32_t na, const void* gy, int32_t ny, void* y, void* gx, void* ga,
                          bool flat) {
     OpArgs<T> q{nparams > 0 ? (T)params[0] : T(0)};
-    aboria_status st;
-    const T* a_s = nullptr;
-    if (na > 0) {
-        if ((st = gather<T>(ctx, c, a, na, c->work)) != ABORIA_OK) return st;
-        a_s = (const T*)c->work;
-    }
-    if ((st = gather<T>(ctx, c, gy, ny, c->work2)) != ABORIA_OK) return st;
-    const T* g_s = (const T*)c->work2;
+    const T *a_s, *g_s;
+    const aboria_status st = gather_inputs<T>(ctx, c, false, a, na, gy, ny, &a_s, &g_s);
+    if (st != ABORIA_OK) return st;
     switch (c->d) {
         case 1: return fused_op<T, 1>(ctx, c, op, q, a_s, g_s, (T*)y, (T*)gx, (T*)ga, flat);
         case 2: return fused_op<T, 2>(ctx, c, op, q, a_s, g_s, (T*)y, (T*)gx, (T*)ga, flat);

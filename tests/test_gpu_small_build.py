@@ -44,3 +44,29 @@ def test_systems_and_domain_error():
     assert e.value.status == "DOMAIN"
     cells.close()
     c.close()
+
+
+@pytest.mark.parametrize("op,params", [("exp_force", (1.0,)), ("dem_spring", (1.0,)), ("soft_sphere", ())])
+@pytest.mark.parametrize("n", [64, 4095, 4096])
+def test_all_pairs_input_order(n, op, params):
+    """The all-pairs sums read gradients and variables in the caller's order below 4096
+    particles, gathered ones above; equal to the row search up to the order of the sums:
+    m = 80 neighbours at most, summands below 40 (a jittered lattice: distances over 0.3,
+    so a Jacobian's entries are below 5, times gradients below 8), so 2 m u m 40 = 6e-11."""
+    c = A.Context(0)
+    rng = np.random.default_rng(n)
+    grid = np.stack(np.meshgrid(*[np.arange(16) * 0.5] * 3, indexing="ij"), -1).reshape(-1, 3)[rng.permutation(4096)[:n]]
+    x = to_dev((grid + 0.25 + 0.1 * (2 * rng.random((n, 3)) - 1)).astype(np.float64))
+    cells = A.build_cells(c, x, [A.BoxSpec(3, [0.0] * 3, [8.0] * 3, [1, 1, 1], 1.0)])
+    a = to_dev(0.3 + 0.3 * rng.random((n, 1))) if op == "dem_spring" else None
+    gy = to_dev(np.clip(rng.standard_normal((n, A.op_ny(op, 3))), -4, 4))
+    got = []
+    for name in ("over all particles of its system", "adjoint evaluated on every candidate"):
+        c.set_variant(next(v for v in range(A.variant_count()) if name in A.variant_name(v)))
+        y = A.pair_sum(c, cells, op, params, a)
+        got.append((y, *A.pair_sum_backward(c, cells, op, params, gy, a)))
+    for u, v in zip(*got):
+        if u is not None:
+            assert float((u - v).abs().max()) <= 6e-11
+    cells.close()
+    c.close()
