@@ -9,6 +9,7 @@ fails loudly.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass, field
 from typing import Optional, Sequence, Union
@@ -122,7 +123,7 @@ def lib():
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -147,6 +148,7 @@ class Context:
 
     def __init__(self, device: int = 0, stream: Optional[torch.cuda.Stream] = None):
         self.device = device
+        self.torch_device = torch.device("cuda", device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(device)
         h = C.c_void_p()
         st = lib().aboria_create(device, C.c_void_p(self.stream.cuda_stream), C.byref(h))
@@ -309,10 +311,12 @@ def autotune_build(ctx: Context, x: torch.Tensor, boxes: Sequence[BoxSpec],
     return int(ipt.value), int(lb.value), int(sh.value)
 
 
+@functools.lru_cache(maxsize=None)
 def op_ny(op: str, d: int) -> int:
     return int(lib().aboria_op_ny(OPS[op], d))
 
 
+@functools.lru_cache(maxsize=None)
 def op_na(op: str) -> int:
     return int(lib().aboria_op_na(OPS[op]))
 
@@ -328,7 +332,7 @@ def pair_sum(ctx: Context, cells: Cells, op: str, params=(), a: Optional[torch.T
     """aboria_pair_sum: returns y[n][ny] in original particle order."""
     ny, na = op_ny(op, cells.d), op_na(op)
     if y is None:
-        y = torch.empty((cells.n, ny), dtype=cells.dtype, device="cuda:%d" % ctx.device)
+        y = torch.empty((cells.n, ny), dtype=cells.dtype, device=ctx.torch_device)
     _check_dev(y, "y", cells.dtype)
     if a is not None:
         _check_dev(a, "a", cells.dtype)
@@ -343,7 +347,7 @@ def pair_sum_backward(ctx: Context, cells: Cells, op: str, params, gy: torch.Ten
                       ga: Optional[torch.Tensor] = None, want_ga: bool = True):
     """aboria_pair_sum_backward: returns (gx[n][d], ga[n][na] or None)."""
     ny, na = op_ny(op, cells.d), op_na(op)
-    dev = "cuda:%d" % ctx.device
+    dev = ctx.torch_device
     _check_dev(gy, "gy", cells.dtype)
     if gx is None:
         gx = torch.empty((cells.n, cells.d), dtype=cells.dtype, device=dev)
@@ -361,7 +365,7 @@ def pair_sum_and_backward(ctx: Context, cells: Cells, op: str, params, gy: torch
                           gx: Optional[torch.Tensor] = None, want_ga: bool = True):
     """aboria_pair_sum_and_backward: (y, gx, ga) from one box search, gy known in advance."""
     ny, na = op_ny(op, cells.d), op_na(op)
-    dev = "cuda:%d" % ctx.device
+    dev = ctx.torch_device
     _check_dev(gy, "gy", cells.dtype)
     if y is None:
         y = torch.empty((cells.n, ny), dtype=cells.dtype, device=dev)
@@ -437,7 +441,7 @@ def pair_list(ctx: Context, cells: Cells):
     st = lib().aboria_pair_list(ctx.handle, cells.handle, 0, None, None, C.byref(total))
     ctx.check(st, "pair_list")
     m = int(total.value)
-    dev = "cuda:%d" % ctx.device
+    dev = ctx.torch_device
     pi = torch.empty(max(m, 1), dtype=torch.int32, device=dev)
     pj = torch.empty(max(m, 1), dtype=torch.int32, device=dev)
     st = lib().aboria_pair_list(ctx.handle, cells.handle, m, _ptr(pi), _ptr(pj), C.byref(total))
@@ -555,7 +559,7 @@ def autotune(ctx: Context, cells: Cells, op: str, params=(), a: Optional[torch.T
     """aboria_autotune: tunes the forward sum (gy None) or the adjoint for gy; returns the variant."""
     ny, na = op_ny(op, cells.d), op_na(op)
     width = ny if gy is None else cells.d
-    out = torch.empty((cells.n, width), dtype=cells.dtype, device="cuda:%d" % ctx.device)
+    out = torch.empty((cells.n, width), dtype=cells.dtype, device=ctx.torch_device)
     if gy is not None:
         _check_dev(gy, "gy", cells.dtype)
     arr, npar = _params(params)
