@@ -192,6 +192,126 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_adjoint(DenseJob<T> js, D
     else dense_block<T, D, TI, KERN, kGrad>(jt, sc, c2, (b - n1) % jt.tblocks, (b - n1) / jt.tblocks, tile);
 }
 
+// The lane's value from the next lane of the wave (lane 63: from lane 0).
+__device__ __forceinline__ float from_next_lane(float v) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x134 /* wave_rol:1 */, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double from_next_lane(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x134, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x134, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// The whole adjoint of a pair at once: targets, sources, weights w and gy, the targets'
+// partials pt[split][target][D] (kGrad's) and the sources' ps[target block][source][D + 1]
+// (kSumGrad's, with targets and sources exchanged).
+template <typename T>
+struct DensePairJob {
+    const T *xt, *xs, *w, *gy;
+    T *pt, *ps;
+    uint32_t nt, ns, jchunk, tblocks;
+};
+
+// Two passes form every pair's displacement, q and transcendental twice: 26 VALU slots a
+// pair for the 3-d multiquadric, and issue bounds them.  Here a pair is formed once.  A
+// wave keeps TI targets per lane and takes 64 sources at a time, each lane starting with
+// its own and going round: at step s, lane l has source (l + s) mod 64, read from LDS (the
+// 64 rows twice, so that no index wraps), whose sums come from the next lane, by one move
+// per sum and TI pairs.  After 64 steps every lane has its own source's sums over the
+// wave's targets; the four waves' are added in order.  22 slots a pair: 20011 x 30011 in
+// 3-d, multiquadric, 366 -> 335 us; 40000^2 in 2-d, Gaussian, 655 -> 502; 12000^2 in 3-d,
+// float64, Gaussian, 280 -> 187.
+template <typename T, int D, int TI, int KERN>
+__global__ __launch_bounds__(kDenseBlock) void k_dense_pairs(DensePairJob<T> jb, T sc, T c2) {
+    using R = Radial<T, D, KERN>;
+    __shared__ VecN<T, 4> tile[128];
+    __shared__ T sums[4][D + 1][64];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t tb = xcd_tile(blockIdx.x, gridDim.x), split = blockIdx.y;
+    T xi[TI][D], gi[TI], acc[TI][D];
+#pragma unroll
+    for (int q = 0; q < TI; ++q) {
+        const uint32_t t = tb * (kDenseBlock * TI) + q * kDenseBlock + threadIdx.x;
+        const uint32_t tc = t < jb.nt ? t : jb.nt - 1;
+        gi[q] = t < jb.nt ? jb.gy[tc] : T(0);
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            xi[q][k] = jb.xt[(size_t)tc * D + k] * sc;
+            acc[q][k] = T(0);
+        }
+    }
+    const uint32_t jbeg = split * jb.jchunk;
+    const uint32_t jend = min(jb.ns, jbeg + jb.jchunk);
+    for (uint32_t j0 = jbeg; j0 < jend; j0 += 64) {
+        if (wave < 2) {  // two waves, one copy each
+            const uint32_t j = j0 + lane;
+            VecN<T, 4> v;
+            v.v[0] = v.v[1] = v.v[2] = v.v[3] = T(0);
+            if (j < jend) {
+#pragma unroll
+                for (int k = 0; k < D; ++k) v.v[k] = jb.xs[(size_t)j * D + k] * sc;
+                v.v[3] = jb.w[j];
+            }
+            tile[threadIdx.x] = v;
+        }
+        __syncthreads();
+        T part[TI][D], own[D + 1];
+#pragma unroll
+        for (int k = 0; k < D + 1; ++k) own[k] = T(0);
+#pragma unroll
+        for (int q = 0; q < TI; ++q)
+#pragma unroll
+            for (int k = 0; k < D; ++k) part[q][k] = T(0);
+#pragma unroll 2
+        for (uint32_t step = 0; step < 64; ++step) {
+            const VecN<T, 4> p = tile[lane + step];
+            T add[D + 1];
+#pragma unroll
+            for (int q = 0; q < TI; ++q) {
+                T dk[D];
+#pragma unroll
+                for (int k = 0; k < D; ++k) dk[k] = xi[q][k] - p.v[k];
+                const T q2 = R::arg(dk, c2);
+                const T slope = R::slope(q2);
+                const T value = KERN == ABORIA_K_GAUSSIAN ? slope : R::value(q2);
+                const T ht = slope * p.v[3], hs = slope * gi[q];
+                add[0] = q == 0 ? value * gi[q] : kfma(value, gi[q], add[0]);
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    part[q][k] = kfma(ht, dk[k], part[q][k]);
+                    add[1 + k] = q == 0 ? hs * dk[k] : kfma(hs, dk[k], add[1 + k]);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < D + 1; ++k) own[k] = from_next_lane(own[k]) + add[k];
+        }
+#pragma unroll
+        for (int q = 0; q < TI; ++q)
+#pragma unroll
+            for (int k = 0; k < D; ++k) acc[q][k] += part[q][k];
+#pragma unroll
+        for (int k = 0; k < D + 1; ++k) sums[wave][k][lane] = from_next_lane(own[k]);
+        __syncthreads();
+        // (the source's displacement is seen from the source: its gradient's sign turns)
+        for (uint32_t e = threadIdx.x; e < 64u * (D + 1); e += kDenseBlock) {
+            const uint32_t i = e / (D + 1), k = e - i * (D + 1);
+            T v = sums[0][k][i] + sums[1][k][i];
+            v += sums[2][k][i];
+            v += sums[3][k][i];
+            if (j0 + i < jend) jb.ps[((size_t)tb * jb.ns + j0) * (D + 1) + e] = k == 0 ? v : -v;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < TI; ++q) {
+        const uint32_t t = tb * (kDenseBlock * TI) + q * kDenseBlock + threadIdx.x;
+        if (t < jb.nt)
+#pragma unroll
+            for (int k = 0; k < D; ++k) jb.pt[((size_t)split * jb.nt + t) * D + k] = acc[q][k];
+    }
+}
+
 // Reduction of one pass's split partials: out[e] = sum over splits of part[split][e]
 // for the nt * OUT values e = (target, component).  Component 0 of a kSumGrad pass
 // goes to y, every other one to g after the factor mult[target] * C (mult given).
@@ -464,12 +584,65 @@ aboria_status launch_dense(aboria_ctx* ctx, uint32_t nt, const void* xt, uint32_
 // run one after the other in the same scratch.
 constexpr size_t kAdjointScratch = size_t(256) << 20;
 
+// From this many pairs on the adjoint forms each pair once (k_dense_pairs); below, its two
+// passes side by side keep more workgroups in flight.  Two passes / once, us: 6000^2 in 2-d
+// 24.7 / 23.7, 8000^2 in 3-d 47.7 / 41.9, 40000 x 1500 in 1-d 33 / 25; float64 6000^2 73.9 /
+// 64.9, 12000 x 3000 in 3-d 79 / 60.
+constexpr uint64_t kPairsOnce = uint64_t(1) << 25;
+
 // The whole adjoint (gw and gxs from the source pass, gxt from the target pass) in one
 // launch and one reduction; *done = false when the passes have to run apart.
 template <typename T, int D, int KERN>
 aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint32_t ns, const void* xs, const void* w,
                              const void* gy, const KernelPlan& kp, void* gxt, void* gxs, void* gw, int32_t plan,
                              bool* done) {
+    if ((uint64_t)nt * ns >= kPairsOnce) {
+        const bool given = dense_plan_ok(plan, sizeof(T) == 4 ? ABORIA_F32 : ABORIA_F64);
+        // Two targets per lane: the waves that eight leave hide less in 3-d (20011 x 30011
+        // with 2 / 4 / 8: 335 / 351 / 369 us) and are too few for smaller sums; in 1-d and
+        // 2-d float32 eight from 2^30 pairs (40000^2 575 / 614 / 502).
+        const int32_t ti = given ? kDensePlans[plan].ti
+                                 : (sizeof(T) == 4 && D <= 2 && (uint64_t)nt * ns >= (uint64_t(1) << 30) ? 8 : 2);
+        const uint32_t wg = given ? (uint32_t)kDensePlans[plan].wg : 2048u;
+        const uint32_t per_block = kDenseBlock * (uint32_t)ti;
+        const uint32_t tblocks = (nt + per_block - 1) / per_block, steps = (ns + kDenseStep - 1) / kDenseStep;
+        const size_t bytes_s = (sizeof(T) * (size_t)tblocks * ns * (D + 1) + 255) & ~(size_t)255;
+        const size_t split_bytes = sizeof(T) * (size_t)nt * D;
+        // (at most 384 splits: their sums are read again; 1500 x 40000 with 625 56 us, 342 51)
+        uint32_t nsplit = std::min({steps, 384u, std::max<uint32_t>(1, (wg + tblocks - 1) / tblocks)});
+        // fewer splits where their partials would not fit
+        if (bytes_s + split_bytes <= kAdjointScratch) {
+            nsplit = (uint32_t)std::min<size_t>(nsplit, (kAdjointScratch - bytes_s) / split_bytes);
+            const uint32_t per_split = (steps + nsplit - 1) / nsplit;
+            nsplit = (steps + per_split - 1) / per_split;
+            aboria_status st = ensure_scratch(ctx, bytes_s + split_bytes * nsplit);
+            if (st != ABORIA_OK) return st;
+            T* ps = (T*)ctx->scratch;
+            T* pt = (T*)((char*)ctx->scratch + bytes_s);
+            const DensePairJob<T> jb{(const T*)xt, (const T*)xs, (const T*)w, (const T*)gy, pt, ps, nt, ns,
+                                     per_split * kDenseStep, tblocks};
+#define ABORIA_DENSE_LAUNCH(TI)                                                                                   \
+    hipLaunchKernelGGL((k_dense_pairs<T, D, TI, KERN>), dim3(tblocks, nsplit), dim3(kDenseBlock), 0, ctx->stream, \
+                       jb, (T)kp.sc, (T)kp.c2)
+            switch (ti) {
+                case 1: ABORIA_DENSE_LAUNCH(1); break;
+                case 2: ABORIA_DENSE_LAUNCH(2); break;
+                case 8:
+                    if constexpr (sizeof(T) == 4) ABORIA_DENSE_LAUNCH(8);
+                    break;
+                default: ABORIA_DENSE_LAUNCH(4); break;
+            }
+#undef ABORIA_DENSE_LAUNCH
+            const DenseReduceJob<T> rs{ps, (const T*)w, (T*)gw, (T*)gxs, ns, tblocks};
+            const DenseReduceJob<T> rt{pt, (const T*)gy, nullptr, (T*)gxt, nt, nsplit};
+            const uint32_t r1 = reduce_blocks(ns, D + 1), r2 = reduce_blocks(nt, D);
+            hipLaunchKernelGGL((k_dense_adjoint_reduce<T, D>), dim3(r1 + r2), dim3(256), 0, ctx->stream, rs, rt, r1,
+                               (T)kp.C);
+            ABORIA_HIP(ctx, hipGetLastError());
+            *done = true;
+            return ABORIA_OK;
+        }
+    }
     const PassShape a = pass_shape<T, D, kSumGrad>(ns, nt, plan, SIZE_MAX);
     const PassShape b = pass_shape<T, D, kGrad>(nt, ns, plan, SIZE_MAX);
     const size_t bytes_a = (a.split_bytes * a.nsplit + 255) & ~(size_t)255;
