@@ -112,17 +112,17 @@ def counted_traffic(names):
 
 def profile_names(variant_name, direction):
     """Kernel names as rocprofv3 reports them for the spring cube (float32, d = 3, no batch,
-    32-bit row offsets)."""
+    32-bit row offsets, one wave for all rows of its particles)."""
     if "recorded" in variant_name:
         k = ["k_nbr_fwd<float, 3, 1, false>"] if direction == "fwd" else ["k_nbr_bwd<float, 3, 1, false>"]
     elif "accepted-pair bit masks" in variant_name:
-        k = ["k_lane_mask<float, 3, 1, false, true, %d>" % (0 if direction == "fwd" else 1)]
+        k = ["k_lane_mask<float, 3, 1, false, true, %d, false>" % (0 if direction == "fwd" else 1)]
     elif "flattened" in variant_name:
-        k = ["k_flat<float, 3, 1, false, true, %d>" % (0 if direction == "fwd" else 1)]
+        k = ["k_flat<float, 3, 1, false, true, %d, false>" % (0 if direction == "fwd" else 1)]
     elif direction == "fwd":
-        k = ["k_lane_fwd<float, 3, 1, false, true>"]
+        k = ["k_lane_fwd<float, 3, 1, false, true, false>"]
     else:
-        k = ["k_lane_bwd<float, 3, 1, false, true>"]
+        k = ["k_lane_bwd<float, 3, 1, false, true, false, false>"]
     return k if direction == "fwd" else ["k_gather_rows<float, 3, 4>"] + k
 
 
@@ -487,9 +487,9 @@ def main():
                                           "plan": A.dense_plan_name(plan_g), "ms_untuned": t_dense0}
         # its adjoint with targets = sources: K^T gy plus the target and source position gradients
         t_dense_b = timed(lambda: A.dense_sum_backward(ctx, xd_t, xd_t, wd_t, sigma, gyd), reps=5)
-        # passes over the N^2 pairs: K^T gy with the source gradient, then the target gradient
-        extra["dense_gaussian_n65536_adjoint"] = {"ms": t_dense_b, "pair_passes": 2,
-                                                  "pairs_per_s": 2 * npair / (t_dense_b * 1e-3),
+        # one pass over the N^2 pairs gives K^T gy and both position gradients
+        extra["dense_gaussian_n65536_adjoint"] = {"ms": t_dense_b, "pair_passes": 1,
+                                                  "pairs_per_s": npair / (t_dense_b * 1e-3),
                                                   "plan": A.dense_plan_name(plan_gb), "ms_untuned": t_dense_b0}
         # the multiquadric basis of the RBF example, c = 0.1 (per pair: 2 sub, mul, fma, add of c^2,
         # fma, and the sqrt)

@@ -917,8 +917,9 @@ __device__ __forceinline__ T gap2(const SysParams<T>& P, int k, int32_t o, T fr)
 // candidates the predicate rejects).  A lane uses its own LDS column only, so
 // no barrier is needed and lanes past the end may simply not call it.  t_self
 // is the lane's own slot (< n), the target of loads issued past its last
-// candidate.  row_done() is called between the candidates of one row and the next.
-template <typename T, int D, int CAP, int BLOCK, bool OFF32, typename Visit, typename RowDone>
+// candidate.  With ROWS, row_done() is called between the candidates of one row and the next
+// (the flag it follows costs 4 to 7 % of the walk).
+template <typename T, int D, int CAP, int BLOCK, bool OFF32, bool ROWS, typename Visit, typename RowDone>
 __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __restrict__ xs,
                                           const uint32_t* __restrict__ off, uint32_t n, const T* xi,
                                           uint32_t t_self, FlatRanges<CAP, BLOCK>& fr_lds, Visit&& visit,
@@ -965,7 +966,7 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
         };
         while (rows_left && kd + pmax <= CAP) {
             const int32_t ry = dy, rz = dz;
-            new_row = kFlatNewRow;
+            new_row = ROWS ? kFlatNewRow : 0u;
             if (++dy > yr) {
                 dy = -yr;
                 if (++dz > zr) rows_left = false;
@@ -1023,7 +1024,7 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
                 nr = false;
                 if (j >= e) {
                     if (kr < (uint32_t)kd) {
-                        nr = (ndc & kFlatNewRow) != 0u;
+                        if (ROWS) nr = (ndc & kFlatNewRow) != 0u;
                         j = ndp.x;
                         e = ndp.y;
                         if (SHIFT) decode_shift<T, D>(P, ndc, cs);
@@ -1040,7 +1041,7 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
             // evaluated on every lane (an idle lane tests its own row, which the
             // predicate rejects) so that the wait for the row is never skipped
             auto test = [&](const VecN<T, PITCH>& xj, uint32_t jj, const T* sh, bool valid, bool first) {
-                if (first) row_done();
+                if (ROWS && first) row_done();
                 T dx[D], d2;
                 const bool acc = pair_test<T, D, SHIFT>(xj.v, xi, sh, r2, dx, &d2);
                 if (acc & valid) {

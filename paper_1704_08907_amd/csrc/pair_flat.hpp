@@ -12,14 +12,14 @@ constexpr int kFlatCap = 8;  // ranges a lane lists per round (>= 2 kMaxReach + 
 
 enum FlatMode { kFlatFwd = 0, kFlatBwd = 1, kFlatFused = 2 };
 
-template <typename T, int D, int OP, bool BATCH, bool OFF32, int MODE>
+template <typename T, int D, int OP, bool BATCH, bool OFF32, int MODE, bool ROWS>
 __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                      const uint32_t* __restrict__ perm, uint32_t n,
                                                      const SysParams<T>* __restrict__ sp,
                                                      const uint32_t* __restrict__ sys_part, int nsys,
                                                      const T* __restrict__ a_s, const T* __restrict__ gy_s,
                                                      OpArgs<T> q, T* __restrict__ y, T* __restrict__ gx,
-                                                     T* __restrict__ ga, bool by_rows) {
+                                                     T* __restrict__ ga) {
     static_assert(kFlatCap >= 2 * kMaxReach + 1, "a row of a narrow grid must fit one round");
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
     T gyi[NY];
     if (BWD) load_gy<T, NY, OFF32>(gy_s, s, gyi);
     constexpr int NA = OpShape<OP, D>::NA;
-    RowSums<T, NY + D + NA> sums(by_rows);
+    RowSums<T, NY + D + NA> sums(ROWS);
     T* const acc = sums.acc;  // y, gx, ga
     T* const accx = acc + NY;
     T* const acca = accx + (NA ? D : 0);
@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
             Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
         }
     };
-    flat_loop<T, D, kFlatCap, kFlatBlock, OFF32>(P, xs, off, n, xi, s, ranges, visit, [&]() { sums.row_done(); });
+    flat_loop<T, D, kFlatCap, kFlatBlock, OFF32, ROWS>(P, xs, off, n, xi, s, ranges, visit, [&]() { sums.row_done(); });
     sums.last();
     const uint32_t o = perm[s];
     if (FWD) {
@@ -70,15 +70,14 @@ void launch_flat(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, con
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const dim3 grid((n + kFlatBlock - 1) / kFlatBlock);
-    const bool by_rows = row_split(c) > 0;
-    if (off32_rows<T>(n))
-        hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, true, MODE>), grid, dim3(kFlatBlock), 0, ctx->stream,
-                           (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga,
-                           by_rows);
-    else
-        hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, false, MODE>), grid, dim3(kFlatBlock), 0, ctx->stream,
-                           (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga,
-                           by_rows);
+#define FL(O, R)                                                                                               \
+    hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, O, MODE, R>), grid, dim3(kFlatBlock), 0, ctx->stream,           \
+                       (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga)
+    // (sums go by rows below a size whose offsets are far below 32 bits)
+    if (row_split(c) > 0) FL(true, (D > 1));
+    else if (off32_rows<T>(n)) FL(true, false);
+    else FL(false, false);
+#undef FL
 }
 
 }  // namespace aboria
