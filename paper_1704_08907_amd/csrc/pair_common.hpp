@@ -71,34 +71,6 @@ struct PairOp {
         }
     }
 
-    // Branchless forms: every lane evaluates the summand and keeps it only if
-    // ok (a select, never a multiply, so the inf/NaN a rejected or sentinel
-    // candidate produces cannot leak into the sums).
-    __device__ __forceinline__ static void fwd_masked(const OpArgs<T>& q, T r, const T* dx, T d2, T ai, T aj, bool ok,
-                                                      T* acc) {
-        if constexpr (OP == ABORIA_OP_COUNT) {
-            acc[0] += ok ? T(1) : T(0);
-        } else if constexpr (OP == ABORIA_OP_SOFT_SPHERE) {
-            const T s = d2 * rsqrt_t(d2);
-            const T v = fma_t(-s, T(1) / r, T(1));
-            const T term = T(0.5) * v * v;
-            acc[0] += ok ? term : T(0);
-        } else {
-            const T rinv = rsqrt_t(d2);
-            T g;
-            if constexpr (OP == ABORIA_OP_SPRING) {
-                g = fma_t(q.p0 * r, rinv, -q.p0);
-            } else if constexpr (OP == ABORIA_OP_EXP_FORCE) {
-                g = q.p0 * exp_neg_t(d2 * rinv) * rinv;
-            } else {
-                g = fma_t(q.p0 * (ai + aj), rinv, -q.p0);
-            }
-            g = ok ? g : T(0);
-#pragma unroll
-            for (int k = 0; k < D; ++k) acc[k] = fma_t(-g, dx[k], acc[k]);
-        }
-    }
-
     // The radial profile of the vector operators f = g(s) u at one pair, as the
     // two factors of its Jacobian J = g I + (g'/s) u u^T: g across u and
     // gpar = g + s g' along u.  Spring and DEM spring: gpar = -k; eq. (1)
@@ -118,50 +90,6 @@ struct PairOp {
         }
     }
 
-    __device__ __forceinline__ static void bwd_masked(const OpArgs<T>& q, T r, const T* dx, T d2, T ai, T aj,
-                                                      const T* gyi, const T* gyj, bool ok, T* gx, T* ga) {
-        if constexpr (OP == ABORIA_OP_COUNT) {
-            return;
-        } else if constexpr (OP == ABORIA_OP_SOFT_SPHERE) {
-            const T rinv = rsqrt_t(d2);
-            const T s = d2 * rinv;
-            const T inv_r = T(1) / r;
-            T coef = (gyi[0] + gyj[0]) * inv_r * fma_t(-s, inv_r, T(1)) * rinv;
-            coef = ok ? coef : T(0);
-#pragma unroll
-            for (int k = 0; k < D; ++k) gx[k] = fma_t(coef, dx[k], gx[k]);
-        } else {
-            // as bwd(); every factor is zeroed on a rejected candidate, whose
-            // d2 may be 0 (rinv = inf), before it meets a finite w
-            const T rinv = rsqrt_t(d2);
-            T w[D];
-            T dw = T(0);
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                w[k] = gyi[k] - gyj[k];
-                dw = fma_t(dx[k], w[k], dw);
-            }
-            T g, gpar;
-            radial_parts(q, r, d2, rinv, ai, aj, g, gpar);
-            if constexpr (OP == ABORIA_OP_DEM_SPRING) {
-                const T ta = -q.p0 * dw * rinv;
-                ga[0] += ok ? ta : T(0);
-            }
-            if constexpr (D == 1) {
-                gx[0] = fma_t(ok ? gpar : T(0), w[0], gx[0]);
-            } else {
-                const T c = ok ? dw * (rinv * rinv) : T(0);
-                g = ok ? g : T(0);
-                const T pc = gpar * c;
-#pragma unroll
-                for (int k = 0; k < D; ++k) {
-                    const T wperp = fma_t(-c, dx[k], w[k]);
-                    gx[k] = fma_t(g, wperp, fma_t(pc, dx[k], gx[k]));
-                }
-            }
-        }
-    }
-
     // gx += J1(i,j)^T gy_i + J2(j,i)^T gy_j ; ga += d/da_i of the same.
     // For f = g(s) u the pair adds J w with w = gy_i - gy_j.  Splitting w into
     // its parts along and across u, w_par = ((dx.w)/s^2) dx and w_perp = w -
@@ -175,10 +103,11 @@ struct PairOp {
         if constexpr (OP == ABORIA_OP_COUNT) {
             return;
         } else if constexpr (OP == ABORIA_OP_SOFT_SPHERE) {
-            const T rinv = rsqrt_t(d2);
-            const T s = d2 * rinv;
+            // (1 - s/r) / s as 1/s - 1/r: two operations less and the rounding of 1/s
+            // alone.  ((1/r) (1/s) - (1/r)^2 would be one more less, but the registers of
+            // (1/r)^2 cost the batch's adjoint a wave per SIMD: 1724 -> 1765 us a pass.)
             const T inv_r = T(1) / r;
-            const T coef = (gyi[0] + gyj[0]) * inv_r * fma_t(-s, inv_r, T(1)) * rinv;
+            const T coef = ((gyi[0] + gyj[0]) * inv_r) * (rsqrt_t(d2) - inv_r);
 #pragma unroll
             for (int k = 0; k < D; ++k) gx[k] = fma_t(coef, dx[k], gx[k]);
         } else {
