@@ -678,8 +678,11 @@ __device__ __forceinline__ void neighbour_loop_staged(const SysParams<T>& P, con
 // order.  The rows of 64 particles can then be spread over several waves whose sums
 // are added in the same order: same bits, whichever kernel forms them.  On larger
 // cell lists one wave takes all rows of its 64 particles and adds every pair to one
-// running sum.  Kernels with SPLIT do the former, with `split` waves per 64 particles;
-// a wave's part of the work:
+// running sum.  Kernels with SPLIT do the former, with `split` waves per 64 particles.
+// A launch is split by the boxes of its time, but one in a graph replays after a rebuild
+// with other boxes: the last wave's rows have no end, so a search that has become deeper
+// than one cell in y or z still visits all of them (their sums joining the last row's).
+// A wave's part of the work:
 struct WaveRows {
     uint32_t first;   // first particle slot of the workgroup
     uint32_t s;       // this lane's particle slot
@@ -696,7 +699,8 @@ __device__ __forceinline__ WaveRows wave_rows(int32_t split) {
         return WaveRows{first, first + threadIdx.x, wave, kAllRows};
     }
     const int32_t per = kStencilRows<D> / split;
-    return WaveRows{tile * 64u, tile * 64u + (threadIdx.x & 63u), wave, RowRange{wave * per, (wave + 1) * per}};
+    return WaveRows{tile * 64u, tile * 64u + (threadIdx.x & 63u), wave,
+                    RowRange{wave * per, wave + 1 == split ? kAllRows.last : (wave + 1) * per}};
 }
 
 // The NV sums of a lane's particle: acc the running sum or, by rows, the current
@@ -747,9 +751,11 @@ struct WaveSums {
                 sums.row_done();
                 return;
             }
+            constexpr int32_t R = kStencilRows<D>;
+            T* const p = reinterpret_cast<T*>(part) + min(row, R - 1) * NV * 64 + (threadIdx.x & 63u);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
-                reinterpret_cast<T*>(part)[(row * NV + k) * 64 + (threadIdx.x & 63u)] = sums.acc[k];
+                p[k * 64] = row < R ? sums.acc[k] : p[k * 64] + sums.acc[k];
                 sums.acc[k] = T(0);
             }
         }
