@@ -94,6 +94,8 @@ struct aboria_ctx {
     bool capturing = false;
     void* scratch = nullptr;         // grow-only scratch for dense partial sums
     size_t scratch_bytes = 0;
+    bool scratch_in_graph = false;        // a capture used it
+    std::vector<void*> scratch_held;      // outgrown scratch that graphs may hold
     int32_t variant_forced = -1;
     int32_t build_strategy = ABORIA_BUILD_RADIX;
     int32_t lds_per_block = 0;       // device limit on LDS per workgroup (queried on first use)

@@ -163,6 +163,7 @@ static void release_ctx(void* p) {
     if (ctx->d_flag) (void)hipFree(ctx->d_flag);
     if (ctx->h_flag) (void)hipHostFree(ctx->h_flag);
     if (ctx->scratch) (void)hipFree(ctx->scratch);
+    for (void* held : ctx->scratch_held) (void)hipFree(held);
     delete ctx;
 }
 

@@ -462,22 +462,39 @@ KernelPlan plan_kernel(int kernel, double prm) {
     return k;
 }
 
+// Gives the context's scratch need bytes; false where it has fewer and a capture is in
+// progress (nothing is allocated then) or the device has none left.  A graph may hold
+// scratch that was there when it was captured: that is kept until the context goes.
+bool grow_scratch(aboria_ctx* ctx, size_t need) {
+    if (ctx->scratch_bytes < need) {
+        if (ctx->capturing) return false;
+        if (ctx->scratch) {
+            if (ctx->scratch_in_graph) {
+                ctx->scratch_held.push_back(ctx->scratch);
+            } else {
+                if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+                (void)hipFree(ctx->scratch);
+            }
+            ctx->scratch = nullptr;
+            ctx->scratch_bytes = 0;
+            ctx->scratch_in_graph = false;
+        }
+        if (hipMalloc(&ctx->scratch, need) != hipSuccess) {
+            (void)hipGetLastError();
+            ctx->scratch = nullptr;
+            return false;
+        }
+        ctx->scratch_bytes = need;
+    }
+    ctx->scratch_in_graph |= ctx->capturing;
+    return true;
+}
+
 aboria_status ensure_scratch(aboria_ctx* ctx, size_t need) {
-    if (ctx->scratch_bytes >= need) return ABORIA_OK;
+    if (grow_scratch(ctx, need)) return ABORIA_OK;
     if (ctx->capturing)
         return fail(ctx, ABORIA_ERR_UNSUPPORTED, "dense scratch must be sized by an uncaptured call first");
-    if (ctx->scratch) {
-        ABORIA_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        (void)hipFree(ctx->scratch);
-        ctx->scratch = nullptr;
-        ctx->scratch_bytes = 0;
-    }
-    if (hipMalloc(&ctx->scratch, need) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(ctx, ABORIA_ERR_OUT_OF_MEMORY, "dense scratch allocation failed");
-    }
-    ctx->scratch_bytes = need;
-    return ABORIA_OK;
+    return fail(ctx, ABORIA_ERR_OUT_OF_MEMORY, "dense scratch allocation failed");
 }
 
 // Device address of this GPU's copy of the no-allocation scratch array, looked
@@ -591,11 +608,16 @@ constexpr size_t kAdjointScratch = size_t(256) << 20;
 constexpr uint64_t kPairsOnce = uint64_t(1) << 25;
 
 // The whole adjoint (gw and gxs from the source pass, gxt from the target pass) in one
-// launch and one reduction; *done = false when the passes have to run apart.
+// launch and one reduction; *done = false when the passes have to run apart.  Both forms
+// here take more scratch than either pass: they are left where it cannot be had (a capture
+// after uncaptured calls for one gradient at a time, a full device), and an uncaptured call
+// leaves scratch for either pass too, so that a capture may ask for fewer gradients.
 template <typename T, int D, int KERN>
 aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint32_t ns, const void* xs, const void* w,
                              const void* gy, const KernelPlan& kp, void* gxt, void* gxs, void* gw, int32_t plan,
                              bool* done) {
+    const PassShape a = pass_shape<T, D, kSumGrad>(ns, nt, plan, SIZE_MAX);
+    const PassShape b = pass_shape<T, D, kGrad>(nt, ns, plan, SIZE_MAX);
     if ((uint64_t)nt * ns >= kPairsOnce) {
         const bool given = dense_plan_ok(plan, sizeof(T) == 4 ? ABORIA_F32 : ABORIA_F64);
         // Two targets per lane: the waves that eight leave hide less in 3-d (20011 x 30011
@@ -611,12 +633,13 @@ aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint3
         // (at most 384 splits: their sums are read again; 1500 x 40000 with 625 56 us, 342 51)
         uint32_t nsplit = std::min({steps, 384u, std::max<uint32_t>(1, (wg + tblocks - 1) / tblocks)});
         // fewer splits where their partials would not fit
-        if (bytes_s + split_bytes <= kAdjointScratch) {
-            nsplit = (uint32_t)std::min<size_t>(nsplit, (kAdjointScratch - bytes_s) / split_bytes);
-            const uint32_t per_split = (steps + nsplit - 1) / nsplit;
-            nsplit = (steps + per_split - 1) / per_split;
-            aboria_status st = ensure_scratch(ctx, bytes_s + split_bytes * nsplit);
-            if (st != ABORIA_OK) return st;
+        const bool fits = bytes_s + split_bytes <= kAdjointScratch;
+        if (fits) nsplit = (uint32_t)std::min<size_t>(nsplit, (kAdjointScratch - bytes_s) / split_bytes);
+        const uint32_t per_split = (steps + nsplit - 1) / nsplit;
+        nsplit = (steps + per_split - 1) / per_split;
+        const size_t need = bytes_s + split_bytes * nsplit;
+        const size_t passes = std::max(a.split_bytes * a.nsplit, b.split_bytes * b.nsplit);
+        if (fits && grow_scratch(ctx, ctx->capturing ? need : std::max(need, passes))) {
             T* ps = (T*)ctx->scratch;
             T* pt = (T*)((char*)ctx->scratch + bytes_s);
             const DensePairJob<T> jb{(const T*)xt, (const T*)xs, (const T*)w, (const T*)gy, pt, ps, nt, ns,
@@ -643,15 +666,11 @@ aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint3
             return ABORIA_OK;
         }
     }
-    const PassShape a = pass_shape<T, D, kSumGrad>(ns, nt, plan, SIZE_MAX);
-    const PassShape b = pass_shape<T, D, kGrad>(nt, ns, plan, SIZE_MAX);
     const size_t bytes_a = (a.split_bytes * a.nsplit + 255) & ~(size_t)255;
     const size_t need = bytes_a + b.split_bytes * b.nsplit;
     // one kernel holds one target count per lane
-    *done = a.ti == b.ti && need <= kAdjointScratch;
+    *done = a.ti == b.ti && need <= kAdjointScratch && grow_scratch(ctx, need);
     if (!*done) return ABORIA_OK;
-    aboria_status st = ensure_scratch(ctx, need);
-    if (st != ABORIA_OK) return st;
     T* pa = (T*)ctx->scratch;
     T* pb = (T*)((char*)ctx->scratch + bytes_a);
     const DenseJob<T> js{(const T*)xs, (const T*)xt, (const T*)gy, pa, ns, nt, a.jchunk, a.tblocks};
