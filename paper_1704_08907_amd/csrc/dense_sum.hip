@@ -20,6 +20,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -231,10 +232,15 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_pairs(DensePairJob<T> jb,
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t tb = xcd_tile(blockIdx.x, gridDim.x), split = blockIdx.y;
     T xi[TI][D], gi[TI], acc[TI][D];
+    // Lanes past the last target stand on it with a gradient of zero.  That leaves a sum as
+    // it is unless their kernel value overflows, where the multiquadric's is left out.
+    const bool whole = (uint64_t)(tb + 1) * (kDenseBlock * TI) <= jb.nt;
+    bool there[TI];
 #pragma unroll
     for (int q = 0; q < TI; ++q) {
         const uint32_t t = tb * (kDenseBlock * TI) + q * kDenseBlock + threadIdx.x;
         const uint32_t tc = t < jb.nt ? t : jb.nt - 1;
+        there[q] = t < jb.nt;
         gi[q] = t < jb.nt ? jb.gy[tc] : T(0);
 #pragma unroll
         for (int k = 0; k < D; ++k) {
@@ -264,29 +270,35 @@ __global__ __launch_bounds__(kDenseBlock) void k_dense_pairs(DensePairJob<T> jb,
         for (int q = 0; q < TI; ++q)
 #pragma unroll
             for (int k = 0; k < D; ++k) part[q][k] = T(0);
+        auto walk = [&](auto mask_tag) {
+            constexpr bool MASK = decltype(mask_tag)::value;
 #pragma unroll 2
-        for (uint32_t step = 0; step < 64; ++step) {
-            const VecN<T, 4> p = tile[lane + step];
-            T add[D + 1];
+            for (uint32_t step = 0; step < 64; ++step) {
+                const VecN<T, 4> p = tile[lane + step];
+                T add[D + 1];
 #pragma unroll
-            for (int q = 0; q < TI; ++q) {
-                T dk[D];
+                for (int q = 0; q < TI; ++q) {
+                    T dk[D];
 #pragma unroll
-                for (int k = 0; k < D; ++k) dk[k] = xi[q][k] - p.v[k];
-                const T q2 = R::arg(dk, c2);
-                const T slope = R::slope(q2);
-                const T value = KERN == ABORIA_K_GAUSSIAN ? slope : R::value(q2);
-                const T ht = slope * p.v[3], hs = slope * gi[q];
-                add[0] = q == 0 ? value * gi[q] : kfma(value, gi[q], add[0]);
+                    for (int k = 0; k < D; ++k) dk[k] = xi[q][k] - p.v[k];
+                    const T q2 = R::arg(dk, c2);
+                    const T slope = R::slope(q2);
+                    T value = KERN == ABORIA_K_GAUSSIAN ? slope : R::value(q2);
+                    if constexpr (MASK) value = there[q] ? value : T(0);
+                    const T ht = slope * p.v[3], hs = slope * gi[q];
+                    add[0] = q == 0 ? value * gi[q] : kfma(value, gi[q], add[0]);
 #pragma unroll
-                for (int k = 0; k < D; ++k) {
-                    part[q][k] = kfma(ht, dk[k], part[q][k]);
-                    add[1 + k] = q == 0 ? hs * dk[k] : kfma(hs, dk[k], add[1 + k]);
+                    for (int k = 0; k < D; ++k) {
+                        part[q][k] = kfma(ht, dk[k], part[q][k]);
+                        add[1 + k] = q == 0 ? hs * dk[k] : kfma(hs, dk[k], add[1 + k]);
+                    }
                 }
-            }
 #pragma unroll
-            for (int k = 0; k < D + 1; ++k) own[k] = from_next_lane(own[k]) + add[k];
-        }
+                for (int k = 0; k < D + 1; ++k) own[k] = from_next_lane(own[k]) + add[k];
+            }
+        };
+        if (KERN == ABORIA_K_GAUSSIAN || whole) walk(std::integral_constant<bool, false>());
+        else walk(std::integral_constant<bool, true>());
 #pragma unroll
         for (int q = 0; q < TI; ++q)
 #pragma unroll
