@@ -619,6 +619,13 @@ constexpr size_t kAdjointScratch = size_t(256) << 20;
 // 64.9, 12000 x 3000 in 3-d 79 / 60.
 constexpr uint64_t kPairsOnce = uint64_t(1) << 25;
 
+// Where that scratch leaves it fewer splits than it wants, the fewest workgroups it still
+// pays with.  Once / two passes, us: 91000^2 in 3-d, multiquadric, 1424 workgroups 4442 /
+// 4650, 91400^2 1074 5082 / 4670, 92000^2 540 6695 / 4720; float64 64200^2 756 6672 / 7520,
+// 64400^2 630 8244 / 7560.
+template <typename T>
+constexpr uint32_t kPairsOnceBlocks = sizeof(T) == 4 ? 1280 : 704;
+
 // The whole adjoint (gw and gxs from the source pass, gxt from the target pass) in one
 // launch and one reduction; *done = false when the passes have to run apart.  Both forms
 // here take more scratch than either pass: they are left where it cannot be had (a capture
@@ -645,8 +652,9 @@ aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint3
         // (at most 384 splits: their sums are read again; 1500 x 40000 with 625 56 us, 342 51)
         uint32_t nsplit = std::min({steps, 384u, std::max<uint32_t>(1, (wg + tblocks - 1) / tblocks)});
         // fewer splits where their partials would not fit
-        const bool fits = bytes_s + split_bytes <= kAdjointScratch;
-        if (fits) nsplit = (uint32_t)std::min<size_t>(nsplit, (kAdjointScratch - bytes_s) / split_bytes);
+        const size_t left = bytes_s < kAdjointScratch ? (kAdjointScratch - bytes_s) / split_bytes : 0;
+        const bool fits = left >= nsplit || tblocks * left >= kPairsOnceBlocks<T>;
+        nsplit = (uint32_t)std::min<size_t>(nsplit, std::max<size_t>(left, 1));
         const uint32_t per_split = (steps + nsplit - 1) / nsplit;
         nsplit = (steps + per_split - 1) / per_split;
         const size_t need = bytes_s + split_bytes * nsplit;
