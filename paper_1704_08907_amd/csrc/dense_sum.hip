@@ -416,10 +416,19 @@ bool dense_plan_ok(int32_t p, int dtype) {
     return p >= 0 && p < kNumDensePlans && (dtype == ABORIA_F32 || kDensePlans[p].ti <= 4);
 }
 
-// Tuning key: direction, kernel, dtype, d and the size buckets (floor log2) of
-// the targets and sources.
+// From this many pairs on the adjoint forms each pair once (k_dense_pairs); below, its two
+// passes side by side keep more workgroups in flight.  Two passes / once, us: 6000^2 in 2-d
+// 24.7 / 23.7, 8000^2 in 3-d 47.7 / 41.9, 40000 x 1500 in 1-d 33 / 25; float64 6000^2 73.9 /
+// 64.9, 12000 x 3000 in 3-d 79 / 60.
+constexpr uint64_t kPairsOnce = uint64_t(1) << 25;
+
+// Tuning key: direction with the adjoint's form (a plan that suits one form of it does not
+// suit the other, and both occur in one pair of size buckets), kernel, dtype, d and the size
+// buckets (floor log2) of the targets and sources.  Directions count from 4: plans that were
+// saved under 0 and 1 were timed on kernels that split the sources by 256 and formed the
+// adjoint's pairs twice.
 uint64_t dense_key(bool backward, int kernel, int dtype, int d, int64_t nt, int64_t ns) {
-    uint64_t k = backward ? 1u : 0u;
+    uint64_t k = 4u + (!backward ? 0u : ((uint64_t)nt * (uint64_t)ns < kPairsOnce ? 1u : 2u));
     k = k * 4 + (uint64_t)kernel;
     k = k * 4 + (uint64_t)dtype;
     k = k * 4 + (uint64_t)d;
@@ -612,12 +621,6 @@ aboria_status launch_dense(aboria_ctx* ctx, uint32_t nt, const void* xt, uint32_
 // Partials of both adjoint passes that one launch may keep at once; above it the passes
 // run one after the other in the same scratch.
 constexpr size_t kAdjointScratch = size_t(256) << 20;
-
-// From this many pairs on the adjoint forms each pair once (k_dense_pairs); below, its two
-// passes side by side keep more workgroups in flight.  Two passes / once, us: 6000^2 in 2-d
-// 24.7 / 23.7, 8000^2 in 3-d 47.7 / 41.9, 40000 x 1500 in 1-d 33 / 25; float64 6000^2 73.9 /
-// 64.9, 12000 x 3000 in 3-d 79 / 60.
-constexpr uint64_t kPairsOnce = uint64_t(1) << 25;
 
 // Where that scratch leaves it fewer splits than it wants, the fewest workgroups it still
 // pays with.  Once / two passes, us: 91000^2 in 3-d, multiquadric, 1424 workgroups 4442 /
