@@ -641,13 +641,15 @@ aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint3
     const PassShape a = pass_shape<T, D, kSumGrad>(ns, nt, plan, SIZE_MAX);
     const PassShape b = pass_shape<T, D, kGrad>(nt, ns, plan, SIZE_MAX);
     if ((uint64_t)nt * ns >= kPairsOnce) {
-        const bool given = dense_plan_ok(plan, sizeof(T) == 4 ? ABORIA_F32 : ABORIA_F64);
+        // (a float-only plan is plan 0 in float64, as in the passes)
+        const int32_t p = dense_plan_ok(plan, sizeof(T) == 4 ? ABORIA_F32 : ABORIA_F64) ? plan : std::min(plan, 0);
+        const bool given = p >= 0;
         // Two targets per lane: the waves that eight leave hide less in 3-d (20011 x 30011
         // with 2 / 4 / 8: 335 / 351 / 369 us) and are too few for smaller sums; in 1-d and
         // 2-d float32 eight from 2^30 pairs (40000^2 575 / 614 / 502).
-        const int32_t ti = given ? kDensePlans[plan].ti
+        const int32_t ti = given ? kDensePlans[p].ti
                                  : (sizeof(T) == 4 && D <= 2 && (uint64_t)nt * ns >= (uint64_t(1) << 30) ? 8 : 2);
-        const uint32_t wg = given ? (uint32_t)kDensePlans[plan].wg : 2048u;
+        const uint32_t wg = given ? (uint32_t)kDensePlans[p].wg : 2048u;
         const uint32_t per_block = kDenseBlock * (uint32_t)ti;
         const uint32_t tblocks = (nt + per_block - 1) / per_block, steps = (ns + kDenseStep - 1) / kDenseStep;
         const size_t bytes_s = (sizeof(T) * (size_t)tblocks * ns * (D + 1) + 255) & ~(size_t)255;

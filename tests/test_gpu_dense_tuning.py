@@ -62,3 +62,17 @@ def test_plans_of_earlier_kernels_are_not_used(tmp_path, monkeypatch):
     assert all(torch.equal(a, b) for a, b in zip(got, want))
     c.close()
     plain.close()
+
+
+@pytest.mark.parametrize("n", [3000, 6000])  # both forms of the adjoint
+def test_float_only_plan_is_plan_0_in_float64(n):
+    x, w, gy = arrays(n, torch.float64)
+    names = [A.dense_plan_name(p) for p in range(9)]
+    c = A.Context(0)
+    got = []
+    for plan in (0, names.index("8 targets per lane, 2048 workgroups")):
+        c.set_dense_plan(plan)
+        got.append([A.dense_sum(c, x, x, w, 0.2), *A.dense_sum_backward(c, x, x, w, 0.2, gy)])
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(*got))
+    c.close()
