@@ -23,6 +23,7 @@
 #include <new>
 
 #include "common.hpp"
+#include "lds_shape.hpp"
 
 namespace aboria {
 
@@ -913,6 +914,7 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
 // loads are all it waits for: 1000 particles in 2-d 5.3 us, where cell ids and a bucket
 // that looked its bounds up took 1.9 and 7.2.
 constexpr int kSmallThreads = 1024;
+static_assert(kSmallThreads / kWave == 16, "small_build_lds counts 16 waves");
 
 template <typename T, int D, bool BATCH>
 __global__ __launch_bounds__(kSmallThreads) void k_small_cells(const T* __restrict__ x, uint32_t n,
@@ -1307,7 +1309,7 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
         constexpr int NT = decltype(nt_tag)::value, KPT = decltype(kpt_tag)::value;
         constexpr bool ROWS = decltype(rows_tag)::value;
         const size_t key_bytes = ROWS ? row_bytes : (pay ? 3 : 2) * sizeof(uint32_t);
-        const size_t cnt_bytes = (2 + NT / kWave) * (size_t)R * sizeof(uint32_t);
+        const size_t cnt_bytes = bucket_counts(c->low_bits, NT);
         // room for the bucket, and what is left of a CU's LDS when as many buckets share it
         // as would at that size (at most four)
         const size_t need = std::max(cnt_bytes, (size_t)want * key_bytes);
@@ -1325,7 +1327,7 @@ aboria_status launch_build_radix_ipt(aboria_ctx* ctx, aboria_cells* c, const voi
         launch(integral_constant<int, 512>(), integral_constant<int, 2>(), Rows());
     else if (want <= 2048.0 && 2048 * row_bytes <= lds_max)
         launch(integral_constant<int, 512>(), integral_constant<int, 4>(), Rows());
-    else if (want <= 4096.0)
+    else if (want <= 4096.0 || bucket_counts(c->low_bits, 1024) > lds_max)
         launch(integral_constant<int, 512>(), integral_constant<int, 8>(), Late());
     else
         launch(integral_constant<int, 1024>(), integral_constant<int, 10>(), Late());
@@ -1361,7 +1363,7 @@ aboria_status launch_build_single(aboria_ctx* ctx, aboria_cells* c, const void* 
 template <typename T, int D>
 aboria_status launch_build_small(aboria_ctx* ctx, aboria_cells* c, const void* x) {
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-    const size_t lds = (size_t)(kSmallThreads / kWave) * sizeof(uint32_t) << c->low_bits;
+    const size_t lds = small_build_lds(c->low_bits);
 #define SC(B)                                                                                                      \
     hipLaunchKernelGGL((k_small_cells<T, D, B>), dim3(1), dim3(kSmallThreads), lds, ctx->stream, (const T*)x,      \
                        (uint32_t)c->n, sp, c->sys_part_dev, c->nsys, c->low_bits, (uint32_t)c->ncells, (T*)c->xs,  \
@@ -1377,7 +1379,8 @@ template <typename T, int D>
 aboria_status launch_build(aboria_ctx* ctx, aboria_cells* c, const void* x) {
     if (c->ncells == c->nsys) return launch_build_single<T, D>(ctx, c, x);  // one cell per system: no sort
     // one bucket of everything (2^low_bits >= ncells), small enough for one workgroup
-    if (ctx->build_strategy == ABORIA_BUILD_RADIX && c->passes == 0 && c->n > 0 && c->n <= 2 * kSmallThreads)
+    if (ctx->build_strategy == ABORIA_BUILD_RADIX && c->passes == 0 && c->n > 0 && c->n <= 2 * kSmallThreads &&
+        small_build_fits(c->low_bits, lds_limit(ctx)))
         return launch_build_small<T, D>(ctx, c, x);
     return ctx->build_strategy == ABORIA_BUILD_RADIX ? launch_build_radix<T, D>(ctx, c, x)
                                                      : launch_build_counting<T, D>(ctx, c, x);

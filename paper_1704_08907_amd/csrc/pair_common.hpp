@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "lds_shape.hpp"
 
 namespace aboria {
 
@@ -781,18 +782,11 @@ constexpr int kSearchThreads = 64 * 9;  // most threads of a search workgroup (a
 
 // row_split: waves per 64 particles of a cell list by its size (0: a running sum).
 // (Kernels that always take one wave only look whether it is 0.)
-// search_shape: launch shape of a box-search kernel, by row_split or with a split of its
-// own, whose waves each need wave_bytes of LDS (their window) and, when split, whose
-// workgroup needs part_bytes more.
-struct SearchShape {
-    int32_t split;
-    uint32_t blocks, threads, lds;
-};
+// search_shape: launch shape of a box-search kernel by row_split, whose waves each need
+// wave_bytes of LDS (their window) and, when split, whose workgroup needs part_bytes more.
 int32_t row_split(const aboria_cells* c);
-SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, int32_t split, uint32_t wave_bytes,
-                         uint32_t part_bytes);
 inline SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, uint32_t wave_bytes, uint32_t part_bytes) {
-    return search_shape(ctx, c, row_split(c), wave_bytes, part_bytes);
+    return settle_search((uint64_t)c->n, row_split(c), [=](int32_t) { return wave_bytes; }, part_bytes, lds_limit(ctx));
 }
 
 // The dynamic LDS of a search workgroup: the waves' windows, then the row sums.

@@ -26,10 +26,6 @@ constexpr uint32_t kMaxNbrCap = 4096;
 
 constexpr uint64_t kSharedWaves = 3500;
 
-// Entries of its rows that a lane keeps in LDS before it knows their place in the list
-// (a row of the 3-d stencil has a ninth of the neighbours, three have a third).
-__host__ __device__ constexpr uint32_t stash_of(int32_t split) { return split > 3 ? 16u : 32u; }
-
 // One lane per particle, the rows read through the wave's LDS window.  With SPLIT and
 // split > 1 the rows of 64 particles are shared by that many waves, as in the sums.  A
 // wave then keeps what it finds in LDS ([entry][lane]), and writes it after the entries of
@@ -110,8 +106,8 @@ void launch_build_nbr(aboria_ctx* ctx, aboria_cells* c) {
     // computes.  One wave / shared: 3000 particles in 2-d 16.3 / 8.6 us, 20000 in 3-d 58 /
     // 19, 100003 64 / 50, 200000 in 2-d float64 27.4 / 25.9; 300007 in 2-d 33.5 / 34.6.
     const int32_t split = ((uint64_t)n + 63) / 64 <= kSharedWaves ? row_split(c) : 0;
-    const SearchShape sh = search_shape(
-        ctx, c, split, WindowBytes<T, D, 0>::value + (split > 0 ? (stash_of(split) + 1u) * 256u : 0u), 0u);
+    const SearchShape sh = settle_search(
+        n, split, [](int32_t sp) { return WindowBytes<T, D, 0>::value + stash_bytes(sp); }, 0u, lds_limit(ctx));
 #define NB(B, O, S)                                                                                             \
     hipLaunchKernelGGL((k_nbr_build<T, D, B, O, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, ctx->stream,     \
                        (const T*)c->xs, c->off, n, sp, c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, \

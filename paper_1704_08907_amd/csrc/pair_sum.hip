@@ -298,16 +298,6 @@ int32_t row_split(const aboria_cells* c) {
     return waves <= 640 ? rows : (waves <= 10000 ? 3 : 0);
 }
 
-SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, int32_t split, uint32_t wave_bytes,
-                         uint32_t part_bytes) {
-    const uint32_t waves = (uint32_t)(((uint64_t)c->n + 63) / 64);
-    // fewer waves (the same sums) where their windows would not fit a workgroup's LDS
-    if (split > 3 && (uint32_t)split * wave_bytes + part_bytes > lds_limit(ctx)) split = 3;
-    if (split > 1 && (uint32_t)split * wave_bytes + part_bytes > lds_limit(ctx)) split = 1;
-    if (split <= 1) return SearchShape{split, (waves + 3) / 4, 256, 4 * wave_bytes};
-    return SearchShape{split, waves, 64u * (uint32_t)split, (uint32_t)split * wave_bytes + part_bytes};
-}
-
 int32_t variant_count() { return kNumVariants; }
 
 const char* variant_name(int32_t v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : ""; }
