@@ -9,6 +9,7 @@
 
 #include "common.hpp"
 #include "lds_shape.hpp"
+#include "nbr_entry.hpp"
 
 namespace aboria {
 
@@ -1096,14 +1097,6 @@ __device__ __forceinline__ T group_reduce(T v) {
 // recorded neighbour lists
 // ---------------------------------------------------------------------------
 
-// An entry of a recorded list: the neighbour's slot, with the top bit set when
-// the box search reached it through a nonzero image shift, and the next one when
-// it is the first neighbour of its stencil row.  (Lists of more than 2^30 slots
-// are not replayed.)
-constexpr uint32_t kNbrShift = 0x80000000u;
-constexpr uint32_t kNbrRow = 0x40000000u;
-constexpr uint32_t kNbrSlot = 0x3FFFFFFFu;
-
 // Displacement and squared distance of a recorded pair, bit for bit those of
 // the box search: dx_k = fl(t_k + s_k) with t_k = fl(x_jk - x_ik).  For a
 // flagged entry s_k is recovered as the minimum image of t_k in each periodic
@@ -1149,6 +1142,7 @@ __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __re
     constexpr uint32_t U = sizeof(T) == 4 && AP < 3 ? 4u : 2u;
     // rows of the list past a lane's count hold anything: it takes its own slot there
     uint32_t e[U];
+    const uint32_t row_flag = nbr_row_flag(n);
     if (cnt == 0u) return;
 #pragma unroll
     for (uint32_t u = 0; u < U; ++u) e[u] = (nbr + (size_t)min(u, cap - 1u) * n)[s];
@@ -1160,7 +1154,7 @@ __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __re
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             e[u] = k + u < cnt ? e[u] : s;
-            const uint32_t j = e[u] & kNbrSlot;
+            const uint32_t j = nbr_slot(e[u], row_flag);
             x[u] = reinterpret_cast<const VecN<T, PITCH>*>(xs)[j];
             if constexpr (NAUX > 0) g[u] = reinterpret_cast<const VecN<T, AP>*>(aux)[j];
             aj[u] = NA > 0 ? a_s[j] : T(0);
@@ -1182,7 +1176,7 @@ __device__ __forceinline__ void replay_list(const SysParams<T>& P, const T* __re
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             if (k + u < cnt) {
-                row_if((e[u] & kNbrRow) != 0u);
+                row_if((e[u] & row_flag) != 0u);
                 visit(dx[u], d2[u], g[u].v, aj[u]);
             }
             e[u] = next[u];

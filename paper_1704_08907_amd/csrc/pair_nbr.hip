@@ -6,8 +6,8 @@
 //
 // Layout: entry k of slot s at nbr[k * n + s] (a wave reads 64 consecutive
 // words per entry), the neighbour's slot with kNbrShift set when the search
-// reached it through an image shift and kNbrRow on the first neighbour of a
-// stencil row, in box-search order, so a replayed sum adds its summands, row by
+// reached it through an image shift and the row flag (nbr_entry.hpp) on the first neighbour
+// of a stencil row, in box-search order, so a replayed sum adds its summands, row by
 // row, in the same order as the search kernels.  nbr_count[s] is
 // the slot's full neighbour count; a slot with more neighbours than the list
 // holds is summed by the box search when replayed.
@@ -51,17 +51,18 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_nbr_build(cons
     SysParams<T> P;
     T xi[D];
     uint32_t cnt = 0;
-    uint32_t row = kNbrRow;  // set until the row's first neighbour
+    const uint32_t row_flag = nbr_row_flag(n);
+    uint32_t row = row_flag;  // set until the row's first neighbour
     auto search = [&](auto&& put) {
         cnt = 0;
-        row = kNbrRow;
+        row = row_flag;
         auto visit = [&](uint32_t j, const T*, T, bool shifted) {
             put(cnt, j | (shifted ? kNbrShift : 0u) | row);
             row = 0u;
             ++cnt;
         };
         neighbour_loop_staged<T, D, OFF32, 0>(P, xs, (const T*)nullptr, off, n, xi, visit,
-                                              [&](int32_t) { row = kNbrRow; }, w.range, wave_window(lds, w.wave, WB));
+                                              [&](int32_t) { row = row_flag; }, w.range, wave_window(lds, w.wave, WB));
     };
     if (s < n) {
         if (s == 0 && w.wave == 0) gen[1] = gen[0];  // the list now belongs to the latest build

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
     T* const acca = accx + (NA ? D : 0);
     const T r = P.r;
     const uint32_t cnt = nbr_count[s];
-    if (gen[0] == gen[1] && cnt <= cap && n <= kNbrSlot + 1u) {
+    if (gen[0] == gen[1] && cnt <= cap) {
         constexpr int NG = OP == ABORIA_OP_COUNT ? 0 : NY;  // the count needs no gradient
         replay_list<T, D, NG, NA>(
             P, xs, gy_s, a_s, nbr, cap, n, s, cnt, xi,

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void k_nbr_fwd(const T* __restrict__ xs, const
     T* const acc = sums.acc;
     const T r = P.r;
     const uint32_t cnt = nbr_count[s];
-    if (gen[0] == gen[1] && cnt <= cap && n <= kNbrSlot + 1u) {
+    if (gen[0] == gen[1] && cnt <= cap) {
         replay_list<T, D, 0, OpShape<OP, D>::NA>(
             P, xs, (const T*)nullptr, a_s, nbr, cap, n, s, cnt, xi,
             [&](const T* dx, T d2, const T*, T aj) { Op::fwd(q, r, dx, d2, ai, aj, acc); },
