@@ -723,8 +723,7 @@ struct RowSums {
             acc[k] = T(0);
         }
     }
-    // row_done() where the lane's new_row is set, without a branch (by_rows false: the
-    // caller clears new_row)
+    // row_done() where the lane's new_row is set, without a branch
     __device__ __forceinline__ void row_done_if(bool new_row) {
 #pragma unroll
         for (int k = 0; k < NV; ++k) {

@@ -8,7 +8,9 @@
 
 namespace aboria {
 
-template <typename T, int D, int OP, bool BATCH>
+// ROWS: the sums go by rows (row_split); a template flag, since the rows' sums cost
+// registers: carried along unused they took a wave per SIMD in float64.
+template <typename T, int D, int OP, bool BATCH, bool ROWS>
 __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                  const uint32_t* __restrict__ perm, uint32_t n,
                                                  const SysParams<T>* __restrict__ sp,
@@ -17,7 +19,7 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
                                                  const uint32_t* __restrict__ nbr_count, uint32_t cap,
                                                  const uint32_t* __restrict__ gen, const T* __restrict__ a_s,
                                                  const T* __restrict__ gy_s, OpArgs<T> q, T* __restrict__ gx,
-                                                 T* __restrict__ ga, bool by_rows) {
+                                                 T* __restrict__ ga) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
@@ -31,7 +33,7 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
     T gyi[NY];
     load_gy<T, NY>(gy_s, s, gyi);
     constexpr int NA = OpShape<OP, D>::NA;
-    RowSums<T, D + NA> sums(by_rows);
+    RowSums<T, D + NA> sums(ROWS);
     T* const accx = sums.acc;
     T* const acca = accx + (NA ? D : 0);
     const T r = P.r;
@@ -41,7 +43,9 @@ __global__ __launch_bounds__(256) void k_nbr_bwd(const T* __restrict__ xs, const
         replay_list<T, D, NG, NA>(
             P, xs, gy_s, a_s, nbr, cap, n, s, cnt, xi,
             [&](const T* dx, T d2, const T* gyj, T aj) { Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca); },
-            [&](bool first) { sums.row_done_if(first & by_rows); });
+            [&](bool first) {
+                if constexpr (ROWS) sums.row_done_if(first);
+            });
     } else {
         auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
             const T aj = NA ? a_s[j] : T(0);
@@ -62,10 +66,13 @@ template <typename T, int D, int OP, bool BATCH>
 void launch_nbr_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
                     T* ga) {
     const uint32_t n = (uint32_t)c->n;
-    hipLaunchKernelGGL((k_nbr_bwd<T, D, OP, BATCH>), dim3((n + 255) / 256), dim3(256), 0, ctx->stream,
-                       (const T*)c->xs, c->off, c->perm, n, reinterpret_cast<const SysParams<T>*>(c->params_dev),
-                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen, a_s, gy_s, q, gx, ga,
-                       row_split(c) > 0);
+#define LN(R)                                                                                                       \
+    hipLaunchKernelGGL((k_nbr_bwd<T, D, OP, BATCH, R>), dim3((n + 255) / 256), dim3(256), 0, ctx->stream,            \
+                       (const T*)c->xs, c->off, c->perm, n, reinterpret_cast<const SysParams<T>*>(c->params_dev),   \
+                       c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, c->gen, a_s, gy_s, q, gx, ga)
+    if (row_split(c) > 0) LN((D > 1));
+    else LN(false);
+#undef LN
 }
 
 #define ABORIA_INST(T, D, OP, BATCH)                                                                         \
