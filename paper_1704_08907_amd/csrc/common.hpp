@@ -166,7 +166,7 @@ struct aboria_cells {
     uint32_t* gen = nullptr;
     // recorded neighbour list (aboria_build_neighbours)
     uint32_t* nbr = nullptr;        // [nbr_cap][n] slot of each accepted neighbour, box-search order
-    uint32_t* nbr_count = nullptr;  // [n] neighbours of each slot (may exceed nbr_cap)
+    uint32_t* nbr_count = nullptr;  // [n] neighbours of each slot (kNbrOverflow: more than nbr_cap)
     int64_t nbr_alloc = 0;          // entries per slot allocated in nbr (fixed once allocated)
     uint32_t nbr_cap = 0;           // entries per slot of the latest recording
     bool nbr_recorded = false;      // a list has been recorded on these cells

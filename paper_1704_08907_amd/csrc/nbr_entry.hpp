@@ -10,6 +10,7 @@
 namespace aboria {
 
 constexpr uint32_t kNbrShift = 0x80000000u;
+constexpr uint32_t kNbrOverflow = 0xFFFFFFFFu;  // a count above every capacity
 
 // The row flag of a list of n slots (0: none), and the slot of an entry of such a list.
 constexpr uint32_t nbr_row_flag(uint32_t n) { return n <= 0x40000000u ? 0x40000000u : 0u; }

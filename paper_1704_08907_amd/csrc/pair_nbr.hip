@@ -9,8 +9,9 @@
 // reached it through an image shift and the row flag (nbr_entry.hpp) on the first neighbour
 // of a stencil row, in box-search order, so a replayed sum adds its summands, row by
 // row, in the same order as the search kernels.  nbr_count[s] is
-// the slot's full neighbour count; a slot with more neighbours than the list
-// holds is summed by the box search when replayed.
+// the slot's neighbour count, or kNbrOverflow where the list does not hold them all: such a
+// slot is summed by the box search when replayed, also by a graph that was captured when
+// the list held more.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,13 +25,11 @@ namespace {
 
 constexpr uint32_t kMaxNbrCap = 4096;
 
-constexpr uint64_t kSharedWaves = 3500;
-
 // One lane per particle, the rows read through the wave's LDS window.  With SPLIT and
 // split > 1 the rows of 64 particles are shared by that many waves, as in the sums.  A
 // wave then keeps what it finds in LDS ([entry][lane]), and writes it after the entries of
 // the waves before it; a wave with a lane of more entries than it can keep searches its
-// rows once more for the rest.
+// rows once more for the rest, unless the list has no room for that particle's anyway.
 template <typename T, int D, bool BATCH, bool OFF32, bool SPLIT>
 __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_nbr_build(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                    uint32_t n, const SysParams<T>* __restrict__ sp,
@@ -80,33 +79,73 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_nbr_build(cons
                     p += n;
                 }
             });
-            nbr_count[s] = cnt;
+            nbr_count[s] = cnt <= cap ? cnt : kNbrOverflow;
         }
     }
     if (!shared_rows) return;
     counts[(uint32_t)w.wave * 64u] = cnt;
     __syncthreads();
     if (s >= n) return;
-    uint32_t base = 0;
-    for (int32_t q = 0; q < w.wave; ++q) base += counts[(uint32_t)q * 64u];
+    uint32_t base = 0, total = 0;
+    for (int32_t q = 0; q < split; ++q) {
+        const uint32_t found = counts[(uint32_t)q * 64u];
+        base += q < w.wave ? found : 0u;
+        total += found;
+    }
     const uint32_t mine = cnt;
-    for (uint32_t k = 0; k < min(mine, kept); ++k)
-        if (base + k < cap) nbr[(size_t)(base + k) * n + s] = stash[k * 64u];
-    if (w.wave == split - 1) nbr_count[s] = base + mine;
-    if (__ballot(mine > kept) != 0ull)
+    const bool listed = total <= cap;
+    if (w.wave == 0) nbr_count[s] = listed ? total : kNbrOverflow;
+    if (listed)
+        for (uint32_t k = 0; k < min(mine, kept); ++k) nbr[(size_t)(base + k) * n + s] = stash[k * 64u];
+    if (__ballot(listed && mine > kept) != 0ull)
         search([&](uint32_t k, uint32_t e) {
-            if (k >= kept && base + k < cap) nbr[(size_t)(base + k) * n + s] = e;
+            if (k >= kept && listed) nbr[(size_t)(base + k) * n + s] = e;
         });
+}
+
+// Mean neighbour count of the densest system: its density times the volume of the cutoff
+// ball.
+double mean_neighbours(const aboria_cells* c) {
+    double mu = 0.0;
+    for (int32_t b = 0; b < c->nsys; ++b) {
+        const aboria_box& bx = c->boxes[(size_t)b];
+        const double nb = (double)(c->sys_off[(size_t)b + 1] - c->sys_off[(size_t)b]);
+        double vol = 1.0;
+        for (int k = 0; k < c->d; ++k) vol *= bx.hi[k] - bx.lo[k];
+        const double r = bx.cutoff;
+        const double ball = c->d == 1 ? 2.0 * r : (c->d == 2 ? M_PI * r * r : 4.0 / 3.0 * M_PI * r * r * r);
+        if (vol > 0.0) mu = std::max(mu, nb / vol * ball);
+    }
+    return mu;
+}
+
+// Entries per particle: the mean neighbour count mu of a uniform system plus six standard
+// deviations of a Poisson count and a margin.
+uint32_t auto_capacity(const aboria_cells* c) {
+    const double mu = mean_neighbours(c);
+    const double want = std::ceil(mu + 6.0 * std::sqrt(mu) + 8.0);
+    uint32_t cap = (uint32_t)std::min<double>(want, (double)kMaxNbrCap);
+    cap = (cap + 7u) & ~7u;
+    return std::max<uint32_t>(cap, 8u);
+}
+
+// Most waves of particles whose rows the recording shares: where the search waits more than
+// it computes.  One wave / shared, us: 3000 particles in 2-d 16.3 / 8.6, 20000 in 3-d 58 /
+// 19, 100003 64 / 50; 224000 in 2-d with 12 neighbours 23.5 / 21.4, with 100 233 / 148;
+// 300007 in 2-d 33.5 / 34.6.  Of many neighbours in 3-d three waves find more than they
+// keep and search twice (48 neighbours, 100003 particles 93 / 93, 150000 96 / 107, in
+// float64 103 / 134; 224000 113 / 146); of few there is little to wait for (5 neighbours,
+// 224000 in 2-d 13.0 / 15.9, in 3-d 29.5 / 31.9).
+uint64_t shared_waves(const aboria_cells* c) {
+    const double mu = mean_neighbours(c);
+    return c->d == 3 && mu > 40.0 ? 1600 : (mu < 10.0 ? 2400 : 3500);
 }
 
 template <typename T, int D>
 void launch_build_nbr(aboria_ctx* ctx, aboria_cells* c) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-    // Shared rows on lists of up to kSharedWaves waves, where the search waits more than it
-    // computes.  One wave / shared: 3000 particles in 2-d 16.3 / 8.6 us, 20000 in 3-d 58 /
-    // 19, 100003 64 / 50, 200000 in 2-d float64 27.4 / 25.9; 300007 in 2-d 33.5 / 34.6.
-    const int32_t split = ((uint64_t)n + 63) / 64 <= kSharedWaves ? row_split(c) : 0;
+    const int32_t split = ((uint64_t)n + 63) / 64 <= shared_waves(c) ? row_split(c) : 0;
     const SearchShape sh = settle_search(
         n, split, [](int32_t sp) { return WindowBytes<T, D, 0>::value + stash_bytes(sp); }, 0u, lds_limit(ctx));
 #define NB(B, O, S)                                                                                             \
@@ -120,26 +159,6 @@ void launch_build_nbr(aboria_ctx* ctx, aboria_cells* c) {
         if (sh.split > 0) NB(true, true, (D > 1)); else if (o32) NB(true, true, false); else NB(true, false, false);
     }
 #undef NB
-}
-
-// Entries per particle from the densest system: the mean neighbour count mu
-// of a uniform system (its density times the volume of the cutoff ball) plus
-// six standard deviations of a Poisson count and a margin.
-uint32_t auto_capacity(const aboria_cells* c) {
-    double mu = 0.0;
-    for (int32_t b = 0; b < c->nsys; ++b) {
-        const aboria_box& bx = c->boxes[(size_t)b];
-        const double nb = (double)(c->sys_off[(size_t)b + 1] - c->sys_off[(size_t)b]);
-        double vol = 1.0;
-        for (int k = 0; k < c->d; ++k) vol *= bx.hi[k] - bx.lo[k];
-        const double r = bx.cutoff;
-        const double ball = c->d == 1 ? 2.0 * r : (c->d == 2 ? M_PI * r * r : 4.0 / 3.0 * M_PI * r * r * r);
-        if (vol > 0.0) mu = std::max(mu, nb / vol * ball);
-    }
-    const double want = std::ceil(mu + 6.0 * std::sqrt(mu) + 8.0);
-    uint32_t cap = (uint32_t)std::min<double>(want, (double)kMaxNbrCap);
-    cap = (cap + 7u) & ~7u;
-    return std::max<uint32_t>(cap, 8u);
 }
 
 }  // namespace
