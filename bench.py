@@ -118,7 +118,7 @@ def profile_names(variant_name, direction):
     elif "accepted-pair bit masks" in variant_name:
         k = ["k_lane_mask<float, 3, 1, false, true, %d, false>" % (0 if direction == "fwd" else 1)]
     elif "flattened" in variant_name:
-        k = ["k_flat<float, 3, 1, false, true, %d, false>" % (0 if direction == "fwd" else 1)]
+        k = ["k_flat<float, 3, 1, false, true, %d>" % (0 if direction == "fwd" else 1)]
     elif direction == "fwd":
         k = ["k_lane_fwd<float, 3, 1, false, true, false>"]
     else:

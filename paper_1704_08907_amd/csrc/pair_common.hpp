@@ -803,15 +803,12 @@ __device__ __forceinline__ char* part_lds(char* lds, uint32_t wave_bytes) {
 
 // Per-lane slot ranges of the flattened search, in LDS: entry k of lane t at
 // [k][t] (consecutive lanes in consecutive banks).  code packs the image shift
-// of the range, two bits per dimension (0: none, 1: -L, 2: +L), and kFlatNewRow
-// where the range is the first one of its row.
+// of the range, two bits per dimension (0: none, 1: -L, 2: +L).
 template <int CAP, int BLOCK>
 struct FlatRanges {
     uint2 range[CAP][BLOCK];
     uint8_t code[CAP][BLOCK];
 };
-
-constexpr uint32_t kFlatNewRow = 0x40u;
 
 template <typename T, int D>
 __device__ __forceinline__ void decode_shift(const SysParams<T>& P, uint32_t code, T* sh) {
@@ -846,13 +843,11 @@ __device__ __forceinline__ T gap2(const SysParams<T>& P, int k, int32_t o, T fr)
 // candidates the predicate rejects).  A lane uses its own LDS column only, so
 // no barrier is needed and lanes past the end may simply not call it.  t_self
 // is the lane's own slot (< n), the target of loads issued past its last
-// candidate.  With ROWS, row_done() is called between the candidates of one row and the next
-// (the flag it follows costs 4 to 7 % of the walk).
-template <typename T, int D, int CAP, int BLOCK, bool OFF32, bool ROWS, typename Visit, typename RowDone>
+// candidate.  It forms running sums only: lists that sum by rows take the row search.
+template <typename T, int D, int CAP, int BLOCK, bool OFF32, typename Visit>
 __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __restrict__ xs,
                                           const uint32_t* __restrict__ off, uint32_t n, const T* xi,
-                                          uint32_t t_self, FlatRanges<CAP, BLOCK>& fr_lds, Visit&& visit,
-                                          RowDone&& row_done) {
+                                          uint32_t t_self, FlatRanges<CAP, BLOCK>& fr_lds, Visit&& visit) {
     constexpr int PITCH = Pitch<D>::value;
     const uint32_t t = threadIdx.x;
     int32_t c[3] = {0, 0, 0};
@@ -881,21 +876,18 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
         // ---- list up to CAP ranges ----
         int kd = 0;
         bool any_shift = false;
-        uint32_t new_row = 0u;
         auto put = [&](uint32_t ca, uint32_t cb, uint32_t code) {
             const uint32_t j0 = off[ca];
             const uint32_t j1 = min(off[cb + 1], n);
             if (j1 > j0) {
                 fr_lds.range[kd][t] = make_uint2(j0, j1);
-                fr_lds.code[kd][t] = (uint8_t)(code | new_row);
+                fr_lds.code[kd][t] = (uint8_t)code;
                 any_shift |= code != 0u;
-                new_row = 0u;
                 ++kd;
             }
         };
         while (rows_left && kd + pmax <= CAP) {
             const int32_t ry = dy, rz = dz;
-            new_row = ROWS ? kFlatNewRow : 0u;
             if (++dy > yr) {
                 dy = -yr;
                 if (++dz > zr) rows_left = false;
@@ -944,16 +936,13 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
             uint2 ndp = fr_lds.range[0][t];
             uint32_t ndc = (uint32_t)fr_lds.code[0][t];
             uint32_t j = 0u, e = 0u;
-            bool nr = false;  // the slot just stepped to is the first of its row
             bool alive = true;
             T cs[3] = {T(0), T(0), T(0)};  // shift of the cursor's range
             // the slot of the lane's next candidate (its own slot once it has none)
             auto step = [&]() -> uint32_t {
                 ++j;
-                nr = false;
                 if (j >= e) {
                     if (kr < (uint32_t)kd) {
-                        if (ROWS) nr = (ndc & kFlatNewRow) != 0u;
                         j = ndp.x;
                         e = ndp.y;
                         if (SHIFT) decode_shift<T, D>(P, ndc, cs);
@@ -969,8 +958,7 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
             };
             // evaluated on every lane (an idle lane tests its own row, which the
             // predicate rejects) so that the wait for the row is never skipped
-            auto test = [&](const VecN<T, PITCH>& xj, uint32_t jj, const T* sh, bool valid, bool first) {
-                if (ROWS && first) row_done();
+            auto test = [&](const VecN<T, PITCH>& xj, uint32_t jj, const T* sh, bool valid) {
                 T dx[D], d2;
                 const bool acc = pair_test<T, D, SHIFT>(xj.v, xi, sh, r2, dx, &d2);
                 if (acc & valid) {
@@ -984,25 +972,24 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
             };
             T sa[3], sb[3];
             uint32_t ja = step();
-            bool va = alive, fa = nr;
+            bool va = alive;
 #pragma unroll
             for (int k = 0; k < 3; ++k) sa[k] = cs[k];
             VecN<T, PITCH> A = load_row<T, PITCH, OFF32>(xs, ja);
             for (;;) {
                 const uint32_t jb = step();
-                const bool vb = alive, fb = nr;
+                const bool vb = alive;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) sb[k] = cs[k];
                 const VecN<T, PITCH> B = load_row<T, PITCH, OFF32>(xs, jb);
-                test(A, ja, sa, va, fa);
+                test(A, ja, sa, va);
                 if (__ballot(vb) == 0ull) break;
                 ja = step();
                 va = alive;
-                fa = nr;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) sa[k] = cs[k];
                 A = load_row<T, PITCH, OFF32>(xs, ja);
-                test(B, jb, sb, vb, fb);
+                test(B, jb, sb, vb);
                 if (__ballot(va) == 0ull) break;
             }
         };

@@ -12,7 +12,7 @@ constexpr int kFlatCap = 8;  // ranges a lane lists per round (>= 2 kMaxReach + 
 
 enum FlatMode { kFlatFwd = 0, kFlatBwd = 1, kFlatFused = 2 };
 
-template <typename T, int D, int OP, bool BATCH, bool OFF32, int MODE, bool ROWS>
+template <typename T, int D, int OP, bool BATCH, bool OFF32, int MODE>
 __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, const uint32_t* __restrict__ off,
                                                      const uint32_t* __restrict__ perm, uint32_t n,
                                                      const SysParams<T>* __restrict__ sp,
@@ -36,10 +36,11 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
     T gyi[NY];
     if (BWD) load_gy<T, NY, OFF32>(gy_s, s, gyi);
     constexpr int NA = OpShape<OP, D>::NA;
-    RowSums<T, NY + D + NA> sums(ROWS);
-    T* const acc = sums.acc;  // y, gx, ga
-    T* const accx = acc + NY;
-    T* const acca = accx + (NA ? D : 0);
+    T acc[NY], accx[D], acca[1] = {T(0)};
+#pragma unroll
+    for (int k = 0; k < NY; ++k) acc[k] = T(0);
+#pragma unroll
+    for (int k = 0; k < D; ++k) accx[k] = T(0);
     const T r = P.r;
     auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
         const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
@@ -50,17 +51,16 @@ __global__ __launch_bounds__(kFlatBlock) void k_flat(const T* __restrict__ xs, c
             Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
         }
     };
-    flat_loop<T, D, kFlatCap, kFlatBlock, OFF32, ROWS>(P, xs, off, n, xi, s, ranges, visit, [&]() { sums.row_done(); });
-    sums.last();
+    flat_loop<T, D, kFlatCap, kFlatBlock, OFF32>(P, xs, off, n, xi, s, ranges, visit);
     const uint32_t o = perm[s];
     if (FWD) {
 #pragma unroll
-        for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = sums.tot[k];
+        for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = acc[k];
     }
     if (BWD) {
 #pragma unroll
-        for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = sums.tot[NY + k];
-        if (NA && ga) ga[o] = sums.tot[NY + D + NA - 1];
+        for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = accx[k];
+        if (NA && ga) ga[o] = acca[0];
     }
 }
 
@@ -70,13 +70,11 @@ void launch_flat(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, con
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const dim3 grid((n + kFlatBlock - 1) / kFlatBlock);
-#define FL(O, R)                                                                                               \
-    hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, O, MODE, R>), grid, dim3(kFlatBlock), 0, ctx->stream,           \
-                       (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga)
-    // (sums go by rows below a size whose offsets are far below 32 bits)
-    if (row_split(c) > 0) FL(true, (D > 1));
-    else if (off32_rows<T>(n)) FL(true, false);
-    else FL(false, false);
+#define FL(O)                                                                                                  \
+    hipLaunchKernelGGL((k_flat<T, D, OP, BATCH, O, MODE>), grid, dim3(kFlatBlock), 0, ctx->stream, (const T*)c->xs, \
+                       c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, y, gx, ga)
+    if (off32_rows<T>(n)) FL(true);
+    else FL(false);
 #undef FL
 }
 
