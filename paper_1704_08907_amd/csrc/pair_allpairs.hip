@@ -13,14 +13,13 @@ namespace aboria {
 // tens of thousands of lanes even for a few hundred particles): lane l of a
 // group takes slots l, l + G, ... of the system; the group's partial sums are
 // combined by a fixed butterfly and its first lane writes the result.
-template <typename T, int D, int OP, bool BATCH, int G>
+template <typename T, int D, int OP, bool BATCH, int G, bool DIRECT>
 __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const uint32_t* __restrict__ perm,
                                                  uint32_t n, const SysParams<T>* __restrict__ sp,
                                                  const uint32_t* __restrict__ sys_part, int nsys,
                                                  const T* __restrict__ a_s, OpArgs<T> q, T* __restrict__ y) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
-    constexpr bool DIRECT = G == 64;  // (all_direct)
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x / G);
     const uint32_t s = first + threadIdx.x / G;
     const uint32_t lane = threadIdx.x % G;
@@ -36,10 +35,14 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = T(0);
     const T r = P.r;
-    auto visit = [&](const T* dx, T d2, const T*, T aj) { Op::fwd(q, r, dx, d2, ai, aj, acc); };
+    constexpr int NA = OpShape<OP, D>::NA;
+    auto visit = [&](uint32_t j, const T* dx, T d2, const T*, T aj) {
+        if constexpr (NA > 0 && !DIRECT) aj = a_s[j];
+        Op::fwd(q, r, dx, d2, ai, aj, acc);
+    };
     if (live)
-        allpairs_loop<T, D, 0, OpShape<OP, D>::NA, DIRECT>(P, xs, (const T*)nullptr, a_s, perm, P.part_base + lane,
-                                                           P.part_end, G, xi, visit);
+        allpairs_loop<T, D, 0, NA, DIRECT>(P, xs, (const T*)nullptr, a_s, perm, P.part_base + lane, P.part_end, G, xi,
+                                           visit);
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = group_reduce<G>(acc[k]);
     if (!live || lane != 0) return;
@@ -48,7 +51,7 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
     for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = acc[k];
 }
 
-template <typename T, int D, int OP, bool BATCH, int G>
+template <typename T, int D, int OP, bool BATCH, int G, bool DIRECT>
 __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const uint32_t* __restrict__ perm,
                                                  uint32_t n, const SysParams<T>* __restrict__ sp,
                                                  const uint32_t* __restrict__ sys_part, int nsys,
@@ -56,7 +59,6 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
                                                  OpArgs<T> q, T* __restrict__ gx, T* __restrict__ ga) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
-    constexpr bool DIRECT = G == 64;  // (all_direct)
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x / G);
     const uint32_t s = first + threadIdx.x / G;
     const uint32_t lane = threadIdx.x % G;
@@ -79,7 +81,16 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
 #pragma unroll
     for (int k = 0; k < D; ++k) accx[k] = T(0);
     const T r = P.r;
-    auto visit = [&](const T* dx, T d2, const T* gyj, T aj) { Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca); };
+    auto visit = [&](uint32_t j, const T* dx, T d2, const T* gyj, T aj) {
+        if constexpr (DIRECT) {
+            Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
+        } else {
+            if constexpr (OpShape<OP, D>::NA > 0) aj = a_s[j];
+            T g[NY];
+            load_gy<T, NY>(gy_s, j, g);
+            Op::bwd(q, r, dx, d2, ai, aj, gyi, g, accx, acca);
+        }
+    };
     if (live)
         allpairs_loop<T, D, NY, OpShape<OP, D>::NA, DIRECT>(P, xs, gy_s, a_s, perm, P.part_base + lane, P.part_end, G,
                                                             xi, visit);
@@ -94,44 +105,50 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
 }
 
 template <typename T, int D, int OP, bool BATCH>
-void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y) {
+void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, bool direct) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const int G = all_group(n);
     const dim3 grid((uint32_t)(((uint64_t)n * G + 255) / 256));
-#define L(GG) hipLaunchKernelGGL((k_all_fwd<T, D, OP, BATCH, GG>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
+#define L(GG, DI) hipLaunchKernelGGL((k_all_fwd<T, D, OP, BATCH, GG, DI>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
                                  c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, q, y)
     switch (G) {
-        case 64: L(64); break;
-        case 16: L(16); break;
-        case 4: L(4); break;
-        default: L(1); break;
+        case 64:
+            if (direct) L(64, true);
+            else L(64, false);
+            break;
+        case 16: L(16, false); break;
+        case 4: L(4, false); break;
+        default: L(1, false); break;
     }
 #undef L
 }
 
 template <typename T, int D, int OP, bool BATCH>
 void launch_all_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
-                    T* ga) {
+                    T* ga, bool direct) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const int G = all_group(n);
     const dim3 grid((uint32_t)(((uint64_t)n * G + 255) / 256));
-#define L(GG) hipLaunchKernelGGL((k_all_bwd<T, D, OP, BATCH, GG>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
+#define L(GG, DI) hipLaunchKernelGGL((k_all_bwd<T, D, OP, BATCH, GG, DI>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
                                  c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, gx, ga)
     switch (G) {
-        case 64: L(64); break;
-        case 16: L(16); break;
-        case 4: L(4); break;
-        default: L(1); break;
+        case 64:
+            if (direct) L(64, true);
+            else L(64, false);
+            break;
+        case 16: L(16, false); break;
+        case 4: L(4, false); break;
+        default: L(1, false); break;
     }
 #undef L
 }
 
 #define ABORIA_INST(T, D, OP, BATCH)                                                                                 \
-    template void launch_all_fwd<T, D, OP, BATCH>(aboria_ctx*, const aboria_cells*, const OpArgs<T>&, const T*, T*); \
+    template void launch_all_fwd<T, D, OP, BATCH>(aboria_ctx*, const aboria_cells*, const OpArgs<T>&, const T*, T*, bool); \
     template void launch_all_bwd<T, D, OP, BATCH>(aboria_ctx*, const aboria_cells*, const OpArgs<T>&, const T*,      \
-                                                  const T*, T*, T*);
+                                                  const T*, T*, T*, bool);
 ABORIA_FOR_EACH_PAIR_INSTANCE(ABORIA_INST)
 #undef ABORIA_INST
 

@@ -1002,30 +1002,30 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
 // all pairs of a small system (the brute-force fallback for small N)
 // ---------------------------------------------------------------------------
 
-// visit(dx, d2, gyj, aj) for every slot j in [j0, j1) that is a neighbour of xi,
+// visit(j, dx, d2, gyj, aj) for every slot j in [j0, j1) that is a neighbour of xi,
 // testing each particle once at its minimum image: in each periodic dimension s_k =
 // -L if t_k > L/2, +L if t_k < -L/2, else 0, with t_k = fl(x_jk - x_ik).  For a
 // neighbour this is the shift the box search uses (the side is at least twice the
 // guarded cutoff, so only one image can be within r), so the pair set and each pair's
 // dx are those of the box search; a non-neighbour is rejected at every image because
 // its nearest one is. The slots visited are j0, j0 + step, j0 + 2 step, ... below j1
-// (a group of lanes splits one particle's slots this way). Every candidate's
-// position, gradient row (NAUX, of aux) and variable (NA, of a_s) are loaded whether
-// it is accepted or not, eight candidates at once: a lane of 64 has sixteen
-// candidates of a thousand particles, and waiting for them two at a time and for each
-// accepted one's gradient again was what the kernel did (1000 particles in 2-d
-// float64, forward / adjoint: 7.2 / 7.2 us, four at once 6.2 / 6.4, eight 5.6 / 6.1).
-// With DIRECT, aux and a_s are in the caller's order (rows of NAUX elements unpadded) and
-// read through perm.
-template <typename T, int D, int NAUX, int NA, bool DIRECT, typename Visit>
+// (a group of lanes splits one particle's slots this way).  Eight candidates' positions
+// are loaded at once while more than four are left, then two: a lane of 64 has sixteen
+// candidates of a thousand particles, and waited for them two at a time (1000 particles
+// in 2-d float64, forward / adjoint: 7.2 / 7.2 us, four at once 6.2 / 6.4, eight 5.6 /
+// 6.1), but eight loads for systems of three cost more than their two rounds (20000 of
+// them, forward 7.7 / 9.2 us).  With EAGER every candidate's gradient row (NAUX, unpadded)
+// and variable (NA) come with its position, read through perm from the caller's order;
+// without, visit reads an accepted one's itself (gyj null): of 2000 particles in 3-d, with
+// 32 candidates a lane, few are accepted (float64 adjoint 19.9 against 26.5).
+template <typename T, int D, int NAUX, int NA, bool EAGER, typename Visit>
 __device__ __forceinline__ void allpairs_loop(const SysParams<T>& P, const T* __restrict__ xs,
                                               const T* __restrict__ aux, const T* __restrict__ a_s,
                                               const uint32_t* __restrict__ perm, uint32_t j0, uint32_t j1,
                                               uint32_t step, const T* xi, Visit&& visit) {
     constexpr int PITCH = Pitch<D>::value;
-    constexpr int AP = NAUX > 0 ? GyPitch<(NAUX > 0 ? NAUX : 1)>::value : 1;
+    constexpr int AP = NAUX > 0 ? NAUX : 1;
     const VecN<T, PITCH>* __restrict__ xv = reinterpret_cast<const VecN<T, PITCH>*>(xs);
-    const VecN<T, AP>* __restrict__ gv = reinterpret_cast<const VecN<T, AP>*>(aux);
     T h[D], L[D];
     bool per[D];
 #pragma unroll
@@ -1035,24 +1035,22 @@ __device__ __forceinline__ void allpairs_loop(const SysParams<T>& P, const T* __
         per[k] = P.periodic[k] != 0;
     }
     const T r2 = P.r2;
-    constexpr int U = 8;
-    for (uint32_t j = j0; j < j1; j += U * step) {
+    // the candidates j, j + step, ... below j1, U of them at most (j < j1)
+    auto round = [&](auto count_tag, uint32_t j) {
+        constexpr int U = decltype(count_tag)::value;
         VecN<T, PITCH> a[U];
-        VecN<T, AP> g[U];
-        T av[U];
+        T g[U][AP], av[U];
 #pragma unroll
         for (int e = 0; e < U; ++e) {
             const uint32_t q = min(j + e * step, j1 - 1u);
             a[e] = xv[q];
-            uint32_t p = q;
-            if constexpr (DIRECT && (NAUX > 0 || NA > 0)) p = perm[q];
-            if constexpr (NAUX > 0 && DIRECT) {
+            av[e] = T(0);
+            if constexpr (EAGER && (NAUX > 0 || NA > 0)) {
+                const uint32_t p = perm[q];
 #pragma unroll
-                for (int k = 0; k < NAUX; ++k) g[e].v[k] = aux[(size_t)p * NAUX + k];
-            } else if constexpr (NAUX > 0) {
-                g[e] = gv[q];
+                for (int k = 0; k < NAUX; ++k) g[e][k] = aux[(size_t)p * NAUX + k];
+                if constexpr (NA > 0) av[e] = a_s[p];
             }
-            av[e] = NA > 0 ? a_s[p] : T(0);
         }
 #pragma unroll
         for (int e = 0; e < U; ++e) {
@@ -1065,9 +1063,12 @@ __device__ __forceinline__ void allpairs_loop(const SysParams<T>& P, const T* __
             T d2 = dx[0] * dx[0];
             if constexpr (D >= 2) d2 = fma_t(dx[1], dx[1], d2);
             if constexpr (D >= 3) d2 = fma_t(dx[2], dx[2], d2);
-            if (d2 > T(0) && d2 < r2 && j + e * step < j1) visit(dx, d2, g[e].v, av[e]);
+            if (d2 > T(0) && d2 < r2 && j + e * step < j1) visit(j + e * step, dx, d2, EAGER ? g[e] : (const T*)nullptr, av[e]);
         }
-    }
+    };
+    uint32_t j = j0;
+    for (; j + 4u * step < j1; j += 8u * step) round(std::integral_constant<int, 8>(), j);
+    for (; j < j1; j += 2u * step) round(std::integral_constant<int, 2>(), j);
 }
 
 // Sum of v over the G lanes of a group (G a power of two dividing the wave) by a
@@ -1265,18 +1266,20 @@ inline int all_group(uint64_t n) {
     if (n < want) return 4;
     return 1;
 }
-// Below that size for a wave the all-pairs kernels read gradients and variables in the
-// caller's order, through perm: gathering them into cell order first costs a launch (1000
-// particles, 2 us and as much on the host) and saves a load per candidate of some 16 a lane.
-inline bool all_direct(uint64_t n) { return all_group(n) == 64; }
+// Below that size for a wave, and with at most 16 candidates a lane (systems of 1024), the
+// all-pairs kernels read gradients and variables in the caller's order, through perm, with
+// every candidate: gathering them into cell order first costs a launch (1000 particles, 2 us
+// and as much on the host).  Larger systems: 2048 in 2-d, float32 adjoint 12.6 gathered, 14.4
+// direct, in 3-d float64 with variables 18.3 / 26.1.
+inline bool all_direct(uint64_t n, int64_t largest) { return all_group(n) == 64 && largest <= 1024; }
 
 // Forward / adjoint over every particle of the lane's system (minimum image); a_s and
 // gy_s in cell order, or with all_direct in the caller's.
 template <typename T, int D, int OP, bool BATCH>
-void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y);
+void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, bool direct);
 template <typename T, int D, int OP, bool BATCH>
 void launch_all_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
-                    T* ga);
+                    T* ga, bool direct);
 
 #define ABORIA_FOR_EACH_PAIR_INSTANCE(X)                                                            \
     X(float, 1, 0, false) X(float, 1, 1, false) X(float, 1, 2, false)                     \

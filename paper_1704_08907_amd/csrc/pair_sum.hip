@@ -162,6 +162,11 @@ int64_t largest_system(const aboria_cells* c) {
 }
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
+// True where a sum reads its variables and gradients in the caller's order.
+bool direct_inputs(const Variant& v, const aboria_cells* c) {
+    return v.kind == 3 && all_direct((uint64_t)c->n, largest_system(c));
+}
+
 // The flattened search forms running sums.  A list that sums by rows (row_split) takes the
 // row search for it: the same bits, and there two to six times as fast (100003 particles in
 // 3-d with 30 neighbours, forward / adjoint 25 / 35 us, flattened 85 / 121; with row sums of
@@ -174,7 +179,7 @@ void launch_fwd_variant(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>&
     if (v.kind == 6) launch_mask_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else if (v.kind == 7) launch_half_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else if (takes_flat(v, c)) launch_flat<T, D, OP, BATCH, kFlatModeFwd>(ctx, c, q, a_s, nullptr, y, nullptr, nullptr);
-    else if (v.kind == 3) launch_all_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
+    else if (v.kind == 3) launch_all_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y, direct_inputs(v, c));
     else if (v.kind == 2) launch_nbr_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else launch_lane_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
 }
@@ -184,7 +189,7 @@ void launch_bwd_variant(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>&
                         T* gx, T* ga, const Variant& v) {
     if (v.kind == 6) launch_mask_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
     else if (takes_flat(v, c)) launch_flat<T, D, OP, BATCH, kFlatModeBwd>(ctx, c, q, a_s, gy_s, nullptr, gx, ga);
-    else if (v.kind == 3) launch_all_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
+    else if (v.kind == 3) launch_all_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga, direct_inputs(v, c));
     else if (v.kind == 2) launch_nbr_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
     else launch_lane_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
 }
@@ -364,7 +369,7 @@ aboria_status pair_sum_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, 
     const size_t tsz = c->dtype == ABORIA_F32 ? 4 : 8;
     if (overlaps(y, tsz * ny * c->n, a, tsz * na * c->n))
         return fail(ctx, ABORIA_ERR_INVALID_ARG, "y overlaps a");
-    const bool direct = variant_of(variant).kind == 3 && all_direct((uint64_t)c->n);
+    const bool direct = direct_inputs(variant_of(variant), c);
     if (c->dtype == ABORIA_F32) {
         OpArgs<float> q{nparams > 0 ? (float)params[0] : 0.f};
         const float *a_s, *none;
@@ -399,7 +404,7 @@ aboria_status pair_bwd_impl(aboria_ctx* ctx, const aboria_cells* c, int32_t op, 
         overlaps(ga, tsz * na * nb, gy, tsz * ny * nb) || overlaps(ga, tsz * na * nb, a, tsz * na * nb) ||
         overlaps(ga, tsz * na * nb, gx, tsz * c->d * nb))
         return fail(ctx, ABORIA_ERR_INVALID_ARG, "outputs overlap inputs");
-    const bool direct = variant_of(variant).kind == 3 && all_direct((uint64_t)c->n);
+    const bool direct = direct_inputs(variant_of(variant), c);
     if (c->dtype == ABORIA_F32) {
         OpArgs<float> q{nparams > 0 ? (float)params[0] : 0.f};
         const float *a_s, *g_s;
