@@ -75,7 +75,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_md_step(const 
     const WaveRows w = wave_rows<D, SPLIT>(split);
     const uint32_t s = w.s;
     const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
-    WaveSums<T, D, D, SPLIT> ws(split, part_lds(lds, WB));
+    WaveSums<T, D, D, SPLIT> ws(split, w.wave, part_lds(lds, WB));
     auto& sums = ws.sums;
     T xi[D];
     if (s < n) {
@@ -120,7 +120,7 @@ template <typename T, int D, int OP, bool SORTED>
 void launch_md_step(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, double dt, void* x, void* v,
                     void* x_out, void* v_out) {
     const uint32_t n = (uint32_t)c->n;
-    const SearchShape sh = search_shape(ctx, c, WindowBytes<T, D, 0>::value, WaveSums<T, D, D, true>::kPartBytes);
+    const SearchShape sh = search_shape(ctx, c, WindowBytes<T, D, 0>::value, WaveSums<T, D, D, true>::part_bytes);
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
 #define MD(B, O, S)                                                                                                 \
     hipLaunchKernelGGL((k_md_step<T, D, OP, B, O, SORTED, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, ctx->stream, \

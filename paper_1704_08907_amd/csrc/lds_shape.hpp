@@ -15,16 +15,17 @@ struct SearchShape {
 };
 
 // The shape of a search of n particles by at most `split` waves per 64, where a wave of a
-// search split s ways needs wave_bytes(s) of LDS and a split workgroup part_bytes beside:
+// search split s ways needs wave_bytes(s) of LDS and its workgroup part_bytes(s) beside:
 // fewer waves (the same sums) where theirs would not fit a workgroup's limit.
-template <typename WaveBytes>
-constexpr SearchShape settle_search(uint64_t n, int32_t split, WaveBytes wave_bytes, uint32_t part_bytes,
+template <typename WaveBytes, typename PartBytes>
+constexpr SearchShape settle_search(uint64_t n, int32_t split, WaveBytes wave_bytes, PartBytes part_bytes,
                                     uint32_t limit) {
     const uint32_t waves = (uint32_t)((n + 63) / 64);
-    if (split > 3 && (uint32_t)split * wave_bytes(split) + part_bytes > limit) split = 3;
-    if (split > 1 && (uint32_t)split * wave_bytes(split) + part_bytes > limit) split = 1;
+    auto lds = [=](int32_t s) { return (uint32_t)s * wave_bytes(s) + part_bytes(s); };
+    if (split > 3 && lds(split) > limit) split = 3;
+    if (split > 1 && lds(split) > limit) split = 1;
     if (split <= 1) return SearchShape{split, (waves + 3) / 4, 256, 4 * wave_bytes(split)};
-    return SearchShape{split, waves, 64u * (uint32_t)split, (uint32_t)split * wave_bytes(split) + part_bytes};
+    return SearchShape{split, waves, 64u * (uint32_t)split, lds(split)};
 }
 
 // Neighbour list recording with shared rows: entries of its rows that a lane keeps in LDS

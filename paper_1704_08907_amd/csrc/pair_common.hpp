@@ -737,23 +737,29 @@ struct RowSums {
     }
 };
 
-// RowSums of a search kernel; with split > 1 the rows' sums go to LDS ([row][NV][64]).
+// RowSums of a search kernel; with split > 1 the first wave adds its rows' sums up and the
+// others leave theirs in LDS ([row][NV][64]) for it: what LDS that takes decides how many
+// workgroups of three waves a CU holds (the fused kernel with variables, 3-d float32: 28 KB
+// with every row's sums, 23 so; float64 57 and 46).
 template <typename T, int D, int NV, bool SPLIT>
 struct WaveSums {
     RowSums<T, NV> sums;
-    int32_t split;
+    int32_t split, wave;
     char* part;
-    static constexpr uint32_t kPartBytes = SPLIT ? (uint32_t)kStencilRows<D> * NV * 64u * (uint32_t)sizeof(T) : 0u;
+    __host__ __device__ static constexpr uint32_t part_bytes(int32_t sp) {
+        return SPLIT && sp > 1 ? (uint32_t)(kStencilRows<D> - kStencilRows<D> / sp) * NV * 64u * (uint32_t)sizeof(T) : 0u;
+    }
 
-    __device__ __forceinline__ WaveSums(int32_t sp, char* part_lds) : sums(SPLIT), split(sp), part(part_lds) {}
+    __device__ __forceinline__ WaveSums(int32_t sp, int32_t w, char* part_lds)
+        : sums(SPLIT), split(sp), wave(w), part(part_lds) {}
     __device__ __forceinline__ void row_done(int32_t row) {
         if constexpr (SPLIT) {
-            if (split == 1) {
+            if (split == 1 || wave == 0) {
                 sums.row_done();
                 return;
             }
             constexpr int32_t R = kStencilRows<D>;
-            T* const p = reinterpret_cast<T*>(part) + min(row, R - 1) * NV * 64 + (threadIdx.x & 63u);
+            T* const p = reinterpret_cast<T*>(part) + (min(row, R - 1) - R / split) * NV * 64 + (threadIdx.x & 63u);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 p[k * 64] = row < R ? sums.acc[k] : p[k * 64] + sums.acc[k];
@@ -767,7 +773,7 @@ struct WaveSums {
         if (SPLIT && split > 1) {
             __syncthreads();
             if (w.wave != 0) return false;
-            for (int32_t row = 0; row < kStencilRows<D>; ++row)
+            for (int32_t row = 0; row < kStencilRows<D> - kStencilRows<D> / split; ++row)
 #pragma unroll
                 for (int k = 0; k < NV; ++k)
                     sums.tot[k] += reinterpret_cast<const T*>(part)[(row * NV + k) * 64 + (threadIdx.x & 63u)];
@@ -783,9 +789,10 @@ constexpr int kSearchThreads = 64 * 9;  // most threads of a search workgroup (a
 // row_split: waves per 64 particles of a cell list by its size (0: a running sum).
 // (Kernels that always take one wave only look whether it is 0.)
 // search_shape: launch shape of a box-search kernel by row_split, whose waves each need
-// wave_bytes of LDS (their window) and, when split, whose workgroup needs part_bytes more.
+// wave_bytes of LDS (their window) and whose workgroup, split s ways, needs part_bytes(s) more.
 int32_t row_split(const aboria_cells* c);
-inline SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, uint32_t wave_bytes, uint32_t part_bytes) {
+template <typename PartBytes>
+inline SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, uint32_t wave_bytes, PartBytes part_bytes) {
     return settle_search((uint64_t)c->n, row_split(c), [=](int32_t) { return wave_bytes; }, part_bytes, lds_limit(ctx));
 }
 

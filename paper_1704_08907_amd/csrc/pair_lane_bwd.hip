@@ -37,7 +37,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_bwd(const
     const WaveRows w = wave_rows<D, SPLIT>(split);
     const uint32_t s = w.s;
     const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
-    WaveSums<T, D, F + D + NA, SPLIT> ws(split, part_lds(lds, WB));
+    WaveSums<T, D, F + D + NA, SPLIT> ws(split, w.wave, part_lds(lds, WB));
     auto& sums = ws.sums;
     if (s < n) {
         const SysParams<T> P = sp[b];
@@ -86,7 +86,7 @@ void launch_bwd_kernel(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& 
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     constexpr int NV = (FUSED ? OpShape<OP, D>::NY : 0) + D + OpShape<OP, D>::NA;
     const SearchShape sh =
-        search_shape(ctx, c, WindowBytes<T, D, kWinGrad<OP, D>>::value, WaveSums<T, D, NV, true>::kPartBytes);
+        search_shape(ctx, c, WindowBytes<T, D, kWinGrad<OP, D>>::value, WaveSums<T, D, NV, true>::part_bytes);
 #define LB(O, S)                                                                                              \
     hipLaunchKernelGGL((k_lane_bwd<T, D, OP, BATCH, O, FUSED, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, \
                        ctx->stream, (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s,   \

@@ -19,7 +19,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_fwd(const
     const WaveRows w = wave_rows<D, SPLIT>(split);
     const uint32_t s = w.s;
     const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
-    WaveSums<T, D, NY, SPLIT> ws(split, part_lds(lds, WB));
+    WaveSums<T, D, NY, SPLIT> ws(split, w.wave, part_lds(lds, WB));
     auto& sums = ws.sums;
     if (s < n) {
         const SysParams<T> P = sp[b];
@@ -46,7 +46,7 @@ void launch_lane_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q,
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const SearchShape sh =
-        search_shape(ctx, c, WindowBytes<T, D, 0>::value, WaveSums<T, D, PairOp<T, D, OP>::NY, true>::kPartBytes);
+        search_shape(ctx, c, WindowBytes<T, D, 0>::value, WaveSums<T, D, PairOp<T, D, OP>::NY, true>::part_bytes);
 #define LF(O, S)                                                                                                    \
     hipLaunchKernelGGL((k_lane_fwd<T, D, OP, BATCH, O, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, ctx->stream, \
                        (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, q, y, sh.split)

@@ -187,8 +187,9 @@ struct MaskSums {
         sizeof(T) == 4 ? WindowBytes<T, D, MODE == 0 ? 0 : GyPitch<OpShape<OP, D>::NY>::value>::value : 0u;
     // row sums, and with MODE 0 a word per wave and lane for the rows' overflow
     template <typename T>
-    static constexpr uint32_t PartSize =
-        WaveSums<T, D, NV, true>::kPartBytes + (MODE == 0 ? (uint32_t)kStencilRows<D> * 64u * 4u : 0u);
+    static constexpr uint32_t part_bytes(int32_t sp) {
+        return WaveSums<T, D, NV, true>::part_bytes(sp) + (MODE == 0 ? (uint32_t)sp * 64u * 4u : 0u);
+    }
 };
 
 // MODE 0: forward sum + record.  MODE 1: adjoint from the record (gy_s gathered
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_mask(cons
     const WaveRows w = wave_rows<D, SPLIT>(split);
     const uint32_t s = w.s;
     const int b = system_of_row<BATCH>(sys_part, nsys, w.first, s);
-    WaveSums<T, D, NV, SPLIT> ws(split, part_lds(lds, WB));
+    WaveSums<T, D, NV, SPLIT> ws(split, w.wave, part_lds(lds, WB));
     auto& sums = ws.sums;
     T* const acc = sums.acc;
     auto row_done = [&](int32_t row) { ws.row_done(row); };
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_mask(cons
       bool overflow = false;
       // split: each row's overflow, after the rows' sums
       uint32_t* const row_ovf =
-          reinterpret_cast<uint32_t*>(ws.part + WaveSums<T, D, NV, SPLIT>::kPartBytes) + (threadIdx.x & 63u);
+          reinterpret_cast<uint32_t*>(ws.part + ws.part_bytes(split)) + (threadIdx.x & 63u);
       if (s < n) {
         const SysParams<T> P = sp[b];
         T xi[D];
@@ -823,7 +824,7 @@ void launch_mask(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, con
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     using MS = MaskSums<MODE, OP, D>;
-    const SearchShape sh = search_shape(ctx, c, MS::template WindowSize<T>, MS::template PartSize<T>);
+    const SearchShape sh = search_shape(ctx, c, MS::template WindowSize<T>, MS::template part_bytes<T>);
 #define LM(O, S)                                                                                                    \
     hipLaunchKernelGGL((k_lane_mask<T, D, OP, BATCH, O, MODE, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds,       \
                        ctx->stream, (const T*)c->xs, c->off, c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, \

@@ -147,7 +147,8 @@ void launch_build_nbr(aboria_ctx* ctx, aboria_cells* c) {
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const int32_t split = ((uint64_t)n + 63) / 64 <= shared_waves(c) ? row_split(c) : 0;
     const SearchShape sh = settle_search(
-        n, split, [](int32_t sp) { return WindowBytes<T, D, 0>::value + stash_bytes(sp); }, 0u, lds_limit(ctx));
+        n, split, [](int32_t sp) { return WindowBytes<T, D, 0>::value + stash_bytes(sp); },
+        [](int32_t) { return 0u; }, lds_limit(ctx));
 #define NB(B, O, S)                                                                                             \
     hipLaunchKernelGGL((k_nbr_build<T, D, B, O, S>), dim3(sh.blocks), dim3(sh.threads), sh.lds, ctx->stream,     \
                        (const T*)c->xs, c->off, n, sp, c->sys_part_dev, c->nsys, c->nbr, c->nbr_count, c->nbr_cap, \

@@ -24,16 +24,18 @@ int main() {
         for (uint32_t w : windows)
             for (int split : {0, 1, 3, 9}) {
                 // list recording: a window, the stash and the counts of each wave, laid out by the settled split
-                const SearchShape r = settle_search(40000, split, [=](int32_t s) { return w + stash_bytes(s); }, 0u, limit);
+                const SearchShape r = settle_search(40000, split, [=](int32_t s) { return w + stash_bytes(s); },
+                                                    [](int32_t) { return 0u; }, limit);
                 const uint32_t waves = r.threads / 64u;
                 const uint32_t kernel = waves * w + (r.split > 1 ? waves * stash_of(r.split) * 256u + waves * 256u : 0u);
                 need(r.split <= 1 || (int)waves == r.split, "waves", split, w, limit);
                 need(kernel <= r.lds, "recording", split, w, limit);
                 need(r.lds <= limit || r.split <= 1, "recording limit", split, w, limit);
-                // sums: windows and the rows' sums
-                for (uint32_t part : {0u, 4608u, 32256u}) {
+                // sums: windows and the rows' sums of all waves but the first (256 to 3584 bytes a row)
+                for (uint32_t row : {256u, 512u, 1792u, 3584u}) {
+                    auto part = [=](int32_t s) { return s > 1 ? (9u - 9u / s) * row : 0u; };
                     const SearchShape s = settle_search(40000, split, [=](int32_t) { return w; }, part, limit);
-                    need(s.lds >= (s.threads / 64u) * w + (s.split > 1 ? part : 0u), "sums", split, w, limit);
+                    need(s.lds >= (s.threads / 64u) * w + part(s.split), "sums", split, w, limit);
                     need(s.lds <= limit || s.split <= 1, "sums limit", split, w, limit);
                     need((uint64_t)s.blocks * (s.split > 1 ? 64u : 256u) >= 40000u, "blocks", split, w, limit);
                 }
