@@ -786,10 +786,12 @@ struct WaveSums {
 
 constexpr int kSearchThreads = 64 * 9;  // most threads of a search workgroup (a wave per row)
 
-// row_split: waves per 64 particles of a cell list by its size (0: a running sum).
-// (Kernels that always take one wave only look whether it is 0.)
+// row_waves: how many waves would share the rows of 64 particles.  row_split: how many do
+// in a sum (0: a running sum).  (Kernels that always take one wave only look whether it
+// is 0.)
 // search_shape: launch shape of a box-search kernel by row_split, whose waves each need
 // wave_bytes of LDS (their window) and whose workgroup, split s ways, needs part_bytes(s) more.
+int32_t row_waves(const aboria_cells* c);
 int32_t row_split(const aboria_cells* c);
 template <typename PartBytes>
 inline SearchShape search_shape(aboria_ctx* ctx, const aboria_cells* c, uint32_t wave_bytes, PartBytes part_bytes) {

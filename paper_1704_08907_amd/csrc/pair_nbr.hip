@@ -145,7 +145,7 @@ template <typename T, int D>
 void launch_build_nbr(aboria_ctx* ctx, aboria_cells* c) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
-    const int32_t split = ((uint64_t)n + 63) / 64 <= shared_waves(c) ? row_split(c) : 0;
+    const int32_t split = ((uint64_t)n + 63) / 64 <= shared_waves(c) ? row_waves(c) : 0;
     const SearchShape sh = settle_search(
         n, split, [](int32_t sp) { return WindowBytes<T, D, 0>::value + stash_bytes(sp); },
         [](int32_t) { return 0u; }, lds_limit(ctx));

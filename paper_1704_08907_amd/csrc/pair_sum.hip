@@ -290,23 +290,42 @@ aboria_status check_variant(aboria_ctx* ctx, const aboria_cells* c, int variant)
 
 }  // namespace
 
-// How many waves share the rows of 64 particles (3^(d-1) rows where the grid is
-// searched one cell deep in y and z): a wave per row up to 640 waves of particles,
-// three up to 10000, above it one wave with a running sum.  A wave takes tens of
-// microseconds for nine rows, most of it waiting, so the chip wants several waves on
-// each of its 1024 SIMDs more than it minds their set-up; where 64 particles a wave
-// already give ten or more, the set-up is all that is left.  Measured with 1 / 3 / 9
-// waves, forward and adjoint, us: 5000 particles (3-d, 30 neighbours, float32)
-// 48 / 20 / 9.4 and 64 / 29 / 14.4; 20000: 39 / 16.5 / 10.2 and 55 / 25 / 15.7; 60000 in
-// float64: 52 / 27 / 29.6 and 66 / 38 / 47; 100003: 49 / 25 / 34 and 49 / 34 / 41; 2^18
-// (soft sphere, 40 neighbours) 60 / 50 / 71 and 84 / 71 / 103; 2^19: 80 / 75 / 128 and
-// 130 / 116 / 168; 2^20: 122 / 123 / 222 and 204 / 206 / 316 (forward and adjoint in one
-// call 201 / 231).  2-d, 300007: 20.4 / 17.6 and 32 / 28.
-int32_t row_split(const aboria_cells* c) {
-    const uint64_t waves = ((uint64_t)c->n + 63) / 64;
+// How many waves share the rows of 64 particles where they do: a wave per row (3^(d-1) rows
+// where the grid is searched one cell deep in y and z) up to 640 waves of particles, above
+// it three; 0 where the search has one row or more.  Measured with 1 / 3 / 9 waves, forward
+// and adjoint, us: 5000 particles (3-d, 30 neighbours, float32) 48 / 20 / 9.4 and 64 / 29 /
+// 14.4; 20000: 39 / 16.5 / 10.2 and 55 / 25 / 15.7; 60000 in float64: 52 / 27 / 29.6 and 66 /
+// 38 / 47; 100003: 49 / 25 / 34 and 49 / 34 / 41.
+int32_t row_waves(const aboria_cells* c) {
     const int32_t rows = c->d == 1 ? 1 : (c->d == 2 ? 3 : 9);
     if (rows == 1 || !rows_reach1(c)) return 0;
-    return waves <= 640 ? rows : (waves <= 10000 ? 3 : 0);
+    return ((uint64_t)c->n + 63) / 64 <= 640 ? rows : 3;
+}
+
+// The most waves of particles whose sums share rows; larger lists keep one wave per 64
+// particles and a running sum.  A wave takes tens of microseconds for its rows, most of it
+// waiting, so the chip wants several waves on each of its 1024 SIMDs more than it minds
+// their set-up; where 64 particles a wave already give enough, the set-up is all that is
+// left, and it weighs the more the fewer candidates a cell holds, the more sums a kernel
+// forms (the fused one, the float64 ones in 3-d, whose LDS then limits the waves) and with a
+// batch's look-up of systems.  Three waves' time in that of one, the slowest of forward,
+// adjoint, record, replay, fused and step kernels (and the plain forward), below and above
+// each line: float64 in 3-d 100003 particles 0.96 (0.71), 130000 1.09 (0.86); batches of
+// float32 in 3-d 190000 0.96 (0.83), 262144 1.14 (0.92), in 2-d 190000 1.04 (0.97), of
+// float64 in 2-d 160000 0.97 (0.88), 190000 1.10 (0.97); cells of fewer than four 224000 1.02
+// (0.99), 300007 1.10 (1.09); of four to ten in 3-d 262144 1.01 (0.86), 300007 1.09 (0.94),
+// in 2-d 400000 1.00 (0.99), 500000 1.04 (1.00); of ten and more 500000 1.03 (0.90).
+uint64_t row_sum_waves(const aboria_cells* c) {
+    const bool f64 = c->dtype == ABORIA_F64;
+    if (f64 && c->d == 3) return 1600;
+    if (c->nsys > 1) return f64 ? 2500 : 3000;
+    const double per_cell = (double)c->n / (double)std::max<int64_t>(c->ncells, 1);
+    if (per_cell < 4.0) return 3500;
+    return per_cell >= 10.0 ? 10000 : (c->d == 3 ? 4200 : 6500);
+}
+
+int32_t row_split(const aboria_cells* c) {
+    return ((uint64_t)c->n + 63) / 64 <= row_sum_waves(c) ? row_waves(c) : 0;
 }
 
 int32_t variant_count() { return kNumVariants; }
