@@ -550,7 +550,11 @@ __device__ __forceinline__ void neighbour_loop_aux(const SysParams<T>& P, const 
         bool lane_shift = false;
 #pragma unroll
         for (int k = 0; k < D; ++k) lane_shift |= sh[k] != T(0);
-        if constexpr (DEFER) {
+        // (without rows of aux, deferred only where the accepted pairs' positions are read
+        // again from LDS: from HBM they cost more than the summands saved.  Float64
+        // exponential, 700001 particles in 3-d with 120 neighbours, whose rows do not fit a
+        // window: forward 877 us, deferred 981)
+        if constexpr (DEFER && (WIN || NAUX > 0)) {
             if (__ballot(lane_shift) != 0ull)
                 scan_range_deferred<T, D, true, OFF32, NAUX, WIN>(xs, aux, j0, j1, xi, sh, r2, lane_shift, visit, w);
             else
