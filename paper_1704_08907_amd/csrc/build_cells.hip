@@ -21,6 +21,7 @@
 #include <cstring>
 #include <limits>
 #include <new>
+#include <type_traits>
 
 #include "common.hpp"
 #include "lds_shape.hpp"
@@ -682,7 +683,7 @@ __global__ __launch_bounds__(kScatterThreads) void k_radix_scatter(const uint32_
 // 2.7 TB/s); counts beside room for 2048 keys, two to a CU, took 20.6.  100003 particles
 // in buckets of 463 keys: 6.4 us, in 54 buckets of 1850 16.4.  5.8 M particles in 512
 // systems, 8500 keys a bucket, gathered late by 1024 threads: 126 us, chunk by chunk 255.
-// A bucket over cap keys is worked off in chunks of NT * KPT, with scattered stores.
+// A bucket over cap keys is worked off in chunks, with scattered stores.
 template <typename T, int D, int NT, int KPT, bool ROWS>
 __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ? 4 : 8) void k_bucket_finalize(const uint32_t* __restrict__ keys_in,
                                                         const uint32_t* __restrict__ vals_in, uint32_t n, int lb,
@@ -697,7 +698,9 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
     constexpr int PITCH = Pitch<D>::value;
     using Row = VecN<T, PITCH>;
     constexpr int NW = NT / kWave;
-    constexpr uint32_t kChunk = NT * KPT;
+    constexpr int KPC = 4;  // keys per thread of a chunk of a larger bucket
+    constexpr int KPM = KPT > KPC ? KPT : KPC;
+    constexpr uint32_t kChunk = NT * KPC;
     constexpr int kMaxPer = (1 << kMaxDigitBits) / NT > 0 ? (1 << kMaxDigitBits) / NT : 1;
     extern __shared__ __align__(32) uint32_t lds[];
     const uint32_t R = 1u << lb, mask = R - 1u;
@@ -752,12 +755,14 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
     // the chunk's keys and indices: every load first, so they are in flight together
     // (without ROWS the indices are read when they are placed, for eight waves per SIMD).
     // dl: a key's digit (its low 10 bits) and above it its place; its key is cell0 + digit.
-    uint32_t dl[KPT], val[ROWS ? KPT : 1];
+    uint32_t dl[KPM], val[ROWS ? KPM : 1];
     constexpr uint32_t kDigit = (1u << kMaxDigitBits) - 1u;
-    auto load_chunk = [&](uint32_t chunk) {
-        const uint32_t wbase = chunk + w * (kWave * KPT);
+    // (K keys per thread from chunk on)
+    auto load_keys = [&](auto count_tag, uint32_t chunk) {
+        constexpr int K = decltype(count_tag)::value;
+        const uint32_t wbase = chunk + w * (kWave * K);
 #pragma unroll
-        for (int st = 0; st < KPT; ++st) {
+        for (int st = 0; st < K; ++st) {
             const uint32_t idx = wbase + st * kWave + lane;
             const bool valid = idx < b1;
             dl[st] = valid ? keys_in[idx] & mask : 0u;
@@ -765,10 +770,11 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
         }
     };
     // rank of each key among the wave's keys of its digit so far, counts in wc
-    auto rank_chunk = [&](uint32_t chunk) {
-        const uint32_t wbase = chunk + w * (kWave * KPT);
+    auto rank_keys = [&](auto count_tag, uint32_t chunk) {
+        constexpr int K = decltype(count_tag)::value;
+        const uint32_t wbase = chunk + w * (kWave * K);
 #pragma unroll
-        for (int st = 0; st < KPT; ++st) {
+        for (int st = 0; st < K; ++st) {
             const bool valid = wbase + st * kWave + lane < b1;
             const uint32_t dg = dl[st];
             uint64_t peers = __ballot(valid);
@@ -783,9 +789,11 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
             dl[st] = dg | (c + below) << kMaxDigitBits;
         }
     };
+    using Whole = std::integral_constant<int, KPT>;
+    using Part = std::integral_constant<int, KPC>;
     if (b1 - b0 <= cap) {
-        // ---- the whole bucket at once (cap <= kChunk) ----
-        load_chunk(b0);
+        // ---- the whole bucket at once (cap <= NT * KPT) ----
+        load_keys(Whole(), b0);
         const uint32_t wbase = b0 + w * (kWave * KPT);
         Row row[ROWS ? KPT : 1];
         if constexpr (ROWS) {
@@ -793,7 +801,7 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
             for (int st = 0; st < KPT; ++st)
                 if (wbase + st * kWave + lane < b1) row[st] = pay ? pay[wbase + st * kWave + lane] : load_xrow(val[st]);
         }
-        rank_chunk(b0);
+        rank_keys(Whole(), b0);
         __syncthreads();
         // each thread's digits: the waves' counts, their exclusive scan over the bucket,
         // the cells' offsets and the waves' first places
@@ -875,9 +883,21 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
             for (uint32_t d = threadIdx.x; d < NW * R; d += NT) cnt[d] = 0;
             __syncthreads();
         }
-        const uint32_t wbase = chunk + w * (kWave * KPT);
-        load_chunk(chunk);
-        rank_chunk(chunk);
+        const uint32_t wbase = chunk + w * (kWave * KPC);
+        // keys, indices and rows first, all in flight together (indices and rows loaded where
+        // they are placed waited for each other: 2^20 particles in a Gaussian blob, 3-d, 225
+        // us with 4096 keys a chunk, 198 so with 2048)
+        load_keys(Part(), chunk);
+        uint32_t v[KPC];
+        Row row[KPC];
+#pragma unroll
+        for (int st = 0; st < KPC; ++st) {
+            const uint32_t idx = min(wbase + st * kWave + lane, b1 - 1u);
+            if constexpr (ROWS) v[st] = val[st];
+            else v[st] = load_val(idx);
+            row[st] = pay ? pay[idx] : load_xrow(v[st]);
+        }
+        rank_keys(Part(), chunk);
         __syncthreads();
         for (uint32_t d = threadIdx.x; d < R; d += NT) {
             // the waves' first destinations of digit d, in wave (= index) order
@@ -892,15 +912,13 @@ __global__ __launch_bounds__(NT, ROWS && sizeof(VecN<T, Pitch<D>::value>) > 16 ?
         }
         __syncthreads();
 #pragma unroll
-        for (int st = 0; st < KPT; ++st) {
-            const uint32_t idx = wbase + st * kWave + lane;
-            if (idx < b1) {
+        for (int st = 0; st < KPC; ++st) {
+            if (wbase + st * kWave + lane < b1) {
                 const uint32_t dest = b0 + wc[dl[st] & kDigit] + (dl[st] >> kMaxDigitBits);
                 if (dest < n) {  // always true for a consistent histogram; keeps a bad one in bounds
-                    const uint32_t v = load_val(idx);
                     keys_out[dest] = cell0 + (dl[st] & kDigit);
-                    perm_out[dest] = v;
-                    reinterpret_cast<Row*>(xs)[dest] = pay ? pay[idx] : load_xrow(v);
+                    perm_out[dest] = v[st];
+                    reinterpret_cast<Row*>(xs)[dest] = row[st];
                 }
             }
         }
@@ -1182,15 +1200,20 @@ uint64_t build_key(int32_t d, int32_t dtype, bool batch, int64_t n, int64_t ncel
 // Key bits the bucket pass sorts: one bucket of everything where that is at most 2048
 // keys; else about 512 keys a bucket, so that a CU runs several at once -- more, up to
 // 1650, while the buckets are too many for 8 bits of a radix pass (whose runs of a digit
-// get short), and at least what one pass of 10 bits leaves.  Build of 100003 particles
-// (3-d, 14 bits of key), us, with 5 / 6 / 7 / 8 bits: 20.2 / 18.3 / 20.3 / 23.1; 2^18 (15 bits):
-// 28.2 / 24.6 / 24.7 / 27.5; 300007 in 2-d (16 bits), 6 / 7 / 8 bits: 28.2 / 26.0 / 23.9.
+// get short), but then no wider than 8 bits up to 300000 particles and 9 up to 600000, where
+// that costs a uniform build 11 % at most and clustered ones gain more (2^18 in 2-d with 5
+// neighbours, 8 / 10 bits: uniform 23.9 / 22.5, in a quarter of the box 27.9 / 48.5; 2^19,
+// 9 / 10: 35.0 / 31.6 and 43.3 / 54.7) -- and at least what one pass of 10 bits leaves.
+// Build of 100003 particles (3-d, 14 bits of key), us, with 5 / 6 / 7 / 8 bits: 20.2 / 18.3 /
+// 20.3 / 23.1; 2^18 (15 bits): 28.2 / 24.6 / 24.7 / 27.5; 300007 in 2-d (16 bits), 6 / 7 / 8
+// bits: 28.2 / 26.0 / 23.9.
 int bucket_bits_for(int64_t n, int64_t ncells, int bits) {
     if (n <= 2048 && bits <= kMaxDigitBits) return bits;
     const double per_cell = std::max((double)n / (double)std::max<int64_t>(ncells, 1), 1e-3);
     const int want = (int)std::lround(9.0 - std::log2(per_cell));
     const int most = (int)std::floor(std::log2(1650.0 / per_cell));
-    const int lb = std::max(std::max(want, std::min(bits - 8, most)), std::max(1, bits - kMaxDigitBits));
+    const int widest = n <= 300000 ? 8 : (n <= 600000 ? 9 : 10);
+    const int lb = std::max(std::max(want, std::min({bits - 8, most, widest})), std::max(1, bits - kMaxDigitBits));
     return std::min(lb, std::min(bits, kMaxDigitBits));
 }
 
