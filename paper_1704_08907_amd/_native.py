@@ -294,8 +294,8 @@ def build_cells(ctx: Context, x: torch.Tensor, boxes: Sequence[BoxSpec], offsets
 
 def autotune_build(ctx: Context, x: torch.Tensor, boxes: Sequence[BoxSpec],
                    offsets: Optional[Sequence[int]] = None) -> tuple:
-    """aboria_autotune_build: times the radix build shapes for these boxes and caches the
-    fastest; returns (keys per thread, bucket bits, shuffle)."""
+    """aboria_autotune_build: times radix build shapes for these boxes and caches the fastest,
+    unless the rule's own is faster; returns (keys per thread, bucket bits, shuffle)."""
     _check_dev(x, "x")
     boxes = list(boxes)
     nsys = len(boxes)

@@ -1180,16 +1180,11 @@ aboria_status launch_build_counting(aboria_ctx* ctx, aboria_cells* c, const void
     return ABORIA_OK;
 }
 
-// Keys per thread of a sort tile for n keys: the largest of 16, 8, 4 that
-// still gives at least 512 tiles (2 per CU; the scatter and bucket passes are
-// latency-bound with fewer), else 4.  Measured on MI355X: a 2^20 cube builds
-// in the same time with 4096- or 2048-key tiles but 25 % faster with 2048 on
-// cells of half the width; 2^18 particles build 22 % faster with 1024-key
-// tiles; 5.8 M particles in 512 systems are fastest with 4096.
 // Key of the radix build-shape cache: d, dtype, batch and the size buckets
-// (floor log2) of the particles and the cells.
+// (floor log2) of the particles and the cells.  d counts from 5: shapes saved under 1 to 3
+// were timed on a bucket pass that took other widths best.
 uint64_t build_key(int32_t d, int32_t dtype, bool batch, int64_t n, int64_t ncells) {
-    uint64_t k = (uint64_t)d;
+    uint64_t k = 4u + (uint64_t)d;
     k = k * 4 + (uint64_t)dtype;
     k = k * 2 + (uint64_t)batch;
     k = k * 64 + (uint64_t)std::floor(std::log2((double)n + 1.0));
@@ -1217,6 +1212,12 @@ int bucket_bits_for(int64_t n, int64_t ncells, int bits) {
     return std::min(lb, std::min(bits, kMaxDigitBits));
 }
 
+// Keys per thread of a sort tile for n keys: the largest of 16, 8, 4 that
+// still gives at least 512 tiles (2 per CU; the scatter and bucket passes are
+// latency-bound with fewer), else 4.  Measured on MI355X: a 2^20 cube builds
+// in the same time with 4096- or 2048-key tiles but 25 % faster with 2048 on
+// cells of half the width; 2^18 particles build 22 % faster with 1024-key
+// tiles; 5.8 M particles in 512 systems are fastest with 4096.
 int sort_ipt_for(int64_t n) {
     if (n >= (int64_t)512 * kBlock * 16) return 16;
     if (n >= (int64_t)512 * kBlock * 8) return 8;
@@ -1497,13 +1498,15 @@ extern "C" aboria_status aboria_build_cells(aboria_ctx* ctx, aboria_dtype dtype,
             c->sort_ipt = sort_ipt_for(n);
             // a forced shape, else the tuned one for this size, replaces the rule
             aboria_ctx::BuildShape shape = ctx->build_forced;
-            if (shape.ipt == 0 && shape.low_bits == 0 && shape.shuffle == 0) {
+            if (shape.ipt == 0 && shape.low_bits == 0 && shape.shuffle == 0 && !ctx->build_by_rule) {
                 const uint64_t bkey = build_key(d, dtype, nsys > 1, n, total_cells);
                 for (const auto& kv : ctx->build_cache)
                     if (kv.first == bkey) shape = kv.second;
             }
             if (shape.ipt == 4 || shape.ipt == 8 || shape.ipt == 16) c->sort_ipt = shape.ipt;
-            if (shape.low_bits >= 8 && shape.low_bits <= kMaxDigitBits) c->low_bits = std::min(bits, shape.low_bits);
+            if (shape.low_bits >= 1 && shape.low_bits <= kMaxDigitBits) c->low_bits = std::min(bits, shape.low_bits);
+            while (c->low_bits < kMaxDigitBits && (total_cells >> c->low_bits) >= (int64_t)1 << 21)
+                ++c->low_bits;  // the buckets' threads stay below 2^32, a grid's most
             if (shape.shuffle == 1 || shape.shuffle == 2) c->shuffle_pref = shape.shuffle;
             const int high = bits - c->low_bits;
             c->passes = (high + kMaxDigitBits - 1) / kMaxDigitBits;
@@ -1623,8 +1626,8 @@ extern "C" aboria_status aboria_set_build_shape(aboria_ctx* ctx, int32_t ipt, in
     if (!ctx) return ABORIA_ERR_INVALID_ARG;
     if (ipt != 0 && ipt != 4 && ipt != 8 && ipt != 16)
         return fail(ctx, ABORIA_ERR_INVALID_ARG, "keys per thread must be 0, 4, 8 or 16");
-    if (low_bits != 0 && (low_bits < 8 || low_bits > kMaxDigitBits))
-        return fail(ctx, ABORIA_ERR_INVALID_ARG, "bucket bits must be 0 or 8 to 10");
+    if (low_bits < 0 || low_bits > kMaxDigitBits)
+        return fail(ctx, ABORIA_ERR_INVALID_ARG, "bucket bits must be 0 to 10");
     if (shuffle < 0 || shuffle > 2) return fail(ctx, ABORIA_ERR_INVALID_ARG, "shuffle must be 0, 1 or 2");
     ctx->build_forced = aboria_ctx::BuildShape{ipt, low_bits, shuffle};
     return ABORIA_OK;
@@ -1651,36 +1654,56 @@ extern "C" aboria_status aboria_autotune_build(aboria_ctx* ctx, aboria_dtype dty
         double best_ms = INFINITY;
         aboria_ctx::BuildShape best{0, 0, 0};
         int64_t ncells = 0, n = offsets_host[nsys];
-        const int32_t ipts[] = {4, 8, 16};
-        const int32_t lows[] = {8, 9, 10};
-        int32_t last_bits = -1;
-        for (int32_t ipt : ipts) {
-            for (int32_t lb : lows) for (int32_t sh = 1; sh <= 2; ++sh) {
-                if (st != ABORIA_OK) break;
-                ctx->build_forced = aboria_ctx::BuildShape{ipt, lb, sh};
-                aboria_cells* c = nullptr;
+        // one shape: a cell list created with it, then five rebuilds
+        auto time_shape = [&](const aboria_ctx::BuildShape& shape, float* ms, int32_t* low_bits, int32_t* key_bits) {
+            ctx->build_forced = shape;
+            aboria_cells* c = nullptr;
+            st = aboria_build_cells(ctx, dtype, nsys, boxes_host, offsets_host, x, &c);
+            if (st != ABORIA_OK) return;
+            ncells = c->ncells;
+            *low_bits = c->low_bits;
+            *key_bits = c->key_bits;
+            (void)hipEventRecord(e0, ctx->stream);
+            for (int rep = 0; rep < 5 && st == ABORIA_OK; ++rep)
                 st = aboria_build_cells(ctx, dtype, nsys, boxes_host, offsets_host, x, &c);
-                if (st != ABORIA_OK) break;
-                ncells = c->ncells;
-                if (c->low_bits != lb && lb != lows[0]) {  // fewer key bits than lb: a smaller lb's shape
-                    (void)aboria_cells_destroy(c);
-                    continue;
-                }
-                last_bits = c->key_bits;
-                (void)hipEventRecord(e0, ctx->stream);
-                for (int rep = 0; rep < 5 && st == ABORIA_OK; ++rep)
-                    st = aboria_build_cells(ctx, dtype, nsys, boxes_host, offsets_host, x, &c);
-                (void)hipEventRecord(e1, ctx->stream);
-                if (hipEventSynchronize(e1) != hipSuccess) st = hip_fail(ctx, hipGetLastError(), "timing a build");
-                float ms = 0.f;
-                (void)hipEventElapsedTime(&ms, e0, e1);
-                (void)aboria_cells_destroy(c);
-                if (st != ABORIA_OK) break;
-                log_msg("autotune_build: %d keys per thread, %d bucket bits, shuffle %s: %.4f ms", ipt, lb,
-                        sh == 1 ? "on" : "off", ms / 5.0);
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best = aboria_ctx::BuildShape{ipt, lb, sh};
+            (void)hipEventRecord(e1, ctx->stream);
+            if (hipEventSynchronize(e1) != hipSuccess) st = hip_fail(ctx, hipGetLastError(), "timing a build");
+            *ms = 0.f;
+            (void)hipEventElapsedTime(ms, e0, e1);
+            (void)aboria_cells_destroy(c);
+        };
+        // The rule's shape, then widths of 8 to 10 bits and, where a radix pass of at most 8
+        // bits takes the rest, those around the rule's.  A width timed with every tile size
+        // and shuffle includes the rule's shape; the rule's own time counts only where its
+        // width is not among them.
+        float ms = 0.f, rule_ms = 0.f;
+        int32_t rule_bits = 0, low_bits = 0, key_bits = 0;
+        ctx->build_by_rule = true;
+        time_shape(aboria_ctx::BuildShape{0, 0, 0}, &rule_ms, &rule_bits, &key_bits);
+        ctx->build_by_rule = false;
+        const int32_t ipts[] = {4, 8, 16};
+        std::vector<int32_t> lows;
+        for (int32_t lb = std::max(rule_bits - 1, 1); lb < 8 && lb <= rule_bits + 1; ++lb)
+            if (key_bits - lb <= 8) lows.push_back(lb);
+        for (int32_t lb = 8; lb <= kMaxDigitBits; ++lb) lows.push_back(lb);
+        // (a width of more than the key's bits is the key's: timed once)
+        const bool rule_timed =
+            std::find_if(lows.begin(), lows.end(), [&](int32_t lb) { return std::min(lb, key_bits) == rule_bits; }) != lows.end();
+        for (int32_t ipt : ipts) {
+            int32_t last = 0;
+            for (int32_t lb : lows) {
+                if (std::min(lb, key_bits) == last) continue;
+                last = std::min(lb, key_bits);
+                for (int32_t sh = 1; sh <= 2; ++sh) {
+                    if (st != ABORIA_OK) break;
+                    time_shape(aboria_ctx::BuildShape{ipt, lb, sh}, &ms, &low_bits, &key_bits);
+                    if (st != ABORIA_OK) break;
+                    log_msg("autotune_build: %d keys per thread, %d bucket bits, shuffle %s: %.4f ms", ipt, lb,
+                            sh == 1 ? "on" : "off", ms / 5.0);
+                    if (ms < best_ms) {
+                        best_ms = ms;
+                        best = aboria_ctx::BuildShape{ipt, lb, sh};
+                    }
                 }
             }
         }
@@ -1691,16 +1714,17 @@ extern "C" aboria_status aboria_autotune_build(aboria_ctx* ctx, aboria_dtype dty
         if (st != ABORIA_OK) return st;
         if (best.ipt == 0) return fail(ctx, ABORIA_ERR_INVALID_ARG, "no build shape could be timed");
         const uint64_t key = build_key(boxes_host[0].d, dtype, nsys > 1, n, ncells);
-        bool found = false;
-        for (auto& kv : ctx->build_cache)
-            if (kv.first == key) {
-                kv.second = best;
-                found = true;
-            }
-        if (!found) ctx->build_cache.emplace_back(key, best);
+        const bool keep_rule = !rule_timed && rule_ms < best_ms;
+        auto& cache = ctx->build_cache;
+        cache.erase(std::remove_if(cache.begin(), cache.end(), [&](const auto& kv) { return kv.first == key; }),
+                    cache.end());
+        if (!keep_rule) cache.emplace_back(key, best);
         tune_cache_save(ctx);
-        log_msg("autotune_build: %d keys per thread, %d bucket bits, shuffle %s chosen (%d key bits)", best.ipt,
-                best.low_bits, best.shuffle == 1 ? "on" : "off", last_bits);
+        if (keep_rule)
+            log_msg("autotune_build: the rule's shape stays (%d bucket bits, %.4f ms)", rule_bits, rule_ms / 5.0);
+        else
+            log_msg("autotune_build: %d keys per thread, %d bucket bits, shuffle %s chosen (%d key bits)", best.ipt,
+                    best.low_bits, best.shuffle == 1 ? "on" : "off", key_bits);
         if (ipt_out) *ipt_out = best.ipt;
         if (low_bits_out) *low_bits_out = best.low_bits;
         if (shuffle_out) *shuffle_out = best.shuffle;
@@ -1708,6 +1732,7 @@ extern "C" aboria_status aboria_autotune_build(aboria_ctx* ctx, aboria_dtype dty
     } catch (...) {
         ctx->build_forced = forced_before;
         ctx->build_strategy = strategy_before;
+        ctx->build_by_rule = false;
         return fail(ctx, ABORIA_ERR_OUT_OF_MEMORY, "host exception in autotune_build");
     }
 }
