@@ -311,12 +311,12 @@ def autotune_build(ctx: Context, x: torch.Tensor, boxes: Sequence[BoxSpec],
     return int(ipt.value), int(lb.value), int(sh.value)
 
 
-@functools.lru_cache(maxsize=None)
+@functools.lru_cache(maxsize=64, typed=True)
 def op_ny(op: str, d: int) -> int:
     return int(lib().aboria_op_ny(OPS[op], d))
 
 
-@functools.lru_cache(maxsize=None)
+@functools.lru_cache(maxsize=64, typed=True)
 def op_na(op: str) -> int:
     return int(lib().aboria_op_na(OPS[op]))
 
