@@ -31,8 +31,8 @@ def test_clustered(d, n, nbr, low_bits, prec):
     check(clustered(syn.SplitMix64(n + d), n, d, L, prec), L, d, prec, (0, low_bits, 0))
 
 
-# the form of eight keys a thread on uniform particles: 8 bits of 7.3 particles a cell, a mean
-# of 1870 keys and room for 2250
+# the form of eight keys a thread on uniform particles: 8 bits of 7.6 particles a cell, a mean
+# of about 1940 keys and room for 2330
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 @pytest.mark.parametrize("n", [60001, 300007])
 def test_eight_keys_a_thread(n, prec):
