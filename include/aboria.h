@@ -383,9 +383,14 @@ aboria_status aboria_dense_sum_noalloc(aboria_ctx* ctx, aboria_dtype dtype, abor
  * for K = phi(q), q = |xt_i - xs_j|^2.  When targets and sources are the same
  * points, dL/dx = gxt + gxs.  Each output may be NULL (not computed); all are
  * overwritten, in dtype, and must not overlap the inputs or each other.  gw and
- * gxs come from one pass over the pairs, gxt from a second (all three requested: in one launch).  Uses
- * the same grow-only scratch as the forward (a first call of a size must not
- * be captured).  Errors as for aboria_dense_sum. */
+ * gxs come from one pass over the pairs, gxt from a second; all three requested,
+ * both passes run in one launch, and from 2^25 pairs on each pair is formed once
+ * for the three.  There a gradient's bits depend on whether the other two were
+ * requested (same tolerance).  Uses the same grow-only scratch as the forward,
+ * for all three gradients up to 256 MiB, beyond which (and where the device has
+ * no more, or a capture may not allocate) the passes run one after the other.
+ * A first call of a size must not be captured; after it, calls of that size may
+ * be, for any of the gradients.  Errors as for aboria_dense_sum. */
 aboria_status aboria_dense_sum_backward(aboria_ctx* ctx, aboria_dtype dtype, aboria_kernel kernel,
                                         const double* params_host, int32_t nparams, int32_t d, int64_t n_target,
                                         const void* xt, int64_t n_source, const void* xs, const void* w,

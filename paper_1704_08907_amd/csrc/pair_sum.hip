@@ -110,6 +110,9 @@ struct Variant {
     const char* name;
 };
 
+// (The names are what tuning files hold, so they stay as first written: variant 0's
+// workgroups have up to 576 threads, and its adjoint defers the operators whose summands
+// cost several pair tests.)
 const Variant kVariants[] = {
     {0, "lane per particle, 256-thread workgroups, adjoint evaluated on every candidate"},
     {2, "lane per particle over the recorded neighbour list (accepted pairs only)"},
