@@ -220,356 +220,356 @@ __global__ __launch_bounds__(SPLIT ? kSearchThreads : 256) void k_lane_mask(cons
     auto row_done = [&](int32_t row) { ws.row_done(row); };
     char* const wave_wb = wave_window(lds, w.wave, WB);
     if constexpr (MODE == 0) {
-      bool overflow = false;
-      // split: each row's overflow, after the rows' sums
-      uint32_t* const row_ovf =
-          reinterpret_cast<uint32_t*>(ws.part + ws.part_bytes(split)) + (threadIdx.x & 63u);
-      if (s < n) {
-        const SysParams<T> P = sp[b];
-        T xi[D];
-        load_point<T, D>(xs, s, xi);
-        const T ai = NA ? a_s[s] : T(0);
-        const T r = P.r, r2 = P.r2;
-        auto visit = [&](uint32_t j, const T* dx, T d2) {
-            const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
-            Op::fwd(q, r, dx, d2, ai, aj, acc);
-        };
-        // candidates [ja, jb): the summand of each accepted one, and its bit shifted
-        // into rec from the bottom (the row's first candidate ends highest; the
-        // record is bit-reversed when the row is done)
-        auto scan = [&](auto shift_tag, uint32_t ja, uint32_t jb, const T* sh, uint64_t& rec) {
-            constexpr bool SHIFT = decltype(shift_tag)::value;
-            uint32_t j = ja;
-            // float: four candidates per iteration keep four loads in flight (the
-            // float64 kernel, with twice the registers per row, stays at two).
-            // With 32-bit row offsets the loop runs on the first candidate's byte
-            // offset, the other three loads take immediate offsets from the same
-            // address, and the four bits enter the record as two 32-bit halves.
-            if constexpr (sizeof(T) == 4 && OFF32) {
+        bool overflow = false;
+        // split: each row's overflow, after the rows' sums
+        uint32_t* const row_ovf =
+            reinterpret_cast<uint32_t*>(ws.part + ws.part_bytes(split)) + (threadIdx.x & 63u);
+        if (s < n) {
+            const SysParams<T> P = sp[b];
+            T xi[D];
+            load_point<T, D>(xs, s, xi);
+            const T ai = NA ? a_s[s] : T(0);
+            const T r = P.r, r2 = P.r2;
+            auto visit = [&](uint32_t j, const T* dx, T d2) {
+                const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
+                Op::fwd(q, r, dx, d2, ai, aj, acc);
+            };
+            // candidates [ja, jb): the summand of each accepted one, and its bit shifted
+            // into rec from the bottom (the row's first candidate ends highest; the
+            // record is bit-reversed when the row is done)
+            auto scan = [&](auto shift_tag, uint32_t ja, uint32_t jb, const T* sh, uint64_t& rec) {
+                constexpr bool SHIFT = decltype(shift_tag)::value;
+                uint32_t j = ja;
+                // float: four candidates per iteration keep four loads in flight (the
+                // float64 kernel, with twice the registers per row, stays at two).
+                // With 32-bit row offsets the loop runs on the first candidate's byte
+                // offset, the other three loads take immediate offsets from the same
+                // address, and the four bits enter the record as two 32-bit halves.
+                if constexpr (sizeof(T) == 4 && OFF32) {
+                    constexpr uint32_t RB = (uint32_t)sizeof(VecN<T, PITCH>);
+                    const char* const xrow = reinterpret_cast<const char*>(xs);
+                    const uint32_t oend = jb * RB;
+                    const uint32_t olast = oend >= 3u * RB ? oend - 3u * RB : 0u;
+                    uint32_t o = ja * RB;
+                    uint32_t lo = (uint32_t)rec, hi = (uint32_t)(rec >> 32);
+                    for (; o < olast; o += 4u * RB) {
+                        const char* const pj = xrow + (size_t)o;
+                        const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(pj);
+                        const VecN<T, PITCH> xb = *reinterpret_cast<const VecN<T, PITCH>*>(pj + RB);
+                        const VecN<T, PITCH> xc = *reinterpret_cast<const VecN<T, PITCH>*>(pj + 2u * RB);
+                        const VecN<T, PITCH> xd = *reinterpret_cast<const VecN<T, PITCH>*>(pj + 3u * RB);
+                        const uint32_t jj = o / RB;
+                        // the record moves up four places first; each accepted candidate
+                        // then sets its bit inside the branch that adds its summand
+                        hi = (hi << 4) | (lo >> 28);
+                        lo <<= 4;
+                        T dx[D], d2;
+                        if (pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2)) {
+                            visit(jj, dx, d2);
+                            lo |= 8u;
+                        }
+                        if (pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2)) {
+                            visit(jj + 1, dx, d2);
+                            lo |= 4u;
+                        }
+                        if (pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2)) {
+                            visit(jj + 2, dx, d2);
+                            lo |= 2u;
+                        }
+                        if (pair_test<T, D, SHIFT>(xd.v, xi, sh, r2, dx, &d2)) {
+                            visit(jj + 3, dx, d2);
+                            lo |= 1u;
+                        }
+                    }
+                    rec = ((uint64_t)hi << 32) | lo;
+                    j = o / RB;
+                }
+                for (; sizeof(T) == 4 && !OFF32 && j + 3 < jb; j += 4) {
+                    const VecN<T, PITCH> xa = load_row<T, PITCH, OFF32>(xs, j);
+                    const VecN<T, PITCH> xb = load_row<T, PITCH, OFF32>(xs, j + 1);
+                    const VecN<T, PITCH> xc = load_row<T, PITCH, OFF32>(xs, j + 2);
+                    const VecN<T, PITCH> xd = load_row<T, PITCH, OFF32>(xs, j + 3);
+                    T dx[D], d2;
+                    const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
+                    if (oa) visit(j, dx, d2);
+                    const bool ob = pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
+                    if (ob) visit(j + 1, dx, d2);
+                    const bool oc = pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2);
+                    if (oc) visit(j + 2, dx, d2);
+                    const bool od = pair_test<T, D, SHIFT>(xd.v, xi, sh, r2, dx, &d2);
+                    if (od) visit(j + 3, dx, d2);
+                    rec = (rec << 4) | (oa ? 8u : 0u) | (ob ? 4u : 0u) | (oc ? 2u : 0u) | (od ? 1u : 0u);
+                }
+                for (; j + 1 < jb; j += 2) {
+                    const VecN<T, PITCH> xa = load_row<T, PITCH, OFF32>(xs, j);
+                    const VecN<T, PITCH> xb = load_row_at<T, PITCH, OFF32>(xs, j, 1);
+                    T dx[D], d2;
+                    const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
+                    if (oa) visit(j, dx, d2);
+                    const bool ob = pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
+                    if (ob) visit(j + 1, dx, d2);
+                    rec = (rec << 2) | (oa ? 2u : 0u) | (ob ? 1u : 0u);
+                }
+                if (j < jb) {
+                    const VecN<T, PITCH> xa = load_row<T, PITCH, OFF32>(xs, j);
+                    T dx[D], d2;
+                    const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
+                    if (oa) visit(j, dx, d2);
+                    rec = (rec << 1) | (oa ? 1u : 0u);
+                }
+            };
+            // candidates [ja, jb) as scan takes them, read from the wave's LDS window
+            // that holds slots [lo, lo + kWindow) (byte offsets from the window start).
+            // An empty run may lie outside the window (its offsets would wrap), so it
+            // returns at once.
+            auto scan_window = [&](auto shift_tag, uint32_t ja, uint32_t jb, const T* sh, uint64_t& rec,
+                                   const char* wb, uint32_t lo) {
+                constexpr bool SHIFT = decltype(shift_tag)::value;
                 constexpr uint32_t RB = (uint32_t)sizeof(VecN<T, PITCH>);
-                const char* const xrow = reinterpret_cast<const char*>(xs);
-                const uint32_t oend = jb * RB;
+                if (jb <= ja) return;
+                const uint32_t oend = (jb - lo) * RB;
                 const uint32_t olast = oend >= 3u * RB ? oend - 3u * RB : 0u;
-                uint32_t o = ja * RB;
-                uint32_t lo = (uint32_t)rec, hi = (uint32_t)(rec >> 32);
+                uint32_t o = (ja - lo) * RB;
+                uint32_t rlo = (uint32_t)rec, rhi = (uint32_t)(rec >> 32);
                 for (; o < olast; o += 4u * RB) {
-                    const char* const pj = xrow + (size_t)o;
+                    const char* const pj = wb + o;
                     const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(pj);
                     const VecN<T, PITCH> xb = *reinterpret_cast<const VecN<T, PITCH>*>(pj + RB);
                     const VecN<T, PITCH> xc = *reinterpret_cast<const VecN<T, PITCH>*>(pj + 2u * RB);
                     const VecN<T, PITCH> xd = *reinterpret_cast<const VecN<T, PITCH>*>(pj + 3u * RB);
-                    const uint32_t jj = o / RB;
-                    // the record moves up four places first; each accepted candidate
-                    // then sets its bit inside the branch that adds its summand
-                    hi = (hi << 4) | (lo >> 28);
-                    lo <<= 4;
+                    const uint32_t jj = lo + o / RB;
+                    // the record moves up four places first; each accepted candidate then
+                    // sets its bit inside the branch that adds its summand
+                    rhi = (rhi << 4) | (rlo >> 28);
+                    rlo <<= 4;
                     T dx[D], d2;
                     if (pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2)) {
                         visit(jj, dx, d2);
-                        lo |= 8u;
+                        rlo |= 8u;
                     }
                     if (pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2)) {
                         visit(jj + 1, dx, d2);
-                        lo |= 4u;
+                        rlo |= 4u;
                     }
                     if (pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2)) {
                         visit(jj + 2, dx, d2);
-                        lo |= 2u;
+                        rlo |= 2u;
                     }
                     if (pair_test<T, D, SHIFT>(xd.v, xi, sh, r2, dx, &d2)) {
                         visit(jj + 3, dx, d2);
-                        lo |= 1u;
+                        rlo |= 1u;
                     }
                 }
-                rec = ((uint64_t)hi << 32) | lo;
-                j = o / RB;
-            }
-            for (; sizeof(T) == 4 && !OFF32 && j + 3 < jb; j += 4) {
-                const VecN<T, PITCH> xa = load_row<T, PITCH, OFF32>(xs, j);
-                const VecN<T, PITCH> xb = load_row<T, PITCH, OFF32>(xs, j + 1);
-                const VecN<T, PITCH> xc = load_row<T, PITCH, OFF32>(xs, j + 2);
-                const VecN<T, PITCH> xd = load_row<T, PITCH, OFF32>(xs, j + 3);
-                T dx[D], d2;
-                const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
-                if (oa) visit(j, dx, d2);
-                const bool ob = pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
-                if (ob) visit(j + 1, dx, d2);
-                const bool oc = pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2);
-                if (oc) visit(j + 2, dx, d2);
-                const bool od = pair_test<T, D, SHIFT>(xd.v, xi, sh, r2, dx, &d2);
-                if (od) visit(j + 3, dx, d2);
-                rec = (rec << 4) | (oa ? 8u : 0u) | (ob ? 4u : 0u) | (oc ? 2u : 0u) | (od ? 1u : 0u);
-            }
-            for (; j + 1 < jb; j += 2) {
-                const VecN<T, PITCH> xa = load_row<T, PITCH, OFF32>(xs, j);
-                const VecN<T, PITCH> xb = load_row_at<T, PITCH, OFF32>(xs, j, 1);
-                T dx[D], d2;
-                const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
-                if (oa) visit(j, dx, d2);
-                const bool ob = pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
-                if (ob) visit(j + 1, dx, d2);
-                rec = (rec << 2) | (oa ? 2u : 0u) | (ob ? 1u : 0u);
-            }
-            if (j < jb) {
-                const VecN<T, PITCH> xa = load_row<T, PITCH, OFF32>(xs, j);
-                T dx[D], d2;
-                const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
-                if (oa) visit(j, dx, d2);
-                rec = (rec << 1) | (oa ? 1u : 0u);
-            }
-        };
-        // candidates [ja, jb) as scan takes them, read from the wave's LDS window
-        // that holds slots [lo, lo + kWindow) (byte offsets from the window start).
-        // An empty run may lie outside the window (its offsets would wrap), so it
-        // returns at once.
-        auto scan_window = [&](auto shift_tag, uint32_t ja, uint32_t jb, const T* sh, uint64_t& rec,
-                               const char* wb, uint32_t lo) {
-            constexpr bool SHIFT = decltype(shift_tag)::value;
-            constexpr uint32_t RB = (uint32_t)sizeof(VecN<T, PITCH>);
-            if (jb <= ja) return;
-            const uint32_t oend = (jb - lo) * RB;
-            const uint32_t olast = oend >= 3u * RB ? oend - 3u * RB : 0u;
-            uint32_t o = (ja - lo) * RB;
-            uint32_t rlo = (uint32_t)rec, rhi = (uint32_t)(rec >> 32);
-            for (; o < olast; o += 4u * RB) {
-                const char* const pj = wb + o;
-                const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(pj);
-                const VecN<T, PITCH> xb = *reinterpret_cast<const VecN<T, PITCH>*>(pj + RB);
-                const VecN<T, PITCH> xc = *reinterpret_cast<const VecN<T, PITCH>*>(pj + 2u * RB);
-                const VecN<T, PITCH> xd = *reinterpret_cast<const VecN<T, PITCH>*>(pj + 3u * RB);
-                const uint32_t jj = lo + o / RB;
-                // the record moves up four places first; each accepted candidate then
-                // sets its bit inside the branch that adds its summand
-                rhi = (rhi << 4) | (rlo >> 28);
-                rlo <<= 4;
-                T dx[D], d2;
-                if (pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2)) {
-                    visit(jj, dx, d2);
-                    rlo |= 8u;
-                }
-                if (pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2)) {
-                    visit(jj + 1, dx, d2);
-                    rlo |= 4u;
-                }
-                if (pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2)) {
-                    visit(jj + 2, dx, d2);
-                    rlo |= 2u;
-                }
-                if (pair_test<T, D, SHIFT>(xd.v, xi, sh, r2, dx, &d2)) {
-                    visit(jj + 3, dx, d2);
-                    rlo |= 1u;
-                }
-            }
-            rec = ((uint64_t)rhi << 32) | rlo;
-            for (; o + RB < oend; o += 2u * RB) {
-                const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(wb + o);
-                const VecN<T, PITCH> xb = *reinterpret_cast<const VecN<T, PITCH>*>(wb + o + RB);
-                const uint32_t jj = lo + o / RB;
-                T dx[D], d2;
-                const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
-                if (oa) visit(jj, dx, d2);
-                const bool ob = pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
-                if (ob) visit(jj + 1, dx, d2);
-                rec = (rec << 2) | (oa ? 2u : 0u) | (ob ? 1u : 0u);
-            }
-            if (o < oend) {
-                const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(wb + o);
-                T dx[D], d2;
-                const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
-                if (oa) visit(lo + o / RB, dx, d2);
-                rec = (rec << 1) | (oa ? 1u : 0u);
-            }
-        };
-        uint64_t rec = 0;  // the current row's bits, most recent lowest
-        uint32_t pos = 0;  // candidates of the current row so far
-        auto begin_row = [&](int) {
-            rec = 0;
-            pos = 0;
-        };
-        auto piece = [&](uint32_t j0, uint32_t j1, const T* sh) {
-            bool lane_shift = false;
-#pragma unroll
-            for (int k = 0; k < D; ++k) lane_shift |= sh[k] != T(0);
-            j1 = max(j1, j0);
-            if (__ballot(lane_shift) != 0ull) scan(std::integral_constant<bool, true>(), j0, j1, sh, rec);
-            else scan(std::integral_constant<bool, false>(), j0, j1, sh, rec);
-            pos += j1 - j0;
-        };
-        auto end_row = [&](int row) {
-            overflow |= pos > (uint32_t)kMaskBits;
-            // c <= 64 bits shifted in put row position k at bit c - 1 - k;
-            // reversed and shifted down by 64 - c it lands at bit k
-            const uint32_t c = min(pos, (uint32_t)kMaskBits);
-            const uint64_t rev = ((uint64_t)__builtin_bitreverse32((uint32_t)rec) << 32) |
-                                 __builtin_bitreverse32((uint32_t)(rec >> 32));
-            const uint64_t m = c == 0u ? 0ull : rev >> (64u - c);
-            masks[(size_t)(2 * row) * n + s] = (uint32_t)m;
-            masks[(size_t)(2 * row + 1) * n + s] = (uint32_t)(m >> 32);
-        };
-        if constexpr (sizeof(T) == 4 && OFF32) {
-            if (__ballot(P.n[0] < 2 * P.reach[0] + 1) == 0ull) {
-                // Every grid of the wave is at least 2 m + 1 cells wide: each row's main
-                // runs are staged in LDS (below); otherwise the plain walk.
-                auto win_piece = [&](uint32_t j0, uint32_t j1, const T* sh, const char* wb, uint32_t lo) {
-                    j1 = max(j1, j0);
-                    if (__ballot(sh[1] != T(0) || sh[2] != T(0)) != 0ull)
-                        scan_window(std::integral_constant<bool, true>(), j0, j1, sh, rec, wb, lo);
-                    else
-                        scan_window(std::integral_constant<bool, false>(), j0, j1, sh, rec, wb, lo);
-                    pos += j1 - j0;
-                };
-                staged_rows<T, D, 0>(P, off, n, xi, xs, nullptr, wave_wb, begin_row, piece, end_row, win_piece, row_done,
-                                     w.range);
-            } else {
-                for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
-            }
-        } else {
-            for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
-        }
-        if (SPLIT && split > 1) row_ovf[w.wave * 64] = overflow ? 1u : 0u;
-      }
-      if (!ws.finish(w, n)) return;
-      if (SPLIT && split > 1)
-          for (int32_t q = 0; q < split; ++q) overflow |= row_ovf[q * 64] != 0u;
-      status[s] = overflow ? kGenNone : gen[0];
-      const uint32_t o = perm[s];
-#pragma unroll
-      for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = sums.tot[k];
-    } else {
-      if (s < n) {
-        const SysParams<T> P = sp[b];
-        T xi[D];
-        load_point<T, D>(xs, s, xi);
-        const T ai = NA ? a_s[s] : T(0);
-        const T r = P.r, r2 = P.r2;
-        T gyi[NY];
-        load_gy<T, NY, OFF32>(gy_s, s, gyi);
-        T* const accx = acc;
-        T* const acca = acc + (NA ? D : 0);
-        auto pair = [&](uint32_t j, const T* dx, T d2, const T* gyj) {
-            const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
-            Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
-        };
-        // the accepted pairs of one piece, bits64 bit k = its k-th slot from j0: popped
-        // three per iteration (their loads overlap), each 32-bit half of the piece's
-        // record in turn (one-word bit operations), from HBM or, with WIN, from the
-        // wave's LDS window, whose xs rows for slots [lo, lo + kWindow) are followed
-        // by the gy rows of the same slots
-        auto replay_s = [&](auto win_tag, auto shift_tag, uint32_t j0, uint64_t bits64, const T* sh, const char* wb,
-                            uint32_t lo) {
-            constexpr bool WIN = decltype(win_tag)::value;
-            constexpr bool SHIFT = decltype(shift_tag)::value;
-            constexpr uint32_t RBX = (uint32_t)sizeof(VecN<T, PITCH>), RBG = (uint32_t)sizeof(VecN<T, GP>);
-#pragma unroll 1
-            for (uint32_t h = 0; h < 2u; ++h) {
-                uint32_t bits = h ? (uint32_t)(bits64 >> 32) : (uint32_t)bits64;
-                const uint32_t base = j0 + 32u * h;
-                // rows of the half's bit k: slot base + k, at window row base - lo + k
-                // (the window addresses of bit 0 formed once per half)
-                const char* const px = wb + (base - lo) * RBX;
-                const char* const pg = wb + (uint32_t)kWindow * RBX + (base - lo) * RBG;
-                auto ldx = [&](uint32_t k) {
-                    if constexpr (WIN) return *reinterpret_cast<const VecN<T, PITCH>*>(px + k * RBX);
-                    else return load_row<T, PITCH, OFF32>(xs, base + k);
-                };
-                auto ldg = [&](uint32_t k) {
-                    if constexpr (WIN) return *reinterpret_cast<const VecN<T, GP>*>(pg + k * RBG);
-                    else return load_row<T, GP, OFF32>(gy_s, base + k);
-                };
-                while (bits != 0u) {
-                    const uint32_t ka = (uint32_t)__builtin_ctz(bits);
-                    bits &= bits - 1u;
-                    const bool vb = bits != 0u;
-                    const uint32_t kb = vb ? (uint32_t)__builtin_ctz(bits) : ka;
-                    bits &= bits - 1u;
-                    const bool vc = bits != 0u;
-                    const uint32_t kc = vc ? (uint32_t)__builtin_ctz(bits) : ka;
-                    bits &= bits - 1u;
-                    const VecN<T, PITCH> xa = ldx(ka);
-                    const VecN<T, GP> ga_ = ldg(ka);
-                    const VecN<T, PITCH> xb = ldx(kb);
-                    const VecN<T, GP> gb_ = ldg(kb);
-                    const VecN<T, PITCH> xc = ldx(kc);
-                    const VecN<T, GP> gc_ = ldg(kc);
+                rec = ((uint64_t)rhi << 32) | rlo;
+                for (; o + RB < oend; o += 2u * RB) {
+                    const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(wb + o);
+                    const VecN<T, PITCH> xb = *reinterpret_cast<const VecN<T, PITCH>*>(wb + o + RB);
+                    const uint32_t jj = lo + o / RB;
                     T dx[D], d2;
-                    (void)pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
-                    pair(base + ka, dx, d2, ga_.v);
-                    keep_issued<D>(xb.v);
-                    keep_issued<NY>(gb_.v);
-                    keep_issued<D>(xc.v);
-                    keep_issued<NY>(gc_.v);
-                    if (vb) {
-                        (void)pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
-                        pair(base + kb, dx, d2, gb_.v);
-                    }
-                    if (vc) {
-                        (void)pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2);
-                        pair(base + kc, dx, d2, gc_.v);
-                    }
+                    const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
+                    if (oa) visit(jj, dx, d2);
+                    const bool ob = pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
+                    if (ob) visit(jj + 1, dx, d2);
+                    rec = (rec << 2) | (oa ? 2u : 0u) | (ob ? 1u : 0u);
                 }
-            }
-        };
-        // the image shift's adds only where some lane of the wave needs them
-        auto replay = [&](auto win_tag, uint32_t j0, uint64_t bits64, const T* sh, const char* wb, uint32_t lo) {
-            bool lane_shift = false;
-#pragma unroll
-            for (int k = 0; k < D; ++k) lane_shift |= sh[k] != T(0);
-            if (__ballot(lane_shift) != 0ull)
-                replay_s(win_tag, std::integral_constant<bool, true>(), j0, bits64, sh, wb, lo);
-            else
-                replay_s(win_tag, std::integral_constant<bool, false>(), j0, bits64, sh, wb, lo);
-        };
-        if (status[s] == gen[0]) {
-            uint64_t m = 0;    // the current row's record
-            uint32_t pos = 0;  // row position of the next piece's first candidate
-            auto begin_row = [&](int row) {
-                m = (uint64_t)masks[(size_t)(2 * row) * n + s] | ((uint64_t)masks[(size_t)(2 * row + 1) * n + s] << 32);
+                if (o < oend) {
+                    const VecN<T, PITCH> xa = *reinterpret_cast<const VecN<T, PITCH>*>(wb + o);
+                    T dx[D], d2;
+                    const bool oa = pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
+                    if (oa) visit(lo + o / RB, dx, d2);
+                    rec = (rec << 1) | (oa ? 1u : 0u);
+                }
+            };
+            uint64_t rec = 0;  // the current row's bits, most recent lowest
+            uint32_t pos = 0;  // candidates of the current row so far
+            auto begin_row = [&](int) {
+                rec = 0;
                 pos = 0;
             };
-            // the record's bits of the piece [j0, j1) (a piece past 64 candidates keeps none)
-            auto piece_bits = [&](uint32_t j0, uint32_t j1) {
-                const uint32_t len = j1 > j0 ? j1 - j0 : 0u;
-                uint64_t bits = pos < 64u ? m >> pos : 0ull;
-                if (len < 64u) bits &= (1ull << len) - 1ull;
-                pos += len;
-                return bits;
-            };
             auto piece = [&](uint32_t j0, uint32_t j1, const T* sh) {
-                const uint64_t bits = piece_bits(j0, j1);
-                replay(std::integral_constant<bool, false>(), j0, bits, sh, nullptr, 0u);
+                bool lane_shift = false;
+#pragma unroll
+                for (int k = 0; k < D; ++k) lane_shift |= sh[k] != T(0);
+                j1 = max(j1, j0);
+                if (__ballot(lane_shift) != 0ull) scan(std::integral_constant<bool, true>(), j0, j1, sh, rec);
+                else scan(std::integral_constant<bool, false>(), j0, j1, sh, rec);
+                pos += j1 - j0;
             };
-            auto end_row = [&](int) {};
+            auto end_row = [&](int row) {
+                overflow |= pos > (uint32_t)kMaskBits;
+                // c <= 64 bits shifted in put row position k at bit c - 1 - k;
+                // reversed and shifted down by 64 - c it lands at bit k
+                const uint32_t c = min(pos, (uint32_t)kMaskBits);
+                const uint64_t rev = ((uint64_t)__builtin_bitreverse32((uint32_t)rec) << 32) |
+                                     __builtin_bitreverse32((uint32_t)(rec >> 32));
+                const uint64_t m = c == 0u ? 0ull : rev >> (64u - c);
+                masks[(size_t)(2 * row) * n + s] = (uint32_t)m;
+                masks[(size_t)(2 * row + 1) * n + s] = (uint32_t)(m >> 32);
+            };
             if constexpr (sizeof(T) == 4 && OFF32) {
                 if (__ballot(P.n[0] < 2 * P.reach[0] + 1) == 0ull) {
-                    // as in the forward: each row's main runs from the wave's LDS window
-                    // (positions, then the gy rows)
-                    staged_rows<T, D, GP>(P, off, n, xi, xs, gy_s, wave_wb, begin_row, piece, end_row,
-                                          [&](uint32_t j0, uint32_t j1, const T* sh, const char* wb, uint32_t lo) {
-                                              const uint64_t bits = piece_bits(j0, j1);
-                                              replay(std::integral_constant<bool, true>(), j0, bits, sh, wb, lo);
-                                          },
-                                          row_done, w.range);
+                    // Every grid of the wave is at least 2 m + 1 cells wide: each row's main
+                    // runs are staged in LDS (below); otherwise the plain walk.
+                    auto win_piece = [&](uint32_t j0, uint32_t j1, const T* sh, const char* wb, uint32_t lo) {
+                        j1 = max(j1, j0);
+                        if (__ballot(sh[1] != T(0) || sh[2] != T(0)) != 0ull)
+                            scan_window(std::integral_constant<bool, true>(), j0, j1, sh, rec, wb, lo);
+                        else
+                            scan_window(std::integral_constant<bool, false>(), j0, j1, sh, rec, wb, lo);
+                        pos += j1 - j0;
+                    };
+                    staged_rows<T, D, 0>(P, off, n, xi, xs, nullptr, wave_wb, begin_row, piece, end_row, win_piece, row_done,
+                                         w.range);
                 } else {
                     for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
                 }
             } else {
                 for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
             }
-        } else {
-            // no record: the plain row search (not its deferred form, whose
-            // registers would lower the replay's occupancy)
-            auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
-                const VecN<T, GP> gj = load_row<T, GP, OFF32>(gy_s, j);
-                pair(j, dx, d2, gj.v);
-            };
-            neighbour_loop<T, D, OFF32>(P, xs, off, n, xi, visit, row_done, w.range);
+            if (SPLIT && split > 1) row_ovf[w.wave * 64] = overflow ? 1u : 0u;
         }
-      }
-      if (!ws.finish(w, n)) return;
-      const uint32_t o = perm[s];
+        if (!ws.finish(w, n)) return;
+        if (SPLIT && split > 1)
+            for (int32_t q = 0; q < split; ++q) overflow |= row_ovf[q * 64] != 0u;
+        status[s] = overflow ? kGenNone : gen[0];
+        const uint32_t o = perm[s];
 #pragma unroll
-      for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = sums.tot[k];
-      if (NA && ga) ga[o] = sums.tot[D + NA - 1];
+        for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = sums.tot[k];
+    } else {
+        if (s < n) {
+            const SysParams<T> P = sp[b];
+            T xi[D];
+            load_point<T, D>(xs, s, xi);
+            const T ai = NA ? a_s[s] : T(0);
+            const T r = P.r, r2 = P.r2;
+            T gyi[NY];
+            load_gy<T, NY, OFF32>(gy_s, s, gyi);
+            T* const accx = acc;
+            T* const acca = acc + (NA ? D : 0);
+            auto pair = [&](uint32_t j, const T* dx, T d2, const T* gyj) {
+                const T aj = OpShape<OP, D>::NA ? load_row<T, 1, OFF32>(a_s, j).v[0] : T(0);
+                Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
+            };
+            // the accepted pairs of one piece, bits64 bit k = its k-th slot from j0: popped
+            // three per iteration (their loads overlap), each 32-bit half of the piece's
+            // record in turn (one-word bit operations), from HBM or, with WIN, from the
+            // wave's LDS window, whose xs rows for slots [lo, lo + kWindow) are followed
+            // by the gy rows of the same slots
+            auto replay_s = [&](auto win_tag, auto shift_tag, uint32_t j0, uint64_t bits64, const T* sh, const char* wb,
+                                uint32_t lo) {
+                constexpr bool WIN = decltype(win_tag)::value;
+                constexpr bool SHIFT = decltype(shift_tag)::value;
+                constexpr uint32_t RBX = (uint32_t)sizeof(VecN<T, PITCH>), RBG = (uint32_t)sizeof(VecN<T, GP>);
+#pragma unroll 1
+                for (uint32_t h = 0; h < 2u; ++h) {
+                    uint32_t bits = h ? (uint32_t)(bits64 >> 32) : (uint32_t)bits64;
+                    const uint32_t base = j0 + 32u * h;
+                    // rows of the half's bit k: slot base + k, at window row base - lo + k
+                    // (the window addresses of bit 0 formed once per half)
+                    const char* const px = wb + (base - lo) * RBX;
+                    const char* const pg = wb + (uint32_t)kWindow * RBX + (base - lo) * RBG;
+                    auto ldx = [&](uint32_t k) {
+                        if constexpr (WIN) return *reinterpret_cast<const VecN<T, PITCH>*>(px + k * RBX);
+                        else return load_row<T, PITCH, OFF32>(xs, base + k);
+                    };
+                    auto ldg = [&](uint32_t k) {
+                        if constexpr (WIN) return *reinterpret_cast<const VecN<T, GP>*>(pg + k * RBG);
+                        else return load_row<T, GP, OFF32>(gy_s, base + k);
+                    };
+                    while (bits != 0u) {
+                        const uint32_t ka = (uint32_t)__builtin_ctz(bits);
+                        bits &= bits - 1u;
+                        const bool vb = bits != 0u;
+                        const uint32_t kb = vb ? (uint32_t)__builtin_ctz(bits) : ka;
+                        bits &= bits - 1u;
+                        const bool vc = bits != 0u;
+                        const uint32_t kc = vc ? (uint32_t)__builtin_ctz(bits) : ka;
+                        bits &= bits - 1u;
+                        const VecN<T, PITCH> xa = ldx(ka);
+                        const VecN<T, GP> ga_ = ldg(ka);
+                        const VecN<T, PITCH> xb = ldx(kb);
+                        const VecN<T, GP> gb_ = ldg(kb);
+                        const VecN<T, PITCH> xc = ldx(kc);
+                        const VecN<T, GP> gc_ = ldg(kc);
+                        T dx[D], d2;
+                        (void)pair_test<T, D, SHIFT>(xa.v, xi, sh, r2, dx, &d2);
+                        pair(base + ka, dx, d2, ga_.v);
+                        keep_issued<D>(xb.v);
+                        keep_issued<NY>(gb_.v);
+                        keep_issued<D>(xc.v);
+                        keep_issued<NY>(gc_.v);
+                        if (vb) {
+                            (void)pair_test<T, D, SHIFT>(xb.v, xi, sh, r2, dx, &d2);
+                            pair(base + kb, dx, d2, gb_.v);
+                        }
+                        if (vc) {
+                            (void)pair_test<T, D, SHIFT>(xc.v, xi, sh, r2, dx, &d2);
+                            pair(base + kc, dx, d2, gc_.v);
+                        }
+                    }
+                }
+            };
+            // the image shift's adds only where some lane of the wave needs them
+            auto replay = [&](auto win_tag, uint32_t j0, uint64_t bits64, const T* sh, const char* wb, uint32_t lo) {
+                bool lane_shift = false;
+#pragma unroll
+                for (int k = 0; k < D; ++k) lane_shift |= sh[k] != T(0);
+                if (__ballot(lane_shift) != 0ull)
+                    replay_s(win_tag, std::integral_constant<bool, true>(), j0, bits64, sh, wb, lo);
+                else
+                    replay_s(win_tag, std::integral_constant<bool, false>(), j0, bits64, sh, wb, lo);
+            };
+            if (status[s] == gen[0]) {
+                uint64_t m = 0;    // the current row's record
+                uint32_t pos = 0;  // row position of the next piece's first candidate
+                auto begin_row = [&](int row) {
+                    m = (uint64_t)masks[(size_t)(2 * row) * n + s] | ((uint64_t)masks[(size_t)(2 * row + 1) * n + s] << 32);
+                    pos = 0;
+                };
+                // the record's bits of the piece [j0, j1) (a piece past 64 candidates keeps none)
+                auto piece_bits = [&](uint32_t j0, uint32_t j1) {
+                    const uint32_t len = j1 > j0 ? j1 - j0 : 0u;
+                    uint64_t bits = pos < 64u ? m >> pos : 0ull;
+                    if (len < 64u) bits &= (1ull << len) - 1ull;
+                    pos += len;
+                    return bits;
+                };
+                auto piece = [&](uint32_t j0, uint32_t j1, const T* sh) {
+                    const uint64_t bits = piece_bits(j0, j1);
+                    replay(std::integral_constant<bool, false>(), j0, bits, sh, nullptr, 0u);
+                };
+                auto end_row = [&](int) {};
+                if constexpr (sizeof(T) == 4 && OFF32) {
+                    if (__ballot(P.n[0] < 2 * P.reach[0] + 1) == 0ull) {
+                        // as in the forward: each row's main runs from the wave's LDS window
+                        // (positions, then the gy rows)
+                        staged_rows<T, D, GP>(P, off, n, xi, xs, gy_s, wave_wb, begin_row, piece, end_row,
+                                              [&](uint32_t j0, uint32_t j1, const T* sh, const char* wb, uint32_t lo) {
+                                                  const uint64_t bits = piece_bits(j0, j1);
+                                                  replay(std::integral_constant<bool, true>(), j0, bits, sh, wb, lo);
+                                              },
+                                              row_done, w.range);
+                    } else {
+                        for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
+                    }
+                } else {
+                    for_each_piece<T, D>(P, off, n, xi, begin_row, piece, end_row, row_done, w.range);
+                }
+            } else {
+                // no record: the plain row search (not its deferred form, whose
+                // registers would lower the replay's occupancy)
+                auto visit = [&](uint32_t j, const T* dx, T d2, bool) {
+                    const VecN<T, GP> gj = load_row<T, GP, OFF32>(gy_s, j);
+                    pair(j, dx, d2, gj.v);
+                };
+                neighbour_loop<T, D, OFF32>(P, xs, off, n, xi, visit, row_done, w.range);
+            }
+        }
+        if (!ws.finish(w, n)) return;
+        const uint32_t o = perm[s];
+#pragma unroll
+        for (int k = 0; k < D; ++k) gx[(size_t)o * D + k] = sums.tot[k];
+        if (NA && ga) ga[o] = sums.tot[D + NA - 1];
     }
 }
 
