@@ -483,17 +483,18 @@ KernelPlan plan_kernel(int kernel, double prm) {
     return k;
 }
 
-// Gives the context's scratch need bytes; false where it has fewer and a capture is in
-// progress (nothing is allocated then) or the device has none left.  A graph may hold
-// scratch that was there when it was captured: that is kept until the context goes.
-bool grow_scratch(aboria_ctx* ctx, size_t need) {
+// Gives the context's scratch need bytes.  UNSUPPORTED where it has fewer and a capture is
+// in progress (nothing is allocated then), OUT_OF_MEMORY where the device has none left; no
+// message, since a caller may have a form that needs less.  A graph may hold scratch that
+// was there when it was captured: that is kept until the context goes.
+aboria_status grow_scratch(aboria_ctx* ctx, size_t need) {
     if (ctx->scratch_bytes < need) {
-        if (ctx->capturing) return false;
+        if (ctx->capturing) return ABORIA_ERR_UNSUPPORTED;
         if (ctx->scratch) {
             if (ctx->scratch_in_graph) {
                 ctx->scratch_held.push_back(ctx->scratch);
             } else {
-                if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+                ABORIA_HIP(ctx, hipStreamSynchronize(ctx->stream));
                 (void)hipFree(ctx->scratch);
             }
             ctx->scratch = nullptr;
@@ -503,19 +504,20 @@ bool grow_scratch(aboria_ctx* ctx, size_t need) {
         if (hipMalloc(&ctx->scratch, need) != hipSuccess) {
             (void)hipGetLastError();
             ctx->scratch = nullptr;
-            return false;
+            return ABORIA_ERR_OUT_OF_MEMORY;
         }
         ctx->scratch_bytes = need;
     }
     ctx->scratch_in_graph |= ctx->capturing;
-    return true;
+    return ABORIA_OK;
 }
 
 aboria_status ensure_scratch(aboria_ctx* ctx, size_t need) {
-    if (grow_scratch(ctx, need)) return ABORIA_OK;
-    if (ctx->capturing)
-        return fail(ctx, ABORIA_ERR_UNSUPPORTED, "dense scratch must be sized by an uncaptured call first");
-    return fail(ctx, ABORIA_ERR_OUT_OF_MEMORY, "dense scratch allocation failed");
+    const aboria_status st = grow_scratch(ctx, need);
+    if (st == ABORIA_ERR_UNSUPPORTED)
+        return fail(ctx, st, "dense scratch must be sized by an uncaptured call first");
+    if (st == ABORIA_ERR_OUT_OF_MEMORY) return fail(ctx, st, "dense scratch allocation failed");
+    return st;
 }
 
 // Device address of this GPU's copy of the no-allocation scratch array, looked
@@ -664,7 +666,7 @@ aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint3
         nsplit = (steps + per_split - 1) / per_split;
         const size_t need = bytes_s + split_bytes * nsplit;
         const size_t passes = std::max(a.split_bytes * a.nsplit, b.split_bytes * b.nsplit);
-        if (fits && grow_scratch(ctx, ctx->capturing ? need : std::max(need, passes))) {
+        if (fits && grow_scratch(ctx, ctx->capturing ? need : std::max(need, passes)) == ABORIA_OK) {
             T* ps = (T*)ctx->scratch;
             T* pt = (T*)((char*)ctx->scratch + bytes_s);
             const DensePairJob<T> jb{(const T*)xt, (const T*)xs, (const T*)w, (const T*)gy, pt, ps, nt, ns,
@@ -694,7 +696,7 @@ aboria_status launch_adjoint(aboria_ctx* ctx, uint32_t nt, const void* xt, uint3
     const size_t bytes_a = (a.split_bytes * a.nsplit + 255) & ~(size_t)255;
     const size_t need = bytes_a + b.split_bytes * b.nsplit;
     // one kernel holds one target count per lane
-    *done = a.ti == b.ti && need <= kAdjointScratch && grow_scratch(ctx, need);
+    *done = a.ti == b.ti && need <= kAdjointScratch && grow_scratch(ctx, need) == ABORIA_OK;
     if (!*done) return ABORIA_OK;
     T* pa = (T*)ctx->scratch;
     T* pb = (T*)((char*)ctx->scratch + bytes_a);
