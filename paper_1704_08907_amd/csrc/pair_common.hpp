@@ -741,29 +741,34 @@ struct RowSums {
     }
 };
 
-// RowSums of a search kernel; with split > 1 the first wave adds its rows' sums up and the
-// others leave theirs in LDS ([row][NV][64]) for it: what LDS that takes decides how many
-// workgroups of three waves a CU holds (the fused kernel with variables, 3-d float32: 28 KB
-// with every row's sums, 23 so; float64 57 and 46).
+// RowSums of a search kernel; with split > 1 the rows' sums go to LDS ([row][NV][64]), for
+// the first wave to add up.  With many sums that LDS decides how many workgroups of three
+// waves a CU holds (the fused kernel with variables, 3-d float32: 28 KB, float64 57): there
+// the first wave adds its own rows' sums up in registers and leaves them out of it (23 and
+// 46 KB; 300007 particles with 30 neighbours 109 -> 94 us).  With few it costs the wave more
+// than it gives (soft sphere, 2^18, forward 49.0 -> 50.0).
 template <typename T, int D, int NV, bool SPLIT>
 struct WaveSums {
     RowSums<T, NV> sums;
     int32_t split, wave;
     char* part;
+    static constexpr bool kKeep = NV >= 6 || (sizeof(T) == 8 && NV >= 4);
+    // rows whose sums the first wave keeps
+    __host__ __device__ static constexpr int32_t kept_rows(int32_t sp) { return kKeep ? kStencilRows<D> / sp : 0; }
     __host__ __device__ static constexpr uint32_t part_bytes(int32_t sp) {
-        return SPLIT && sp > 1 ? (uint32_t)(kStencilRows<D> - kStencilRows<D> / sp) * NV * 64u * (uint32_t)sizeof(T) : 0u;
+        return SPLIT && sp > 1 ? (uint32_t)(kStencilRows<D> - kept_rows(sp)) * NV * 64u * (uint32_t)sizeof(T) : 0u;
     }
 
     __device__ __forceinline__ WaveSums(int32_t sp, int32_t w, char* part_lds)
         : sums(SPLIT), split(sp), wave(w), part(part_lds) {}
     __device__ __forceinline__ void row_done(int32_t row) {
         if constexpr (SPLIT) {
-            if (split == 1 || wave == 0) {
+            if (split == 1 || (kKeep && wave == 0)) {
                 sums.row_done();
                 return;
             }
             constexpr int32_t R = kStencilRows<D>;
-            T* const p = reinterpret_cast<T*>(part) + (min(row, R - 1) - R / split) * NV * 64 + (threadIdx.x & 63u);
+            T* const p = reinterpret_cast<T*>(part) + (min(row, R - 1) - kept_rows(split)) * NV * 64 + (threadIdx.x & 63u);
 #pragma unroll
             for (int k = 0; k < NV; ++k) {
                 p[k * 64] = row < R ? sums.acc[k] : p[k * 64] + sums.acc[k];
@@ -777,7 +782,7 @@ struct WaveSums {
         if (SPLIT && split > 1) {
             __syncthreads();
             if (w.wave != 0) return false;
-            for (int32_t row = 0; row < kStencilRows<D> - kStencilRows<D> / split; ++row)
+            for (int32_t row = 0; row < kStencilRows<D> - kept_rows(split); ++row)
 #pragma unroll
                 for (int k = 0; k < NV; ++k)
                     sums.tot[k] += reinterpret_cast<const T*>(part)[(row * NV + k) * 64 + (threadIdx.x & 63u)];
