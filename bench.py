@@ -114,7 +114,7 @@ def profile_names(variant_name, direction):
     """Kernel names as rocprofv3 reports them for the spring cube (float32, d = 3, no batch,
     32-bit row offsets, one wave for all rows of its particles)."""
     if "recorded" in variant_name:
-        k = ["k_nbr_fwd<float, 3, 1, false>"] if direction == "fwd" else ["k_nbr_bwd<float, 3, 1, false>"]
+        k = ["k_nbr_fwd<float, 3, 1, false, false>"] if direction == "fwd" else ["k_nbr_bwd<float, 3, 1, false, false>"]
     elif "accepted-pair bit masks" in variant_name:
         k = ["k_lane_mask<float, 3, 1, false, true, %d, false>" % (0 if direction == "fwd" else 1)]
     elif "flattened" in variant_name:
