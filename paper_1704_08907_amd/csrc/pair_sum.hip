@@ -322,7 +322,9 @@ uint64_t row_sum_waves(const aboria_cells* c) {
     const bool f64 = c->dtype == ABORIA_F64;
     if (f64 && c->d == 3) return 1600;
     if (c->nsys > 1) return f64 ? 2500 : 3000;
-    const double per_cell = (double)c->n / (double)std::max<int64_t>(c->ncells, 1);
+    // in a cell one cutoff wide, also where the grid's cells are a fraction of it in x: a row
+    // is the same run of candidates there, and the lines lie at the same sizes
+    const double per_cell = (double)c->n / (double)std::max<int64_t>(c->ncells, 1) * max_reach(c, 0);
     if (per_cell < 4.0) return 3500;
     return per_cell >= 10.0 ? 10000 : (c->d == 3 ? 4200 : 6500);
 }
