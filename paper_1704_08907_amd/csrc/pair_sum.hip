@@ -317,7 +317,8 @@ int32_t row_waves(const aboria_cells* c) {
 // float32 in 3-d 190000 0.96 (0.83), 262144 1.14 (0.92), in 2-d 190000 1.04 (0.97), of
 // float64 in 2-d 160000 0.97 (0.88), 190000 1.10 (0.97); cells of fewer than four 224000 1.02
 // (0.99), 300007 1.10 (1.09); of four to ten in 3-d 262144 1.01 (0.86), 300007 1.09 (0.94),
-// in 2-d 400000 1.00 (0.99), 500000 1.04 (1.00); of ten and more 500000 1.03 (0.90).
+// in 2-d 400000 1.00 (0.99), 500000 1.04 (1.00); of ten and more 640000 1.00 (0.88) but for
+// the DEM spring's replay, 1.10.
 uint64_t row_sum_waves(const aboria_cells* c) {
     const bool f64 = c->dtype == ABORIA_F64;
     if (f64 && c->d == 3) return 1600;
