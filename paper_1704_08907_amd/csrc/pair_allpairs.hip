@@ -13,13 +13,14 @@ namespace aboria {
 // tens of thousands of lanes even for a few hundred particles): lane l of a
 // group takes slots l, l + G, ... of the system; the group's partial sums are
 // combined by a fixed butterfly and its first lane writes the result.
-template <typename T, int D, int OP, bool BATCH, int G, bool DIRECT>
+template <typename T, int D, int OP, bool BATCH, int G, bool EAGER>
 __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const uint32_t* __restrict__ perm,
                                                  uint32_t n, const SysParams<T>* __restrict__ sp,
                                                  const uint32_t* __restrict__ sys_part, int nsys,
                                                  const T* __restrict__ a_s, OpArgs<T> q, T* __restrict__ y) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
+    constexpr bool DIRECT = G == 64;  // (all_direct)
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x / G);
     const uint32_t s = first + threadIdx.x / G;
     const uint32_t lane = threadIdx.x % G;
@@ -37,11 +38,11 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
     const T r = P.r;
     constexpr int NA = OpShape<OP, D>::NA;
     auto visit = [&](uint32_t j, const T* dx, T d2, const T*, T aj) {
-        if constexpr (NA > 0 && !DIRECT) aj = a_s[j];
+        if constexpr (NA > 0 && !EAGER) aj = a_s[DIRECT ? perm[j] : j];
         Op::fwd(q, r, dx, d2, ai, aj, acc);
     };
     if (live)
-        allpairs_loop<T, D, 0, NA, DIRECT>(P, xs, (const T*)nullptr, a_s, perm, P.part_base + lane, P.part_end, G, xi,
+        allpairs_loop<T, D, 0, NA, EAGER>(P, xs, (const T*)nullptr, a_s, perm, P.part_base + lane, P.part_end, G, xi,
                                            visit);
 #pragma unroll
     for (int k = 0; k < NY; ++k) acc[k] = group_reduce<G>(acc[k]);
@@ -51,7 +52,7 @@ __global__ __launch_bounds__(256) void k_all_fwd(const T* __restrict__ xs, const
     for (int k = 0; k < NY; ++k) y[(size_t)o * NY + k] = acc[k];
 }
 
-template <typename T, int D, int OP, bool BATCH, int G, bool DIRECT>
+template <typename T, int D, int OP, bool BATCH, int G, bool EAGER>
 __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const uint32_t* __restrict__ perm,
                                                  uint32_t n, const SysParams<T>* __restrict__ sp,
                                                  const uint32_t* __restrict__ sys_part, int nsys,
@@ -59,6 +60,7 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
                                                  OpArgs<T> q, T* __restrict__ gx, T* __restrict__ ga) {
     using Op = PairOp<T, D, OP>;
     constexpr int NY = Op::NY;
+    constexpr bool DIRECT = G == 64;  // (all_direct)
     const uint32_t first = xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x / G);
     const uint32_t s = first + threadIdx.x / G;
     const uint32_t lane = threadIdx.x % G;
@@ -82,17 +84,23 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
     for (int k = 0; k < D; ++k) accx[k] = T(0);
     const T r = P.r;
     auto visit = [&](uint32_t j, const T* dx, T d2, const T* gyj, T aj) {
-        if constexpr (DIRECT) {
+        if constexpr (EAGER) {
             Op::bwd(q, r, dx, d2, ai, aj, gyi, gyj, accx, acca);
         } else {
-            if constexpr (OpShape<OP, D>::NA > 0) aj = a_s[j];
+            const uint32_t p = DIRECT ? perm[j] : j;
+            if constexpr (OpShape<OP, D>::NA > 0) aj = a_s[p];
             T g[NY];
-            load_gy<T, NY>(gy_s, j, g);
+            if constexpr (DIRECT) {
+#pragma unroll
+                for (int k = 0; k < NY; ++k) g[k] = gy_s[(size_t)p * NY + k];
+            } else {
+                load_gy<T, NY>(gy_s, j, g);
+            }
             Op::bwd(q, r, dx, d2, ai, aj, gyi, g, accx, acca);
         }
     };
     if (live)
-        allpairs_loop<T, D, NY, OpShape<OP, D>::NA, DIRECT>(P, xs, gy_s, a_s, perm, P.part_base + lane, P.part_end, G,
+        allpairs_loop<T, D, NY, OpShape<OP, D>::NA, EAGER>(P, xs, gy_s, a_s, perm, P.part_base + lane, P.part_end, G,
                                                             xi, visit);
 #pragma unroll
     for (int k = 0; k < D; ++k) accx[k] = group_reduce<G>(accx[k]);
@@ -105,16 +113,16 @@ __global__ __launch_bounds__(256) void k_all_bwd(const T* __restrict__ xs, const
 }
 
 template <typename T, int D, int OP, bool BATCH>
-void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, bool direct) {
+void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, bool eager) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const int G = all_group(n);
     const dim3 grid((uint32_t)(((uint64_t)n * G + 255) / 256));
-#define L(GG, DI) hipLaunchKernelGGL((k_all_fwd<T, D, OP, BATCH, GG, DI>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
+#define L(GG, EA) hipLaunchKernelGGL((k_all_fwd<T, D, OP, BATCH, GG, EA>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
                                  c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, q, y)
     switch (G) {
         case 64:
-            if (direct) L(64, true);
+            if (eager) L(64, true);
             else L(64, false);
             break;
         case 16: L(16, false); break;
@@ -126,16 +134,16 @@ void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, 
 
 template <typename T, int D, int OP, bool BATCH>
 void launch_all_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
-                    T* ga, bool direct) {
+                    T* ga, bool eager) {
     const uint32_t n = (uint32_t)c->n;
     const SysParams<T>* sp = reinterpret_cast<const SysParams<T>*>(c->params_dev);
     const int G = all_group(n);
     const dim3 grid((uint32_t)(((uint64_t)n * G + 255) / 256));
-#define L(GG, DI) hipLaunchKernelGGL((k_all_bwd<T, D, OP, BATCH, GG, DI>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
+#define L(GG, EA) hipLaunchKernelGGL((k_all_bwd<T, D, OP, BATCH, GG, EA>), grid, dim3(256), 0, ctx->stream, (const T*)c->xs, \
                                  c->perm, n, sp, c->sys_part_dev, c->nsys, a_s, gy_s, q, gx, ga)
     switch (G) {
         case 64:
-            if (direct) L(64, true);
+            if (eager) L(64, true);
             else L(64, false);
             break;
         case 16: L(16, false); break;

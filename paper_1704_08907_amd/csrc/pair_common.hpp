@@ -1034,8 +1034,7 @@ __device__ __forceinline__ void flat_loop(const SysParams<T>& P, const T* __rest
 // 6.1), but eight loads for systems of three cost more than their two rounds (20000 of
 // them, forward 7.7 / 9.2 us).  With EAGER every candidate's gradient row (NAUX, unpadded)
 // and variable (NA) come with its position, read through perm from the caller's order;
-// without, visit reads an accepted one's itself (gyj null): of 2000 particles in 3-d, with
-// 32 candidates a lane, few are accepted (float64 adjoint 19.9 against 26.5).
+// without, visit reads an accepted one's itself (gyj null; all_eager).
 template <typename T, int D, int NAUX, int NA, bool EAGER, typename Visit>
 __device__ __forceinline__ void allpairs_loop(const SysParams<T>& P, const T* __restrict__ xs,
                                               const T* __restrict__ aux, const T* __restrict__ a_s,
@@ -1284,20 +1283,23 @@ inline int all_group(uint64_t n) {
     if (n < want) return 4;
     return 1;
 }
-// Below that size for a wave, and with at most 16 candidates a lane (systems of 1024), the
-// all-pairs kernels read gradients and variables in the caller's order, through perm, with
-// every candidate: gathering them into cell order first costs a launch (1000 particles, 2 us
-// and as much on the host).  Larger systems: 2048 in 2-d, float32 adjoint 12.6 gathered, 14.4
-// direct, in 3-d float64 with variables 18.3 / 26.1.
-inline bool all_direct(uint64_t n, int64_t largest) { return all_group(n) == 64 && largest <= 1024; }
+// Below that size for a wave the all-pairs kernels read gradients and variables in the
+// caller's order, through perm: gathering them into cell order first costs a launch (1000
+// particles, 2 us and as much on the host).
+inline bool all_direct(uint64_t n) { return all_group(n) == 64; }
+// They come with every candidate where a lane has at most 16 (systems of 1024), else of the
+// accepted ones alone.  Adjoint, us, every candidate's / accepted ones' / gathered: 2-d
+// float32 1100 particles 11.1 / 7.3 / 9.5, 2048 14.3 / 9.4 / 11.5; 3-d float64 with variables
+// 2048 25.0 / 14.6 / 16.7; below 500 the accepted ones' alone are up to 10 % slower.
+inline bool all_eager(int64_t largest) { return largest <= 1024; }
 
 // Forward / adjoint over every particle of the lane's system (minimum image); a_s and
 // gy_s in cell order, or with all_direct in the caller's.
 template <typename T, int D, int OP, bool BATCH>
-void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, bool direct);
+void launch_all_fwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, T* y, bool eager);
 template <typename T, int D, int OP, bool BATCH>
 void launch_all_bwd(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>& q, const T* a_s, const T* gy_s, T* gx,
-                    T* ga, bool direct);
+                    T* ga, bool eager);
 
 #define ABORIA_FOR_EACH_PAIR_INSTANCE(X)                                                            \
     X(float, 1, 0, false) X(float, 1, 1, false) X(float, 1, 2, false)                     \

@@ -167,7 +167,7 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 // True where a sum reads its variables and gradients in the caller's order.
 bool direct_inputs(const Variant& v, const aboria_cells* c) {
-    return v.kind == 3 && all_direct((uint64_t)c->n, largest_system(c));
+    return v.kind == 3 && all_direct((uint64_t)c->n);
 }
 
 // The flattened search forms running sums.  A list that sums by rows (row_split) takes the
@@ -182,7 +182,7 @@ void launch_fwd_variant(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>&
     if (v.kind == 6) launch_mask_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else if (v.kind == 7) launch_half_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else if (takes_flat(v, c)) launch_flat<T, D, OP, BATCH, kFlatModeFwd>(ctx, c, q, a_s, nullptr, y, nullptr, nullptr);
-    else if (v.kind == 3) launch_all_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y, direct_inputs(v, c));
+    else if (v.kind == 3) launch_all_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y, all_eager(largest_system(c)));
     else if (v.kind == 2) launch_nbr_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
     else launch_lane_fwd<T, D, OP, BATCH>(ctx, c, q, a_s, y);
 }
@@ -192,7 +192,7 @@ void launch_bwd_variant(aboria_ctx* ctx, const aboria_cells* c, const OpArgs<T>&
                         T* gx, T* ga, const Variant& v) {
     if (v.kind == 6) launch_mask_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
     else if (takes_flat(v, c)) launch_flat<T, D, OP, BATCH, kFlatModeBwd>(ctx, c, q, a_s, gy_s, nullptr, gx, ga);
-    else if (v.kind == 3) launch_all_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga, direct_inputs(v, c));
+    else if (v.kind == 3) launch_all_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga, all_eager(largest_system(c)));
     else if (v.kind == 2) launch_nbr_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
     else launch_lane_bwd<T, D, OP, BATCH>(ctx, c, q, a_s, gy_s, gx, ga);
 }

@@ -1,6 +1,7 @@
 """All-pairs sums at the edges of their rounds of eight and two candidates, for every number
-of lanes per particle, with inputs read in the caller's order (systems of up to 1024 in
-lists below 4096) and gathered, against the oracle."""
+of lanes per particle, with inputs read in the caller's order (lists below 4096; of every
+candidate in systems of up to 1024, else of the accepted ones) and gathered, against the
+oracle."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +19,7 @@ EDGES = [1, 2, 3, 4, 5, 6, 8, 9, 10, 12, 13, 33, 64, 65, 257]
 @pytest.mark.parametrize("prec", ["f32", "f64"])
 @pytest.mark.parametrize("d", [2, 3])
 @pytest.mark.parametrize("sizes", [EDGES + [1024], EDGES + [1025], [1024], [1025], [320, 321], EDGES * 8, EDGES * 35,
-                                   EDGES * 140], ids=["edges", "gathered", "1024", "1025", "five_each", "16", "4", "1"])
+                                   EDGES * 140], ids=["edges", "accepted", "1024", "1025", "five_each", "16", "4", "1"])
 def test_rounds(sizes, d, prec):
     c = A.Context(0)
     rng = syn.SplitMix64(sum(sizes) + d)
