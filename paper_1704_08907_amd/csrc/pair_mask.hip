@@ -57,40 +57,44 @@ __device__ __forceinline__ void for_each_piece(const SysParams<T>& P, const uint
         else if (c[0] + M >= nx) { a1 = 0; b1 = c[0] + M - nx; s1 = P.L[0]; }
     }
     const int32_t zr = D >= 3 ? 1 : 0, yr = D >= 2 ? 1 : 0;
-    int32_t row = -1;
     // the row and offset loops stay rolled: unrolled, the compiler hoists work
     // across rows and the kernels hold 8 to 9 more registers per lane
 #pragma unroll 1
-    for (int32_t dz = -zr; dz <= zr; ++dz)
+    for (int32_t dz = -zr; dz <= zr; ++dz) {
+        int32_t cz = 0;
+        T sz = T(0);
+        // (once a plane: asked for in every row, its cell and shift cost float64 six registers
+        // and up to a wave per SIMD)
+        const bool ez = D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz);
 #pragma unroll 1
-    for (int32_t dy = -yr; dy <= yr; ++dy) {
-        ++row;
-        if (row < range.first || row >= range.last) continue;
-        int32_t cz = 0, cy = 0;
-        T sz = T(0), sy = T(0);
-        if ((D < 3 || wrap_cell(c[2] + dz, P.n[2], P.periodic[2], P.L[2], &cz, &sz)) &&
-            (D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy))) {
-            const uint32_t rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
-            T sh[3] = {T(0), sy, sz};
-            begin(row);
-            auto run = [&](uint32_t ca, uint32_t cb) { piece(off[ca], min(off[cb + 1], n), sh); };
-            if (wide) {
-                run(rowbase + a0, rowbase + b0);
-                if (b1 >= a1) {
-                    sh[0] = s1;
-                    run(rowbase + a1, rowbase + b1);
-                }
-            } else {
+        for (int32_t dy = -yr; dy <= yr; ++dy) {
+            const int32_t row = (dz + zr) * (2 * yr + 1) + (dy + yr);
+            if (row < range.first || row >= range.last) continue;
+            int32_t cy = 0;
+            T sy = T(0);
+            if (ez && (D < 2 || wrap_cell(c[1] + dy, P.n[1], P.periodic[1], P.L[1], &cy, &sy))) {
+                const uint32_t rowbase = P.cell_base + (uint32_t)nx * ((uint32_t)cy + (uint32_t)P.n[1] * (uint32_t)cz);
+                T sh[3] = {T(0), sy, sz};
+                begin(row);
+                auto run = [&](uint32_t ca, uint32_t cb) { piece(off[ca], min(off[cb + 1], n), sh); };
+                if (wide) {
+                    run(rowbase + a0, rowbase + b0);
+                    if (b1 >= a1) {
+                        sh[0] = s1;
+                        run(rowbase + a1, rowbase + b1);
+                    }
+                } else {
 #pragma unroll 1
-                for (int32_t o = -M; o <= M; ++o) {
-                    int32_t cx;
-                    if (!wrap_cell(c[0] + o, nx, P.periodic[0], P.L[0], &cx, &sh[0])) continue;
-                    run(rowbase + cx, rowbase + cx);
+                    for (int32_t o = -M; o <= M; ++o) {
+                        int32_t cx;
+                        if (!wrap_cell(c[0] + o, nx, P.periodic[0], P.L[0], &cx, &sh[0])) continue;
+                        run(rowbase + cx, rowbase + cx);
+                    }
                 }
+                end(row);
             }
-            end(row);
+            row_done(row);
         }
-        row_done(row);
     }
 }
 
