@@ -313,7 +313,8 @@ int32_t row_waves(const aboria_cells* c) {
 // forms (the fused one, the float64 ones in 3-d, whose LDS then limits the waves) and with a
 // batch's look-up of systems.  Three waves' time in that of one, the slowest of forward,
 // adjoint, record, replay, fused and step kernels (and the plain forward), below and above
-// each line: float64 in 3-d 100003 particles 0.96 (0.71), 130000 1.09 (0.86); batches of
+// each line: float64 in 3-d cells of fewer than seven 100003 particles 0.96 (0.71), 130000
+// 1.12 (0.87), of seven and more 200000 1.01 (0.80), 240000 1.22 (0.90); batches of
 // float32 in 3-d 190000 0.96 (0.83), 262144 1.14 (0.92), in 2-d 190000 1.04 (0.97), of
 // float64 in 2-d 160000 0.97 (0.88), 190000 1.10 (0.97); cells of fewer than four 224000 1.02
 // (0.99), 300007 1.10 (1.09); of four to ten in 3-d 262144 1.01 (0.86), 300007 1.09 (0.94),
@@ -321,11 +322,11 @@ int32_t row_waves(const aboria_cells* c) {
 // the DEM spring's replay, 1.10.
 uint64_t row_sum_waves(const aboria_cells* c) {
     const bool f64 = c->dtype == ABORIA_F64;
-    if (f64 && c->d == 3) return 1600;
-    if (c->nsys > 1) return f64 ? 2500 : 3000;
     // in a cell one cutoff wide, also where the grid's cells are a fraction of it in x: a row
     // is the same run of candidates there, and the lines lie at the same sizes
     const double per_cell = (double)c->n / (double)std::max<int64_t>(c->ncells, 1) * max_reach(c, 0);
+    if (f64 && c->d == 3) return c->nsys == 1 && per_cell >= 7.0 ? 3200 : 1600;
+    if (c->nsys > 1) return f64 ? 2500 : 3000;
     if (per_cell < 4.0) return 3500;
     return per_cell >= 10.0 ? 10000 : (c->d == 3 ? 4200 : 6500);
 }
